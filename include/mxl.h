@@ -311,8 +311,9 @@ mxl_status mxl_bjacobi_info(const mxl_op *P, int64_t *nblocks, double *cond,
  * the previous sweep's factors: s = a_ij - sum_{k<min(i,j)} l_ik u_kj,
  * l_ij = s / u_jj or u_ij = s).  mxl_apply(P, r, z) computes
  * z = U^{-1} L^{-1} r by two triangular solves: trisolve 0 exact
- * substitution (level-scheduled: one launch per dependency level of each
- * triangle), 1 iterative, trs_sweeps Jacobi sweeps per triangle from
+ * substitution (along chains of rows that depend on their neighbour, one
+ * launch per triangle, or, for factors without long chains, one launch per
+ * dependency level), 1 iterative, trs_sweeps Jacobi sweeps per triangle from
  * y = r and z = y / u_ii.  P preconditions GMRES.  A FP64, square, stored
  * (not matrix-free); P keeps a reference to A.  Errors: INVALID_ARG
  * (sweeps or trs_sweeps < 0, trisolve not 0/1, empty A), NOT_IMPLEMENTED,

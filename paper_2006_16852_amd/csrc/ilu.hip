@@ -417,6 +417,7 @@ static unsigned blocks(int64_t n) { return (unsigned)((n + 255) / 256 > 0 ? (n +
 hipError_t ilu_apply(const IluImpl &P, double alpha, const void *r, double beta, void *out, hipStream_t s) {
     const MatrixImpl &A = *P.A;
     const int64_t n = A.nrows;
+    if (P.chain) return ilu_chain_apply(P, alpha, (const double *)r, beta, (double *)out, s);
     const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p;
     const double *lu = (const double *)P.lu->p;
     const int *dpos = (const int *)P.dpos->p;
@@ -700,11 +701,14 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
         std::swap(cur, nxt);
     }
     if ((e = hipGetLastError()) != hipSuccess) return set_error(MXL_ERR_DEVICE, hipGetErrorString(e));
-    // exact solves walk the dependency levels (built on the host); Jacobi
-    // sweeps need only the split layout's slot counts, found on the device
+    // exact solves run along the rows' chains where they form some (planned on
+    // the device: 128^3 convection-diffusion 66 -> 2 ms with the sweeps), else
+    // over the dependency levels (built on the host); Jacobi sweeps need only
+    // the split layout's slot counts, found on the device
     mxl_status lst;
-    if (trisolve == 0 && (lst = ilu_levels(*P)) != MXL_OK) return lst;
-    if (trisolve == 0 && (lst = ilu_pack_levels(*P)) != MXL_OK) return lst;
+    if (trisolve == 0 && (lst = ilu_build_chains(*P)) != MXL_OK) return lst;
+    if (trisolve == 0 && !P->chain && (lst = ilu_levels(*P)) != MXL_OK) return lst;
+    if (trisolve == 0 && !P->chain && (lst = ilu_pack_levels(*P)) != MXL_OK) return lst;
     // Jacobi sweeps read the factors repacked slot-major when the padding
     // stays within 4x the factor storage
     if (trisolve == 1) {

@@ -1,0 +1,676 @@
+// ilu_chain.hip -- exact triangular solves of the ILU-type preconditioner
+// (Sec. 3.2) for factors whose rows form chains, in one launch per triangle
+// without levels.
+//
+// A chain is a maximal run of consecutive rows each of which depends on its
+// neighbour (the row before it in L, the row after it in U); on a grid
+// numbered line by line a chain is a grid line.  The substitution inside a
+// chain is sequential whatever the schedule, so one lane solves one chain and
+// its latest value never leaves a register; all other operands come from
+// lanes that run beside it.  A workgroup owns a group of at most 64 chains:
+//
+//  * One worker wave, lane = chain.  A pass over the wave solves the next row
+//    of every chain whose operands are there.  It touches LDS only: solved
+//    values of the group's own rows, and records that the loaders prepare.
+//  * Loader waves, NL / C lanes per chain, each lane one row ahead of the
+//    other.  A lane loads its row's entries, polls the operands that other
+//    groups produce until they arrive, and writes the row's record: right-hand
+//    side, coefficient of the chain neighbour, and for every other entry a
+//    coefficient and an LDS operand (for an operand of another group the
+//    finished product, with the constant 1 as operand).
+//
+// What bounds it is the dependency chain, not bytes: 382 rows after another
+// on a 128^3 grid (0.27 us each, the worker's pass: two LDS round trips and
+// some 75 instructions) plus the hops from group to group through memory
+// (2 us each: store, poll, record).  Groups are therefore two-dimensional
+// tiles of chains where the numbering allows (8 x 8 grid lines: 30 hops
+// instead of 128).  128^3 convection-diffusion, both triangles: 485 us, of
+// which the level-scheduled launches took 2,740 us (4.3 us per level); with
+// 64 consecutive chains per group 1,050 us.  700^2 5-point: 1,040 us against
+// 5,560 us.
+//
+// Values of other groups are their own flags: y and z are filled with a NaN
+// pattern that no result carries (a result with that pattern is replaced by
+// an ordinary NaN), stored with device-scope atomics as they are solved, and
+// polled until the pattern is gone.
+//
+// No wait can be circular: groups take tickets in solve order, every operand
+// of a group lies in the group itself or in one with an earlier ticket
+// (checked at generation for the tiled order), a ticket is held by a
+// workgroup that runs, and no lane waits inside a branch for another lane of
+// its wave (every pass tries once and goes on).  As a backstop a workgroup
+// that sees no progress for kTrsMaxSpin passes turns its unsolved rows into
+// NaN and ends.
+#include <algorithm>
+#include <climits>
+#include <string>
+#include <vector>
+
+#include "device_common.hpp"
+#include "internal.hpp"
+
+namespace mxl {
+
+constexpr unsigned kTrsWaitHi = 0x7ff4a5a5u;  // a signalling NaN: no arithmetic yields it
+constexpr unsigned long long kTrsWaitBits = 0x7ff4a5a55a5a5a5aull;
+constexpr int kTrsPad = 0x7fffffff;           // code of an empty slot
+constexpr int kTrsMaxSpin = 1 << 26;          // passes without progress: over ten seconds
+constexpr int kTrsLanes = 64;                 // worker lanes = chains of a group
+constexpr int kTrsTJ = 8;                     // tile of chains along the numbering
+constexpr size_t kTrsLdsMax = 158 * 1024;
+
+// Record shapes: entries besides the chain neighbour, loader lanes, ring
+// depth in rows per loader lane.  The narrow shape serves 5- and 7-point
+// patterns, the wide one up to the 12 of a 27-point one.
+constexpr int kTrsNarrow = 3, kTrsWide = 12;
+constexpr int kTrsLoaders = 256;
+
+__device__ __forceinline__ bool trs_ready(double v) { return (unsigned)__double2hiint(v) != kTrsWaitHi; }
+__device__ __forceinline__ double trs_wait() { return __longlong_as_double((long long)kTrsWaitBits); }
+__device__ __forceinline__ double trs_pub(double v) { return trs_ready(v) ? v : (double)__builtin_nan(""); }
+template <typename T>
+__device__ __forceinline__ T lds_get(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ double mem_get(const double *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void mem_put(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One triangle as the kernel reads it.  Entries besides the diagonal and the
+// chain neighbour are slot-major in column order, slot s of row i at
+// s * n_pad + i; code: an operand's column (>= 0: produced by another group,
+// or beyond the group's LDS places), 0x80000000 | its LDS place, or kTrsPad.
+struct TrsView {
+    int64_t n_pad;
+    const int *code;
+    const double *val, *prev, *diag;
+    int w;
+    const int *cstart;       // chain t holds rows cstart[t] .. cstart[t + 1] - 1
+    const int *cbase;        // LDS place of its first solved row
+    const int *glist, *gptr; // group g: chains glist[gptr[g]] .. glist[gptr[g + 1] - 1]
+    int groups, C, cap;
+};
+
+template <bool LOWER, int NE, int NL, int RD>
+constexpr size_t trs_lds_bytes(int cap) {
+    return (size_t)(cap + 1) * 8 + (size_t)NL * RD * (8 + 8 + (LOWER ? 0 : 8) + 12 * NE);
+}
+
+// LOWER: x = L^{-1} b, rows ascending, and znext is filled with the wait
+// pattern for the upper solve.  Otherwise x = U^{-1} b, rows descending, and
+// out = alpha x + beta out.  The arithmetic of a row is the sequential one in
+// column order without contraction.
+template <bool LOWER, int NE, int NL, int RD>
+__global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const double *__restrict__ b, double *x,
+                                                              double *__restrict__ znext, double alpha, double beta,
+                                                              double *__restrict__ out, unsigned *ticket) {
+#pragma clang fp contract(off)
+    extern __shared__ double lds[];
+    __shared__ int s_tk, s_abort;
+    constexpr int NS = NL * RD;  // records
+    const int cap = M.cap, C = M.C, one = cap;
+    // solved values (cap places and the constant 1), then the records
+    double *xl = lds, *rs = xl + cap + 1, *rvp = rs + NS, *rv = rvp + NS, *rd = rv + NE * NS;
+    int *rl = (int *)(rd + (LOWER ? 0 : NS));
+    const int tid = threadIdx.x;
+    if (tid == 0) {
+        s_tk = (int)atomicAdd(ticket, 1u);
+        s_abort = 0;
+    }
+    for (int j = tid; j < cap + 1 + NS; j += kTrsLanes + NL) lds[j] = j == one ? 1.0 : trs_wait();
+    __syncthreads();
+    if (s_tk >= M.groups) return;
+    const int g = LOWER ? s_tk : M.groups - 1 - s_tk;
+    const int q0 = M.gptr[g], nc = M.gptr[g + 1] - q0;
+    const int D = NL / C, RB = D * RD;  // loader lanes and ring slots per chain
+    if (tid >= kTrsLanes) {  // ---------------------------------------- loaders
+        const int lid = tid - kTrsLanes, ch = lid / D, o = lid % D;
+        const bool on = ch < nc;
+        const int t = on ? M.glist[q0 + ch] : 0;
+        const int cs = on ? M.cstart[t] : 0, len = on ? M.cstart[t + 1] - cs : 0;
+        int c[NE], cn[NE];  // the row in hand and, already under way, the lane's next one
+        double v[NE], vn[NE], xr[NE];
+        double s = 0.0, sn = 0.0, d = 1.0, dn = 1.0, vp = 0.0, vpn = 0.0;
+        unsigned need = 0;  // operands not yet seen
+        int p = o;
+        auto fetch = [&](int pp) {
+            if (pp < len) {
+                const int i = LOWER ? cs + pp : cs + len - 1 - pp;
+#pragma unroll
+                for (int m = 0; m < NE; ++m) {
+                    cn[m] = m < M.w ? M.code[(int64_t)m * M.n_pad + i] : kTrsPad;
+                    vn[m] = m < M.w ? M.val[(int64_t)m * M.n_pad + i] : 0.0;
+                }
+                vpn = M.prev[i];
+                sn = b[i];
+                if (!LOWER) dn = M.diag[i];
+            }
+        };
+        auto take = [&]() {
+            need = 0;
+#pragma unroll
+            for (int m = 0; m < NE; ++m) {
+                c[m] = cn[m];
+                v[m] = vn[m];
+                if (c[m] >= 0 && c[m] != kTrsPad) need |= 1u << m;
+                xr[m] = 1.0;
+            }
+            s = sn;
+            d = dn;
+            vp = vpn;
+        };
+        bool act = p < len;
+        fetch(p);
+        if (act) take();
+        fetch(p + D);
+        int spins = 0;
+        while (__any(act)) {
+            double xp[NE];
+#pragma unroll
+            for (int m = 0; m < NE; ++m) xp[m] = act && (need >> m & 1) ? mem_get(x + c[m]) : trs_wait();
+            // ring slots row by row over the chains: the worker's lanes read neighbouring ones
+            const int idx = act ? (p & (RB - 1)) * C + ch : 0;
+            const bool empty = act && !trs_ready(lds_get(rs + idx));
+#pragma unroll
+            for (int m = 0; m < NE; ++m)
+                if (trs_ready(xp[m])) {
+                    xr[m] = xp[m];
+                    need &= ~(1u << m);
+                }
+            const bool pub = act && need == 0 && empty;
+            if (pub) {
+#pragma unroll
+                for (int m = 0; m < NE; ++m) {
+                    const bool pad = c[m] == kTrsPad, loc = c[m] < 0;
+                    lds_put(rl + m * NS + idx, loc ? c[m] & kTrsPad : one);
+                    lds_put(rv + m * NS + idx, pad ? 0.0 : loc ? v[m] : v[m] * xr[m]);
+                }
+                lds_put(rvp + idx, vp);
+                if (!LOWER) lds_put(rd + idx, d);
+                // the right-hand side is the record's flag: written last
+                __hip_atomic_store(rs + idx, trs_pub(s), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+                p += D;
+                act = p < len;
+                if (act) take();
+                fetch(p + D);
+                spins = 0;
+            }
+            if (!__any(pub)) {
+                if (++spins > kTrsMaxSpin) lds_put(&s_abort, 1);
+                if (lds_get(&s_abort)) break;
+            }
+        }
+        return;
+    }
+    // ------------------------------------------------------------- the worker
+    __builtin_amdgcn_s_setprio(3);  // its passes are the critical path
+    const bool on = tid < nc;
+    const int t = on ? M.glist[q0 + tid] : 0;
+    const int cs = on ? M.cstart[t] : 0, len = on ? M.cstart[t + 1] - cs : 0;
+    int pl = on ? M.cbase[t] : 0;
+    int p = 0, spins = 0;
+    int i = LOWER ? cs : cs + len - 1;
+    int idx = on ? tid : 0;
+    double yprev = 0.0;
+    bool act = p < len;
+    // the loads above are done: without this the loop waits for all its own
+    // stores in every pass (vmcnt 0, the other counters untouched)
+    __builtin_amdgcn_s_waitcnt(0xF70);
+    while (__any(act)) {
+        // the flag first: LDS serves a wave in order, so a record read after
+        // a set flag is whole
+        double s = lds_get(rs + idx);
+        int l[NE];
+        double xv[NE], vv[NE];
+#pragma unroll
+        for (int m = 0; m < NE; ++m) l[m] = lds_get(rl + m * NS + idx);
+#pragma unroll
+        for (int m = 0; m < NE; ++m) vv[m] = lds_get(rv + m * NS + idx);
+        const double vp = lds_get(rvp + idx);
+        double dd = 1.0;
+        if (!LOWER) dd = lds_get(rd + idx);
+        bool ok = act && trs_ready(s);
+#pragma unroll
+        for (int m = 0; m < NE; ++m) xv[m] = lds_get(xl + (ok ? l[m] : one));
+#pragma unroll
+        for (int m = 0; m < NE; ++m) ok = ok && trs_ready(xv[m]);
+        // column order: the neighbour is the last entry of L, the first of U;
+        // a chain's first row has none (coefficient and yprev are 0)
+        if (!LOWER) s = s - vp * yprev;
+#pragma unroll
+        for (int m = 0; m < NE; ++m) s = s - vv[m] * xv[m];
+        if (LOWER) s = s - vp * yprev;
+        if (ok) {
+            if (!LOWER) s = s / dd;
+            yprev = trs_pub(s);
+            if (pl < cap) lds_put(xl + pl, yprev);
+            mem_put(x + i, yprev);
+            lds_put(rs + idx, trs_wait());  // the slot is free again
+            if (LOWER) {
+                znext[i] = trs_wait();
+            } else if (beta == 0.0) {
+                out[i] = alpha * yprev;
+            } else {
+                out[i] = alpha * yprev + beta * out[i];
+            }
+            ++p;
+            ++pl;
+            i += LOWER ? 1 : -1;
+            act = p < len;
+            idx = act ? (p & (RB - 1)) * C + tid : 0;
+            spins = 0;
+        }
+        if (!__any(ok)) {
+            if (++spins > kTrsMaxSpin) lds_put(&s_abort, 1);
+            if (lds_get(&s_abort)) break;
+        }
+    }
+    for (; p < len; ++p, i += LOWER ? 1 : -1) {  // the backstop: also ends the waits of later groups
+        mem_put(x + i, (double)__builtin_nan(""));
+        if (LOWER) znext[i] = trs_wait();
+        else out[i] = (double)__builtin_nan("");
+    }
+}
+
+__global__ void k_trs_begin(int64_t n, double *__restrict__ y, unsigned *tickets) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 2) tickets[i] = 0;
+    if (i < n) y[i] = trs_wait();
+}
+
+// ------------------------------------------------------------ generation
+// Row i opens a chain: in L when it has no entry i - 1, in U when row i - 1
+// has no entry i (chains are listed by ascending rows in both).
+__device__ __forceinline__ bool trs_head(bool lower, int64_t i, const int *__restrict__ rp,
+                                         const int *__restrict__ col, const int *__restrict__ dpos) {
+    if (i == 0) return true;
+    if (lower) return !(dpos[i] > rp[i] && col[dpos[i] - 1] == (int)i - 1);
+    return !(dpos[i - 1] + 1 < rp[i] && col[dpos[i - 1] + 1] == (int)i);
+}
+
+constexpr int kTrsScan = 1024;  // rows per workgroup of the two scan passes
+
+__global__ __launch_bounds__(kWG) void k_trs_count(int64_t n, int lower, const int *__restrict__ rp,
+                                                   const int *__restrict__ col, const int *__restrict__ dpos,
+                                                   int *__restrict__ sums) {
+    __shared__ int part[kWG / kWave];
+    int h = 0;
+    for (int e = 0; e < kTrsScan / kWG; ++e) {
+        const int64_t i = (int64_t)blockIdx.x * kTrsScan + e * kWG + threadIdx.x;
+        if (i < n) h += trs_head(lower, i, rp, col, dpos);
+    }
+    h = wave_sum(h);
+    if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = h;
+    __syncthreads();
+    if (threadIdx.x == 0) sums[blockIdx.x] = part[0] + part[1] + part[2] + part[3];
+}
+
+// Inclusive sum over the workgroup's 256 threads.
+__device__ __forceinline__ int trs_block_scan(int v, int *part) {
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int u = __shfl_up(v, d, kWave);
+        if (lane >= d) v += u;
+    }
+    __syncthreads();
+    if (lane == kWave - 1) part[wid] = v;
+    __syncthreads();
+    for (int k = 0; k < wid; ++k) v += part[k];
+    return v;
+}
+
+// Exclusive sums in place (one workgroup); the total goes to sums[nb].
+__global__ __launch_bounds__(kWG) void k_trs_scan(int nb, int *sums) {
+    __shared__ int part[kWG / kWave];
+    __shared__ int carry;
+    if (threadIdx.x == 0) carry = 0;
+    __syncthreads();
+    for (int b0 = 0; b0 < nb; b0 += kWG) {
+        const int b = b0 + threadIdx.x;
+        const int v = b < nb ? sums[b] : 0;
+        const int s = trs_block_scan(v, part) + carry;
+        if (b < nb) sums[b] = s - v;
+        __syncthreads();
+        if (threadIdx.x == kWG - 1) carry = s;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) sums[nb] = carry;
+}
+
+// Chain of every row and first row of every chain (cstart[nch] = n).
+__global__ __launch_bounds__(kWG) void k_trs_chains(int64_t n, int lower, const int *__restrict__ rp,
+                                                    const int *__restrict__ col, const int *__restrict__ dpos,
+                                                    const int *__restrict__ sums, int nb, int *__restrict__ rowchain,
+                                                    int *__restrict__ cstart) {
+    __shared__ int part[kWG / kWave];
+    __shared__ int carry;
+    if (threadIdx.x == 0) carry = sums[blockIdx.x];
+    __syncthreads();
+    for (int e = 0; e < kTrsScan / kWG; ++e) {
+        const int64_t i = (int64_t)blockIdx.x * kTrsScan + e * kWG + threadIdx.x;
+        const int h = i < n ? (int)trs_head(lower, i, rp, col, dpos) : 0;
+        const int s = trs_block_scan(h, part) + carry;
+        if (i < n) {
+            rowchain[i] = s - 1;
+            if (h) cstart[s - 1] = (int)i;
+        }
+        __syncthreads();
+        if (threadIdx.x == kWG - 1) carry = s;
+        __syncthreads();
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) cstart[sums[nb]] = (int)n;
+}
+
+// Entries of row i's triangle besides the chain neighbour, in column order.
+template <typename F>
+__device__ __forceinline__ void trs_entries(bool lower, int i, const int *__restrict__ rp,
+                                            const int *__restrict__ col, const int *__restrict__ dpos, F f) {
+    const int q0 = lower ? rp[i] : dpos[i] + 1, q1 = lower ? dpos[i] : rp[i + 1];
+    const int nb = lower ? i - 1 : i + 1;
+    for (int q = q0; q < q1; ++q)
+        if (col[q] != nb) f(q, col[q]);
+}
+
+// st[0]: the widest row; st[1], st[2]: smallest and largest distance, in
+// chains, of an operand more than one chain away.
+__global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const int *__restrict__ rp,
+                                                   const int *__restrict__ col, const int *__restrict__ dpos,
+                                                   const int *__restrict__ rowchain, int *st) {
+    int w = 0, lo = INT_MAX, hi = 0;
+    for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += (int64_t)gridDim.x * kWG) {
+        int a = 0;
+        const int me = rowchain[i];
+        trs_entries(lower, (int)i, rp, col, dpos, [&](int, int c) {
+            ++a;
+            const int o = abs(me - rowchain[c]);
+            if (o > 1) {
+                lo = o < lo ? o : lo;
+                hi = o > hi ? o : hi;
+            }
+        });
+        w = a > w ? a : w;
+    }
+    w = wave_max(w);
+    hi = wave_max(hi);
+    lo = -wave_max(-lo);
+    if (threadIdx.x % kWave == 0) {
+        atomicMax(st, w);
+        atomicMin(st + 1, lo);
+        atomicMax(st + 2, hi);
+    }
+}
+
+// *bad = 1 when an operand's tile is not at or before its row's tile in both
+// tile coordinates (chain t = (t % W, t / W), columns skewed by the row).
+__global__ void k_trs_order(int64_t n, int lower, const int *__restrict__ rp, const int *__restrict__ col,
+                            const int *__restrict__ dpos, const int *__restrict__ rowchain, int W, int skew, int TK,
+                            int *bad) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    auto tj = [&](int t) { return (t % W + skew * (t / W)) / kTrsTJ; };
+    auto tk = [&](int t) { return (t / W) / TK; };
+    const int me = rowchain[i];
+    bool wrong = false;
+    trs_entries(lower, (int)i, rp, col, dpos, [&](int, int c) {
+        const int ot = rowchain[c];
+        const int first = lower ? ot : me, then = lower ? me : ot;  // ascending numbering
+        wrong = wrong || tj(first) > tj(then) || tk(first) > tk(then);
+    });
+    if (wrong) atomicOr(bad, 1);
+}
+
+// Places of a group's chains (one after the other) and each chain's group;
+// *most = the largest group's rows.
+__global__ void k_trs_places(int groups, const int *__restrict__ gptr, const int *__restrict__ glist,
+                             const int *__restrict__ cstart, int *__restrict__ cbase, int *__restrict__ cgroup,
+                             int *most) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= groups) return;
+    int64_t rows = 0;
+    for (int q = gptr[g]; q < gptr[g + 1]; ++q) {
+        const int t = glist[q];
+        cbase[t] = (int)(rows < INT_MAX ? rows : INT_MAX);
+        cgroup[t] = g;
+        rows += cstart[t + 1] - cstart[t];
+    }
+    atomicMax(most, (int)(rows < INT_MAX ? rows : INT_MAX));
+}
+
+__global__ void k_trs_encode(int64_t n, int64_t n_pad, int lower, int w, int cap, const int *__restrict__ rp,
+                             const int *__restrict__ col, const int *__restrict__ dpos,
+                             const double *__restrict__ lu, const int *__restrict__ rowchain,
+                             const int *__restrict__ cstart, const int *__restrict__ cbase,
+                             const int *__restrict__ cgroup, int *__restrict__ code, double *__restrict__ val,
+                             double *__restrict__ prev, double *__restrict__ diag) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int g = cgroup[rowchain[i]];
+    int a = 0;
+    trs_entries(lower, (int)i, rp, col, dpos, [&](int q, int c) {
+        const int t = rowchain[c];
+        int e = c;
+        if (cgroup[t] == g) {
+            const int64_t pl = (int64_t)cbase[t] + (lower ? c - cstart[t] : cstart[t + 1] - 1 - c);
+            if (pl < cap) e = (int)((unsigned)pl | 0x80000000u);
+        }
+        code[(int64_t)a * n_pad + i] = e;
+        val[(int64_t)a * n_pad + i] = lu[q];
+        ++a;
+    });
+    for (; a < w; ++a) {
+        code[(int64_t)a * n_pad + i] = kTrsPad;
+        val[(int64_t)a * n_pad + i] = 0.0;
+    }
+    const int nbq = lower ? dpos[i] - 1 : dpos[i] + 1;
+    const bool has = lower ? nbq >= rp[i] && col[nbq] == (int)i - 1 : nbq < rp[i + 1] && col[nbq] == (int)i + 1;
+    prev[i] = has ? lu[nbq] : 0.0;
+    if (diag) diag[i] = lu[dpos[i]];
+}
+
+namespace {
+
+BufPtr trs_buf(size_t bytes) {
+    auto d = std::make_shared<DevBuf>();
+    if (hipMalloc(&d->p, bytes ? bytes : 16) != hipSuccess) return BufPtr();
+    d->bytes = bytes;
+    d->owned = true;
+    return d;
+}
+
+unsigned trs_grid(int64_t n, int per) { return (unsigned)((n + per - 1) / per > 0 ? (n + per - 1) / per : 1); }
+
+#define TRS_TRY(expr, what)                                                                                    \
+    do {                                                                                                       \
+        const hipError_t e_ = (expr);                                                                          \
+        if (e_ != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string(what ": ") + hipGetErrorString(e_)); \
+    } while (0)
+
+// Groups of chains: 8 x TK tiles of the chains (t % W, t / W) in row-major
+// tile order, or (W = 0) C consecutive chains each.
+void trs_groups(int nch, int C, int W, int skew, int TK, std::vector<int> &glist, std::vector<int> &gptr) {
+    glist.resize((size_t)nch);
+    gptr.assign(1, 0);
+    if (W == 0) {
+        for (int t = 0; t < nch; ++t) glist[(size_t)t] = t;
+        for (int t = C; t < nch; t += C) gptr.push_back(t);
+        gptr.push_back(nch);
+        return;
+    }
+    const int64_t K = (nch - 1) / W, NJ = ((int64_t)W - 1 + skew * K) / kTrsTJ + 1, NK = K / TK + 1;
+    auto tile = [&](int t) { return ((int64_t)(t / W) / TK) * NJ + (t % W + (int64_t)skew * (t / W)) / kTrsTJ; };
+    std::vector<int> at((size_t)(NJ * NK) + 1, 0);
+    for (int t = 0; t < nch; ++t) ++at[(size_t)tile(t) + 1];
+    for (size_t q = 1; q < at.size(); ++q) {
+        at[q] += at[q - 1];
+        if (at[q] > at[q - 1]) gptr.push_back(at[q]);
+    }
+    for (int t = 0; t < nch; ++t) glist[(size_t)at[(size_t)tile(t)]++] = t;
+}
+
+// Plans and packs one triangle; ok = false (and no error) when its rows do
+// not suit the chain solve.
+mxl_status trs_build(IluImpl &P, bool lower, TrsSide &T, bool &ok) {
+    const MatrixImpl &A = *P.A;
+    const int64_t n = A.nrows;
+    hipStream_t s = A.ctx->stream;
+    const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p, *dpos = (const int *)P.dpos->p;
+    const int nb = (int)trs_grid(n, kTrsScan);
+    ok = false;
+    BufPtr sums = trs_buf((size_t)(nb + 1) * 4), rowchain = trs_buf((size_t)n * 4), st = trs_buf(16);
+    BufPtr cstart = trs_buf((size_t)(n + 1) * 4);
+    if (!sums || !rowchain || !st || !cstart) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve plan");
+    int h[4] = {0, INT_MAX, 0, 0}, nch = 0;
+    TRS_TRY(hipMemcpyAsync(st->p, h, 16, hipMemcpyHostToDevice, s), "triangular solve plan");
+    hipLaunchKernelGGL(k_trs_count, dim3(nb), dim3(kWG), 0, s, n, (int)lower, rp, col, dpos, (int *)sums->p);
+    hipLaunchKernelGGL(k_trs_scan, dim3(1), dim3(kWG), 0, s, nb, (int *)sums->p);
+    hipLaunchKernelGGL(k_trs_chains, dim3(nb), dim3(kWG), 0, s, n, (int)lower, rp, col, dpos, (const int *)sums->p,
+                       nb, (int *)rowchain->p, (int *)cstart->p);
+    hipLaunchKernelGGL(k_trs_stats, dim3(std::min(trs_grid(n, kWG), 2048u)), dim3(kWG), 0, s, n, (int)lower, rp, col,
+                       dpos, (const int *)rowchain->p, (int *)st->p);
+    TRS_TRY(hipGetLastError(), "triangular solve plan");
+    TRS_TRY(hipMemcpyAsync(h, st->p, 16, hipMemcpyDeviceToHost, s), "triangular solve plan");
+    TRS_TRY(hipMemcpyAsync(&nch, (int *)sums->p + nb, 4, hipMemcpyDeviceToHost, s), "triangular solve plan");
+    TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
+    const int w = h[0];
+    // Chains shorter than 8 rows on average keep the worker's lanes waiting
+    // for records, and rows wider than a record do not fit it: such factors
+    // (random patterns, node blocks) have few levels, which the level
+    // launches serve.
+    if (nch < 1 || n / nch < 8 || w > kTrsWide) return MXL_OK;
+    const bool wide = w > kTrsNarrow;
+    const size_t rec = wide ? trs_lds_bytes<false, kTrsWide, kTrsLoaders, 1>(0)
+                            : trs_lds_bytes<false, kTrsNarrow, kTrsLoaders, 2>(0);
+    const int places = (int)((kTrsLdsMax - rec) / 8) - 1;
+    // As many chains per group as its LDS holds (fewer hops between groups):
+    // 64 of 128 rows take 64 KB.
+    int C = kTrsLanes;
+    while (C > 4 && (int64_t)C * (n / nch) > places - places / 8) C /= 2;
+    int W = 0, skew = 0;
+    const int TK = C / kTrsTJ;
+    if (TK > 1 && h[2] > 0) {  // operands further than one chain away: a plane of chains lies between
+        const int mid = (int)(((int64_t)h[1] + h[2]) / 2), sk = mid - h[1];
+        if (mid >= kTrsTJ && mid < nch && sk <= 4 && (int64_t)nch / mid * sk <= 8 * (int64_t)mid) {
+            W = mid;
+            skew = sk;
+            int zero = 0;
+            TRS_TRY(hipMemcpyAsync((int *)st->p + 3, &zero, 4, hipMemcpyHostToDevice, s), "triangular solve plan");
+            hipLaunchKernelGGL(k_trs_order, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, (int)lower, rp, col, dpos,
+                               (const int *)rowchain->p, W, skew, TK, (int *)st->p + 3);
+            int bad = 1;
+            TRS_TRY(hipMemcpyAsync(&bad, (int *)st->p + 3, 4, hipMemcpyDeviceToHost, s), "triangular solve plan");
+            TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
+            if (bad) W = 0;
+        }
+    }
+    std::vector<int> glist, gptr;
+    trs_groups(nch, C, W, skew, TK, glist, gptr);
+    T.groups = (int)gptr.size() - 1;
+    T.C = C;
+    T.w = w;
+    P.n_pad = (n + 63) / 64 * 64;
+    BufPtr cgroup = trs_buf((size_t)nch * 4);
+    T.cstart = trs_buf((size_t)(nch + 1) * 4);
+    T.cbase = trs_buf((size_t)nch * 4);
+    T.glist = trs_buf((size_t)nch * 4);
+    T.gptr = trs_buf(gptr.size() * 4);
+    T.code = trs_buf((size_t)w * P.n_pad * 4);
+    T.val = trs_buf((size_t)w * P.n_pad * 8);
+    T.prev = trs_buf((size_t)n * 8);
+    if (!lower) P.udiag = trs_buf((size_t)n * 8);
+    if (!cgroup || !T.cstart || !T.cbase || !T.glist || !T.gptr || !T.code || !T.val || !T.prev ||
+        (!lower && !P.udiag))
+        return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve factors");
+    int most = 0;
+    TRS_TRY(hipMemcpyAsync(T.cstart->p, cstart->p, (size_t)(nch + 1) * 4, hipMemcpyDeviceToDevice, s), "chains");
+    TRS_TRY(hipMemcpyAsync(T.glist->p, glist.data(), glist.size() * 4, hipMemcpyHostToDevice, s), "chain groups");
+    TRS_TRY(hipMemcpyAsync(T.gptr->p, gptr.data(), gptr.size() * 4, hipMemcpyHostToDevice, s), "chain groups");
+    TRS_TRY(hipMemcpyAsync(st->p, &most, 4, hipMemcpyHostToDevice, s), "chain groups");
+    hipLaunchKernelGGL(k_trs_places, dim3(trs_grid(T.groups, 64)), dim3(64), 0, s, T.groups, (const int *)T.gptr->p,
+                       (const int *)T.glist->p, (const int *)T.cstart->p, (int *)T.cbase->p, (int *)cgroup->p,
+                       (int *)st->p);
+    TRS_TRY(hipMemcpyAsync(&most, st->p, 4, hipMemcpyDeviceToHost, s), "chain groups");
+    TRS_TRY(hipStreamSynchronize(s), "chain groups");
+    T.cap = std::min(most, places);
+    hipLaunchKernelGGL(k_trs_encode, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, P.n_pad, (int)lower, w, T.cap, rp,
+                       col, dpos, (const double *)P.lu->p, (const int *)rowchain->p, (const int *)T.cstart->p,
+                       (const int *)T.cbase->p, (const int *)cgroup->p, (int *)T.code->p, (double *)T.val->p,
+                       (double *)T.prev->p, lower ? nullptr : (double *)P.udiag->p);
+    TRS_TRY(hipGetLastError(), "triangular solve factors");
+    TRS_TRY(hipStreamSynchronize(s), "triangular solve factors");  // the plan's temporaries end here
+    ok = true;
+    return MXL_OK;
+}
+
+template <int NE, int RD>
+hipError_t trs_allow_lds() {
+    const int v = (int)kTrsLdsMax;
+    hipError_t e = hipFuncSetAttribute((const void *)k_trs_chain<true, NE, kTrsLoaders, RD>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, v);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_trs_chain<false, NE, kTrsLoaders, RD>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, v);
+    return e;
+}
+
+TrsView trs_view(const IluImpl &P, const TrsSide &T, bool lower) {
+    TrsView M;
+    M.n_pad = P.n_pad;
+    M.code = (const int *)T.code->p;
+    M.val = (const double *)T.val->p;
+    M.prev = (const double *)T.prev->p;
+    M.diag = lower ? nullptr : (const double *)P.udiag->p;
+    M.w = T.w;
+    M.cstart = (const int *)T.cstart->p;
+    M.cbase = (const int *)T.cbase->p;
+    M.glist = (const int *)T.glist->p;
+    M.gptr = (const int *)T.gptr->p;
+    M.groups = T.groups;
+    M.C = T.C;
+    M.cap = T.cap;
+    return M;
+}
+
+template <bool LOWER, int NE, int RD>
+void trs_launch(const TrsView &M, const double *b, double *x, double *znext, double alpha, double beta, double *out,
+                unsigned *ticket, hipStream_t s) {
+    hipLaunchKernelGGL((k_trs_chain<LOWER, NE, kTrsLoaders, RD>), dim3(M.groups), dim3(kTrsLanes + kTrsLoaders),
+                       (trs_lds_bytes<LOWER, NE, kTrsLoaders, RD>(M.cap)), s, M, b, x, znext, alpha, beta, out, ticket);
+}
+
+}  // namespace
+
+mxl_status ilu_build_chains(IluImpl &P) {
+    bool ok = false;
+    mxl_status st = trs_build(P, true, P.lo, ok);
+    if (st != MXL_OK || !ok) return st;
+    if ((st = trs_build(P, false, P.up, ok)) != MXL_OK || !ok) return st;
+    P.tickets = trs_buf(8);
+    if (!P.tickets) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve tickets");
+    TRS_TRY((trs_allow_lds<kTrsNarrow, 2>()), "LDS attribute");
+    TRS_TRY((trs_allow_lds<kTrsWide, 1>()), "LDS attribute");
+    P.chain = true;
+    return MXL_OK;
+}
+
+hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, double beta, double *out, hipStream_t s) {
+    const int64_t n = P.A->nrows;
+    double *y = (double *)P.y->p, *z = (double *)P.z->p;
+    unsigned *tk = (unsigned *)P.tickets->p;
+    const TrsView L = trs_view(P, P.lo, true), U = trs_view(P, P.up, false);
+    hipLaunchKernelGGL(k_trs_begin, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, y, tk);
+    if (L.w > kTrsNarrow) trs_launch<true, kTrsWide, 1>(L, r, y, z, 1.0, 0.0, nullptr, tk, s);
+    else trs_launch<true, kTrsNarrow, 2>(L, r, y, z, 1.0, 0.0, nullptr, tk, s);
+    if (U.w > kTrsNarrow) trs_launch<false, kTrsWide, 1>(U, y, z, nullptr, alpha, beta, out, tk + 1, s);
+    else trs_launch<false, kTrsNarrow, 2>(U, y, z, nullptr, alpha, beta, out, tk + 1, s);
+    return hipGetLastError();
+}
+
+}  // namespace mxl

@@ -128,6 +128,13 @@ struct JacobiImpl {
     std::vector<int32_t> bptr_h;
 };
 
+// One triangle of an ILU preconditioner packed for the chain solve
+// (ilu_chain.hip): entries, chains and the groups of chains.
+struct TrsSide {
+    BufPtr code, val, prev, cstart, cbase, glist, gptr;
+    int w = 0, groups = 0, C = 0, cap = 0;
+};
+
 // ILU-type preconditioner: factors on A's pattern (strict lower = L with
 // unit diagonal, the rest = U), diagonal positions, dependency levels of
 // both triangles (rows listed level by level) and three work vectors.
@@ -136,7 +143,11 @@ struct IluImpl {
     int sweeps = 0, trisolve = 0, trs_sweeps = 0;
     BufPtr lu, dpos, lperm, uperm, y, t, z;
     std::vector<int64_t> lptr, uptr;
-    // exact solves: the level offsets on the device (runs of small levels are
+    // exact solves of factors whose rows form chains: no levels are built
+    bool chain = false;
+    TrsSide lo, up;
+    BufPtr tickets;
+    // other exact solves: the level offsets on the device (runs of small levels are
     // solved by one workgroup in one launch) and the schedule of launches
     BufPtr lptr_d, uptr_d;
     std::vector<int2> lruns, uruns;  // (first level, end level): a run of small levels, or one level
@@ -347,6 +358,11 @@ hipError_t gm_small(int n, int m, const int *rp, const int *col, const double *v
 // ------------------------------------------------------------- ilu.hip
 // out = alpha U^{-1} L^{-1} r + beta out (beta == 0 overwrites)
 hipError_t ilu_apply(const IluImpl &P, double alpha, const void *r, double beta, void *out, hipStream_t s);
+
+// ------------------------------------------------------- ilu_chain.hip
+// Packs both triangles for the chain solve and sets P.chain when they suit it.
+mxl_status ilu_build_chains(IluImpl &P);
+hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, double beta, double *out, hipStream_t s);
 
 // ------------------------------------------------------------- runtime.hip
 mxl_status set_error(mxl_status st, const std::string &msg);
