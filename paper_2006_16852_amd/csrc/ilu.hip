@@ -658,21 +658,18 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     P->sweeps = sweeps;
     P->trisolve = trisolve;
     P->trs_sweeps = trs_sweeps;
-    auto mk = [&](size_t bytes) {
-        auto d = std::make_shared<DevBuf>();
-        if (hipMalloc(&d->p, bytes ? bytes : 16) != hipSuccess) return BufPtr();
-        d->bytes = bytes;
-        d->owned = true;
-        return d;
-    };
-    BufPtr row = mk((size_t)nnz * 4), old = mk((size_t)nnz * 8), bad = mk(4);
-    P->lu = mk((size_t)nnz * 8);
-    P->dpos = mk((size_t)n * 4);
-    P->y = mk((size_t)n * 8);
-    P->t = mk((size_t)n * 8);
-    P->z = mk((size_t)n * 8);
-    if (!row || !old || !bad || !P->lu || !P->dpos || !P->y || !P->t || !P->z)
-        return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
+    BufPtr row, old, bad, w2;
+    Arena tmp, keep;
+    tmp.want(row, (size_t)nnz * 4);
+    tmp.want(old, (size_t)nnz * 8);
+    tmp.want(bad, 4);
+    tmp.want(w2, 8);
+    keep.want(P->lu, (size_t)nnz * 8);
+    keep.want(P->dpos, (size_t)n * 4);
+    keep.want(P->y, (size_t)n * 8);
+    keep.want(P->t, (size_t)n * 8);
+    keep.want(P->z, (size_t)n * 8);
+    if (!tmp.alloc() || !keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
     const int *rp = (const int *)A->row_ptr->p, *col = (const int *)A->col->p;
     const double *val = (const double *)A->val->p;
     int none = INT_MAX, hb = INT_MAX;
@@ -702,7 +699,7 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     }
     if ((e = hipGetLastError()) != hipSuccess) return set_error(MXL_ERR_DEVICE, hipGetErrorString(e));
     // exact solves run along the rows' chains where they form some (planned on
-    // the device: 128^3 convection-diffusion 66 -> 2 ms with the sweeps), else
+    // the device, no host copy of the matrix: a new 101^3 system 33 -> 2.3 ms), else
     // over the dependency levels (built on the host); Jacobi sweeps need only
     // the split layout's slot counts, found on the device
     mxl_status lst;
@@ -712,9 +709,7 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     // Jacobi sweeps read the factors repacked slot-major when the padding
     // stays within 4x the factor storage
     if (trisolve == 1) {
-        auto w2 = mk(8);
         int zero2[2] = {0, 0}, hw[2] = {0, 0};
-        if (!w2) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU widths");
         if (hipMemcpyAsync(w2->p, zero2, 8, hipMemcpyHostToDevice, s) != hipSuccess)
             return set_error(MXL_ERR_DEVICE, "ILU widths init");
         hipLaunchKernelGGL(k_ilu_widths, dim3((unsigned)std::min<int64_t>(blocks(n), 2048)), dim3(256), 0, s, n, rp,
@@ -727,12 +722,12 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
             P->wl = wl;
             P->wu = wu;
             P->n_pad = n_pad;
-            P->lcol = mk((size_t)wl * n_pad * 4);
-            P->lval = mk((size_t)wl * n_pad * 8);
-            P->ucol = mk((size_t)wu * n_pad * 4);
-            P->uval = mk((size_t)wu * n_pad * 8);
-            P->udiag = mk((size_t)n * 8);
-            if (!P->lcol || !P->lval || !P->ucol || !P->uval || !P->udiag)
+            keep.want(P->lcol, (size_t)wl * n_pad * 4);
+            keep.want(P->lval, (size_t)wl * n_pad * 8);
+            keep.want(P->ucol, (size_t)wu * n_pad * 4);
+            keep.want(P->uval, (size_t)wu * n_pad * 8);
+            keep.want(P->udiag, (size_t)n * 8);
+            if (!keep.alloc())
                 return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU split factors");
             hipLaunchKernelGGL(k_ilu_split, dim3(blocks(n)), dim3(256), 0, s, n, n_pad, rp, col,
                                (const double *)P->lu->p, wl, wu, (int *)P->lcol->p, (double *)P->lval->p,

@@ -286,6 +286,80 @@ __global__ void k_trs_begin(int64_t n, double *__restrict__ y, unsigned *tickets
 }
 
 // ------------------------------------------------------------ generation
+// What the plan of one triangle is made from, gathered on the device.
+struct TrsInfo {
+    int w;       // widest row (entries besides the diagonal and the chain neighbour)
+    int lo, hi;  // smallest and largest distance, in chains, of an operand more than one chain away
+    int longest; // rows of the longest chain
+    int nch;     // chains
+    int bad;     // 1: two-dimensional tiles would not be in solve order
+};
+
+// The groups of a triangle: `groups` runs of C consecutive chains, or (W > 0)
+// tiles of kTrsTJ x TK chains of the chains laid out as (t % W, t / W), the
+// columns shifted by skew per row, tile rows of NJ tiles.
+struct TrsPlan {
+    int ok, wide, places, C, W, skew, TK, NJ, groups;
+};
+
+__host__ __device__ inline void trs_count_groups(TrsPlan &p, int nch) {
+    if (p.W == 0) {
+        p.NJ = 0;
+        p.groups = (nch + p.C - 1) / p.C;
+        return;
+    }
+    const int K = (nch - 1) / p.W;
+    p.NJ = (p.W - 1 + p.skew * K) / kTrsTJ + 1;
+    p.groups = p.NJ * (K / p.TK + 1);
+}
+
+__host__ __device__ inline TrsPlan trs_plan(int64_t n, const TrsInfo &f) {
+    TrsPlan p{};
+    // Chains shorter than 8 rows on average keep the worker's lanes waiting
+    // for records, and rows wider than a record do not fit it: such factors
+    // (random patterns, node blocks) have few levels, which the level
+    // launches serve.
+    p.ok = f.nch >= 1 && n / f.nch >= 8 && f.w <= kTrsWide;
+    if (!p.ok) return p;
+    p.wide = f.w > kTrsNarrow;
+    const size_t rec = p.wide ? trs_lds_bytes<false, kTrsWide, kTrsLoaders, 1>(0)
+                              : trs_lds_bytes<false, kTrsNarrow, kTrsLoaders, 2>(0);
+    p.places = (int)((kTrsLdsMax - rec) / 8) - 1;
+    // As many chains per group as its LDS holds (fewer hops between groups):
+    // 64 of 128 rows take 64 KB.
+    p.C = kTrsLanes;
+    while (p.C > 4 && (int64_t)p.C * (n / f.nch) > p.places - p.places / 8) p.C /= 2;
+    p.TK = p.C / kTrsTJ;
+    if (p.TK > 1 && f.hi > 0) {  // operands further than one chain away: a plane of chains lies between
+        const int mid = (int)(((int64_t)f.lo + f.hi) / 2), sk = mid - f.lo;
+        if (mid >= kTrsTJ && mid < f.nch && sk <= 4 && (int64_t)f.nch / mid * sk <= 8 * (int64_t)mid) {
+            p.W = mid;
+            p.skew = sk;
+        }
+    }
+    trs_count_groups(p, f.nch);
+    return p;
+}
+
+// Chains of group g, ascending.
+template <typename F>
+__device__ __forceinline__ void trs_group(const TrsPlan &p, int nch, int g, F f) {
+    if (p.W == 0) {
+        for (int t = g * p.C; t < nch && t < (g + 1) * p.C; ++t) f(t);
+        return;
+    }
+    const int J = g % p.NJ, K = g / p.NJ;
+    for (int k = K * p.TK; k < (K + 1) * p.TK; ++k)
+        for (int e = 0; e < kTrsTJ; ++e) {
+            const int64_t j = (int64_t)J * kTrsTJ + e - (int64_t)p.skew * k, t = (int64_t)k * p.W + j;
+            if (j >= 0 && j < p.W && t < nch) f((int)t);
+        }
+}
+
+__global__ void k_trs_info(TrsInfo *f) {
+    if (threadIdx.x < 2) f[threadIdx.x] = TrsInfo{0, INT_MAX, 0, 0, 0, 0};
+}
+
 // Row i opens a chain: in L when it has no entry i - 1, in U when row i - 1
 // has no entry i (chains are listed by ascending rows in both).
 __device__ __forceinline__ bool trs_head(bool lower, int64_t i, const int *__restrict__ rp,
@@ -379,12 +453,14 @@ __device__ __forceinline__ void trs_entries(bool lower, int i, const int *__rest
         if (col[q] != nb) f(q, col[q]);
 }
 
-// st[0]: the widest row; st[1], st[2]: smallest and largest distance, in
-// chains, of an operand more than one chain away.
 __global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const int *__restrict__ rp,
                                                    const int *__restrict__ col, const int *__restrict__ dpos,
-                                                   const int *__restrict__ rowchain, int *st) {
-    int w = 0, lo = INT_MAX, hi = 0;
+                                                   const int *__restrict__ rowchain,
+                                                   const int *__restrict__ cstart, const int *__restrict__ nchp,
+                                                   TrsInfo *f) {
+    __shared__ int part[4][kWG / kWave];
+    int v[4] = {0, -INT_MAX, 0, 0};  // widest, -closest, farthest, longest
+    const int64_t nch = *nchp;
     for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += (int64_t)gridDim.x * kWG) {
         int a = 0;
         const int me = rowchain[i];
@@ -392,56 +468,75 @@ __global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const i
             ++a;
             const int o = abs(me - rowchain[c]);
             if (o > 1) {
-                lo = o < lo ? o : lo;
-                hi = o > hi ? o : hi;
+                v[1] = -o > v[1] ? -o : v[1];
+                v[2] = o > v[2] ? o : v[2];
             }
         });
-        w = a > w ? a : w;
+        v[0] = a > v[0] ? a : v[0];
+        if (i < nch) {
+            const int len = cstart[i + 1] - cstart[i];
+            v[3] = len > v[3] ? len : v[3];
+        }
     }
-    w = wave_max(w);
-    hi = wave_max(hi);
-    lo = -wave_max(-lo);
-    if (threadIdx.x % kWave == 0) {
-        atomicMax(st, w);
-        atomicMin(st + 1, lo);
-        atomicMax(st + 2, hi);
+    // one atomic per workgroup and value: one per wave took 286 us on a 101^3 grid
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int m = wave_max(v[j]);
+        if (threadIdx.x % kWave == 0) part[j][threadIdx.x / kWave] = m;
     }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const int *q = part[threadIdx.x];
+        const int m = max(max(q[0], q[1]), max(q[2], q[3]));
+        if (threadIdx.x == 0) atomicMax(&f->w, m);
+        else if (threadIdx.x == 1) atomicMin(&f->lo, -m);
+        else if (threadIdx.x == 2) atomicMax(&f->hi, m);
+        else atomicMax(&f->longest, m);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) f->nch = (int)nch;
 }
 
-// *bad = 1 when an operand's tile is not at or before its row's tile in both
-// tile coordinates (chain t = (t % W, t / W), columns skewed by the row).
+// f->bad = 1 when an operand's tile is not at or before its row's tile in
+// both tile coordinates: then a row's operands always come from tiles with
+// earlier tickets, in ascending order for L and descending for U.
 __global__ void k_trs_order(int64_t n, int lower, const int *__restrict__ rp, const int *__restrict__ col,
-                            const int *__restrict__ dpos, const int *__restrict__ rowchain, int W, int skew, int TK,
-                            int *bad) {
+                            const int *__restrict__ dpos, const int *__restrict__ rowchain, TrsInfo *f) {
+    const TrsPlan p = trs_plan(n, *f);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    auto tj = [&](int t) { return (t % W + skew * (t / W)) / kTrsTJ; };
-    auto tk = [&](int t) { return (t / W) / TK; };
+    if (i >= n || !p.ok || p.W == 0) return;
+    auto tj = [&](int t) { return (t % p.W + (int64_t)p.skew * (t / p.W)) / kTrsTJ; };
+    auto tk = [&](int t) { return (t / p.W) / p.TK; };
     const int me = rowchain[i];
     bool wrong = false;
     trs_entries(lower, (int)i, rp, col, dpos, [&](int, int c) {
         const int ot = rowchain[c];
-        const int first = lower ? ot : me, then = lower ? me : ot;  // ascending numbering
+        const int first = lower ? ot : me, then = lower ? me : ot;
         wrong = wrong || tj(first) > tj(then) || tk(first) > tk(then);
     });
-    if (wrong) atomicOr(bad, 1);
+    if (__any(wrong) && threadIdx.x % kWave == 0) atomicOr(&f->bad, 1);
 }
 
-// Places of a group's chains (one after the other) and each chain's group;
-// *most = the largest group's rows.
-__global__ void k_trs_places(int groups, const int *__restrict__ gptr, const int *__restrict__ glist,
-                             const int *__restrict__ cstart, int *__restrict__ cbase, int *__restrict__ cgroup,
-                             int *most) {
+__global__ void k_trs_sizes(TrsPlan p, int nch, int *__restrict__ gptr) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= groups) return;
+    if (g >= p.groups) return;
+    int c = 0;
+    trs_group(p, nch, g, [&](int) { ++c; });
+    gptr[g] = c;
+}
+
+// Each group's chains, their places (one after the other) and their group.
+__global__ void k_trs_lists(TrsPlan p, int nch, const int *__restrict__ gptr, const int *__restrict__ cstart,
+                            int *__restrict__ glist, int *__restrict__ cbase, int *__restrict__ cgroup) {
+    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= p.groups) return;
+    int q = gptr[g];
     int64_t rows = 0;
-    for (int q = gptr[g]; q < gptr[g + 1]; ++q) {
-        const int t = glist[q];
+    trs_group(p, nch, g, [&](int t) {
+        glist[q++] = t;
         cbase[t] = (int)(rows < INT_MAX ? rows : INT_MAX);
         cgroup[t] = g;
         rows += cstart[t + 1] - cstart[t];
-    }
-    atomicMax(most, (int)(rows < INT_MAX ? rows : INT_MAX));
+    });
 }
 
 __global__ void k_trs_encode(int64_t n, int64_t n_pad, int lower, int w, int cap, const int *__restrict__ rp,
@@ -477,14 +572,6 @@ __global__ void k_trs_encode(int64_t n, int64_t n_pad, int lower, int w, int cap
 
 namespace {
 
-BufPtr trs_buf(size_t bytes) {
-    auto d = std::make_shared<DevBuf>();
-    if (hipMalloc(&d->p, bytes ? bytes : 16) != hipSuccess) return BufPtr();
-    d->bytes = bytes;
-    d->owned = true;
-    return d;
-}
-
 unsigned trs_grid(int64_t n, int per) { return (unsigned)((n + per - 1) / per > 0 ? (n + per - 1) / per : 1); }
 
 #define TRS_TRY(expr, what)                                                                                    \
@@ -493,120 +580,43 @@ unsigned trs_grid(int64_t n, int per) { return (unsigned)((n + per - 1) / per > 
         if (e_ != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string(what ": ") + hipGetErrorString(e_)); \
     } while (0)
 
-// Groups of chains: 8 x TK tiles of the chains (t % W, t / W) in row-major
-// tile order, or (W = 0) C consecutive chains each.
-void trs_groups(int nch, int C, int W, int skew, int TK, std::vector<int> &glist, std::vector<int> &gptr) {
-    glist.resize((size_t)nch);
-    gptr.assign(1, 0);
-    if (W == 0) {
-        for (int t = 0; t < nch; ++t) glist[(size_t)t] = t;
-        for (int t = C; t < nch; t += C) gptr.push_back(t);
-        gptr.push_back(nch);
-        return;
-    }
-    const int64_t K = (nch - 1) / W, NJ = ((int64_t)W - 1 + skew * K) / kTrsTJ + 1, NK = K / TK + 1;
-    auto tile = [&](int t) { return ((int64_t)(t / W) / TK) * NJ + (t % W + (int64_t)skew * (t / W)) / kTrsTJ; };
-    std::vector<int> at((size_t)(NJ * NK) + 1, 0);
-    for (int t = 0; t < nch; ++t) ++at[(size_t)tile(t) + 1];
-    for (size_t q = 1; q < at.size(); ++q) {
-        at[q] += at[q - 1];
-        if (at[q] > at[q - 1]) gptr.push_back(at[q]);
-    }
-    for (int t = 0; t < nch; ++t) glist[(size_t)at[(size_t)tile(t)]++] = t;
-}
-
-// Plans and packs one triangle; ok = false (and no error) when its rows do
-// not suit the chain solve.
-mxl_status trs_build(IluImpl &P, bool lower, TrsSide &T, bool &ok) {
+// The device passes of a triangle's plan, up to its TrsInfo.
+hipError_t trs_gather(const IluImpl &P, bool lower, int *sums, int *rowchain, int *cstart, TrsInfo *f) {
     const MatrixImpl &A = *P.A;
     const int64_t n = A.nrows;
     hipStream_t s = A.ctx->stream;
     const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p, *dpos = (const int *)P.dpos->p;
-    const int nb = (int)trs_grid(n, kTrsScan);
-    ok = false;
-    BufPtr sums = trs_buf((size_t)(nb + 1) * 4), rowchain = trs_buf((size_t)n * 4), st = trs_buf(16);
-    BufPtr cstart = trs_buf((size_t)(n + 1) * 4);
-    if (!sums || !rowchain || !st || !cstart) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve plan");
-    int h[4] = {0, INT_MAX, 0, 0}, nch = 0;
-    TRS_TRY(hipMemcpyAsync(st->p, h, 16, hipMemcpyHostToDevice, s), "triangular solve plan");
-    hipLaunchKernelGGL(k_trs_count, dim3(nb), dim3(kWG), 0, s, n, (int)lower, rp, col, dpos, (int *)sums->p);
-    hipLaunchKernelGGL(k_trs_scan, dim3(1), dim3(kWG), 0, s, nb, (int *)sums->p);
-    hipLaunchKernelGGL(k_trs_chains, dim3(nb), dim3(kWG), 0, s, n, (int)lower, rp, col, dpos, (const int *)sums->p,
-                       nb, (int *)rowchain->p, (int *)cstart->p);
-    hipLaunchKernelGGL(k_trs_stats, dim3(std::min(trs_grid(n, kWG), 2048u)), dim3(kWG), 0, s, n, (int)lower, rp, col,
-                       dpos, (const int *)rowchain->p, (int *)st->p);
-    TRS_TRY(hipGetLastError(), "triangular solve plan");
-    TRS_TRY(hipMemcpyAsync(h, st->p, 16, hipMemcpyDeviceToHost, s), "triangular solve plan");
-    TRS_TRY(hipMemcpyAsync(&nch, (int *)sums->p + nb, 4, hipMemcpyDeviceToHost, s), "triangular solve plan");
-    TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
-    const int w = h[0];
-    // Chains shorter than 8 rows on average keep the worker's lanes waiting
-    // for records, and rows wider than a record do not fit it: such factors
-    // (random patterns, node blocks) have few levels, which the level
-    // launches serve.
-    if (nch < 1 || n / nch < 8 || w > kTrsWide) return MXL_OK;
-    const bool wide = w > kTrsNarrow;
-    const size_t rec = wide ? trs_lds_bytes<false, kTrsWide, kTrsLoaders, 1>(0)
-                            : trs_lds_bytes<false, kTrsNarrow, kTrsLoaders, 2>(0);
-    const int places = (int)((kTrsLdsMax - rec) / 8) - 1;
-    // As many chains per group as its LDS holds (fewer hops between groups):
-    // 64 of 128 rows take 64 KB.
-    int C = kTrsLanes;
-    while (C > 4 && (int64_t)C * (n / nch) > places - places / 8) C /= 2;
-    int W = 0, skew = 0;
-    const int TK = C / kTrsTJ;
-    if (TK > 1 && h[2] > 0) {  // operands further than one chain away: a plane of chains lies between
-        const int mid = (int)(((int64_t)h[1] + h[2]) / 2), sk = mid - h[1];
-        if (mid >= kTrsTJ && mid < nch && sk <= 4 && (int64_t)nch / mid * sk <= 8 * (int64_t)mid) {
-            W = mid;
-            skew = sk;
-            int zero = 0;
-            TRS_TRY(hipMemcpyAsync((int *)st->p + 3, &zero, 4, hipMemcpyHostToDevice, s), "triangular solve plan");
-            hipLaunchKernelGGL(k_trs_order, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, (int)lower, rp, col, dpos,
-                               (const int *)rowchain->p, W, skew, TK, (int *)st->p + 3);
-            int bad = 1;
-            TRS_TRY(hipMemcpyAsync(&bad, (int *)st->p + 3, 4, hipMemcpyDeviceToHost, s), "triangular solve plan");
-            TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
-            if (bad) W = 0;
-        }
-    }
-    std::vector<int> glist, gptr;
-    trs_groups(nch, C, W, skew, TK, glist, gptr);
-    T.groups = (int)gptr.size() - 1;
-    T.C = C;
-    T.w = w;
-    P.n_pad = (n + 63) / 64 * 64;
-    BufPtr cgroup = trs_buf((size_t)nch * 4);
-    T.cstart = trs_buf((size_t)(nch + 1) * 4);
-    T.cbase = trs_buf((size_t)nch * 4);
-    T.glist = trs_buf((size_t)nch * 4);
-    T.gptr = trs_buf(gptr.size() * 4);
-    T.code = trs_buf((size_t)w * P.n_pad * 4);
-    T.val = trs_buf((size_t)w * P.n_pad * 8);
-    T.prev = trs_buf((size_t)n * 8);
-    if (!lower) P.udiag = trs_buf((size_t)n * 8);
-    if (!cgroup || !T.cstart || !T.cbase || !T.glist || !T.gptr || !T.code || !T.val || !T.prev ||
-        (!lower && !P.udiag))
-        return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve factors");
-    int most = 0;
-    TRS_TRY(hipMemcpyAsync(T.cstart->p, cstart->p, (size_t)(nch + 1) * 4, hipMemcpyDeviceToDevice, s), "chains");
-    TRS_TRY(hipMemcpyAsync(T.glist->p, glist.data(), glist.size() * 4, hipMemcpyHostToDevice, s), "chain groups");
-    TRS_TRY(hipMemcpyAsync(T.gptr->p, gptr.data(), gptr.size() * 4, hipMemcpyHostToDevice, s), "chain groups");
-    TRS_TRY(hipMemcpyAsync(st->p, &most, 4, hipMemcpyHostToDevice, s), "chain groups");
-    hipLaunchKernelGGL(k_trs_places, dim3(trs_grid(T.groups, 64)), dim3(64), 0, s, T.groups, (const int *)T.gptr->p,
-                       (const int *)T.glist->p, (const int *)T.cstart->p, (int *)T.cbase->p, (int *)cgroup->p,
-                       (int *)st->p);
-    TRS_TRY(hipMemcpyAsync(&most, st->p, 4, hipMemcpyDeviceToHost, s), "chain groups");
-    TRS_TRY(hipStreamSynchronize(s), "chain groups");
-    T.cap = std::min(most, places);
-    hipLaunchKernelGGL(k_trs_encode, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, P.n_pad, (int)lower, w, T.cap, rp,
-                       col, dpos, (const double *)P.lu->p, (const int *)rowchain->p, (const int *)T.cstart->p,
-                       (const int *)T.cbase->p, (const int *)cgroup->p, (int *)T.code->p, (double *)T.val->p,
-                       (double *)T.prev->p, lower ? nullptr : (double *)P.udiag->p);
-    TRS_TRY(hipGetLastError(), "triangular solve factors");
-    TRS_TRY(hipStreamSynchronize(s), "triangular solve factors");  // the plan's temporaries end here
-    ok = true;
-    return MXL_OK;
+    const int nb = (int)trs_grid(n, kTrsScan), lw = lower;
+    hipLaunchKernelGGL(k_trs_count, dim3(nb), dim3(kWG), 0, s, n, lw, rp, col, dpos, sums);
+    hipLaunchKernelGGL(k_trs_scan, dim3(1), dim3(kWG), 0, s, nb, sums);
+    hipLaunchKernelGGL(k_trs_chains, dim3(nb), dim3(kWG), 0, s, n, lw, rp, col, dpos, (const int *)sums, nb, rowchain,
+                       cstart);
+    hipLaunchKernelGGL(k_trs_stats, dim3(std::min(trs_grid(n, kWG), 1024u)), dim3(kWG), 0, s, n, lw, rp, col, dpos,
+                       (const int *)rowchain, (const int *)cstart, (const int *)sums + nb, f);
+    hipLaunchKernelGGL(k_trs_order, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, lw, rp, col, dpos,
+                       (const int *)rowchain, f);
+    return hipGetLastError();
+}
+
+// Lists and packs a planned triangle (all of it on the stream).
+hipError_t trs_pack(IluImpl &P, bool lower, const TrsPlan &p, int nch, TrsSide &T, const int *rowchain,
+                    const int *cstart, int *cgroup) {
+    const MatrixImpl &A = *P.A;
+    const int64_t n = A.nrows;
+    hipStream_t s = A.ctx->stream;
+    hipError_t e = hipMemcpyAsync(T.cstart->p, cstart, (size_t)(nch + 1) * 4, hipMemcpyDeviceToDevice, s);
+    if (e != hipSuccess) return e;
+    const dim3 g(trs_grid(p.groups, 64));
+    hipLaunchKernelGGL(k_trs_sizes, g, dim3(64), 0, s, p, nch, (int *)T.gptr->p);
+    hipLaunchKernelGGL(k_trs_scan, dim3(1), dim3(kWG), 0, s, p.groups, (int *)T.gptr->p);
+    hipLaunchKernelGGL(k_trs_lists, g, dim3(64), 0, s, p, nch, (const int *)T.gptr->p, (const int *)T.cstart->p,
+                       (int *)T.glist->p, (int *)T.cbase->p, cgroup);
+    hipLaunchKernelGGL(k_trs_encode, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, P.n_pad, (int)lower, T.w, T.cap,
+                       (const int *)A.row_ptr->p, (const int *)A.col->p, (const int *)P.dpos->p,
+                       (const double *)P.lu->p, rowchain, (const int *)T.cstart->p, (const int *)T.cbase->p,
+                       (const int *)cgroup, (int *)T.code->p, (double *)T.val->p, (double *)T.prev->p,
+                       lower ? nullptr : (double *)P.udiag->p);
+    return hipGetLastError();
 }
 
 template <int NE, int RD>
@@ -648,14 +658,59 @@ void trs_launch(const TrsView &M, const double *b, double *x, double *znext, dou
 }  // namespace
 
 mxl_status ilu_build_chains(IluImpl &P) {
-    bool ok = false;
-    mxl_status st = trs_build(P, true, P.lo, ok);
-    if (st != MXL_OK || !ok) return st;
-    if ((st = trs_build(P, false, P.up, ok)) != MXL_OK || !ok) return st;
-    P.tickets = trs_buf(8);
-    if (!P.tickets) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve tickets");
+    const int64_t n = P.A->nrows;
+    hipStream_t s = P.A->ctx->stream;
+    BufPtr info, sums, rowchain[2], cstart[2], cgroup[2];
+    Arena tmp;
+    tmp.want(info, 2 * sizeof(TrsInfo));
+    tmp.want(sums, ((size_t)trs_grid(n, kTrsScan) + 1) * 4);
+    for (int k = 0; k < 2; ++k) {
+        tmp.want(rowchain[k], (size_t)n * 4);
+        tmp.want(cstart[k], (size_t)(n + 1) * 4);
+        tmp.want(cgroup[k], (size_t)n * 4);
+    }
+    if (!tmp.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve plan");
+    TrsInfo f[2];
+    hipLaunchKernelGGL(k_trs_info, dim3(1), dim3(64), 0, s, (TrsInfo *)info->p);
+    for (int k = 0; k < 2; ++k)
+        TRS_TRY(trs_gather(P, k == 0, (int *)sums->p, (int *)rowchain[k]->p, (int *)cstart[k]->p,
+                           (TrsInfo *)info->p + k), "triangular solve plan");
+    TRS_TRY(hipMemcpyAsync(f, info->p, sizeof f, hipMemcpyDeviceToHost, s), "triangular solve plan");
+    TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
+    TrsPlan p[2];
+    for (int k = 0; k < 2; ++k) {
+        p[k] = trs_plan(n, f[k]);
+        if (!p[k].ok) return MXL_OK;
+        if (f[k].bad) {
+            p[k].W = 0;
+            trs_count_groups(p[k], f[k].nch);
+        }
+    }
+    P.n_pad = (n + 63) / 64 * 64;
+    Arena keep;
+    for (int k = 0; k < 2; ++k) {
+        TrsSide &T = k == 0 ? P.lo : P.up;
+        T.groups = p[k].groups;
+        T.C = p[k].C;
+        T.w = f[k].w;
+        T.cap = (int)std::min<int64_t>((int64_t)p[k].C * f[k].longest, p[k].places);
+        keep.want(T.cstart, (size_t)(f[k].nch + 1) * 4);
+        keep.want(T.cbase, (size_t)f[k].nch * 4);
+        keep.want(T.glist, (size_t)f[k].nch * 4);
+        keep.want(T.gptr, (size_t)(p[k].groups + 1) * 4);
+        keep.want(T.code, (size_t)T.w * P.n_pad * 4);
+        keep.want(T.val, (size_t)T.w * P.n_pad * 8);
+        keep.want(T.prev, (size_t)n * 8);
+    }
+    keep.want(P.udiag, (size_t)n * 8);
+    keep.want(P.tickets, 8);
+    if (!keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve factors");
+    for (int k = 0; k < 2; ++k)
+        TRS_TRY(trs_pack(P, k == 0, p[k], f[k].nch, k == 0 ? P.lo : P.up, (const int *)rowchain[k]->p,
+                         (const int *)cstart[k]->p, (int *)cgroup[k]->p), "triangular solve factors");
     TRS_TRY((trs_allow_lds<kTrsNarrow, 2>()), "LDS attribute");
     TRS_TRY((trs_allow_lds<kTrsWide, 1>()), "LDS attribute");
+    TRS_TRY(hipStreamSynchronize(s), "triangular solve factors");  // the plan's temporaries end here
     P.chain = true;
     return MXL_OK;
 }

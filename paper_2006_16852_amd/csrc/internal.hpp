@@ -20,16 +20,52 @@ namespace mxl {
 struct SolverState;
 
 // A device allocation, freed when the last shared owner lets go.  Borrowed
-// views (owned = false) are never freed.
+// views (owned = false) are never freed; a view of a larger allocation keeps
+// it alive (whole).
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
     bool owned = false;
+    std::shared_ptr<DevBuf> whole;
     ~DevBuf() {
         if (owned && p) (void)hipFree(p);
     }
 };
 using BufPtr = std::shared_ptr<DevBuf>;
+
+// Several buffers that live and die together, in one device allocation: a
+// hipFree of a used buffer costs about 0.1 ms whatever its size (thirty of
+// them were half of an ILU generation on a 101^3 grid).
+class Arena {
+public:
+    void want(BufPtr &b, size_t bytes) { parts.emplace_back(&b, bytes); }
+    // false: no memory, and no buffer is set
+    bool alloc() {
+        size_t total = 0;
+        for (auto &q : parts) total += (q.second + 255) / 256 * 256;
+        auto a = std::make_shared<DevBuf>();
+        if (hipMalloc(&a->p, total ? total : 256) != hipSuccess) {
+            a->p = nullptr;
+            return false;
+        }
+        a->bytes = total;
+        a->owned = true;
+        size_t at = 0;
+        for (auto &q : parts) {
+            auto v = std::make_shared<DevBuf>();
+            v->p = (char *)a->p + at;
+            v->bytes = q.second;
+            v->whole = a;
+            *q.first = v;
+            at += (q.second + 255) / 256 * 256;
+        }
+        parts.clear();
+        return true;
+    }
+
+private:
+    std::vector<std::pair<BufPtr *, size_t>> parts;
+};
 
 }  // namespace mxl
 
