@@ -417,17 +417,22 @@ mxl_status mxl_batch_csr_create(mxl_ctx *ctx, int64_t nsys,
 typedef struct { int32_t wg_size; int32_t wgs_per_cu; int32_t order; int32_t format; } mxl_tuning;
 
 /* Jacobi-PCG on every system independently (per-system stopping status,
- * Sec. 2.5), all in one persistent launch.  crit->max_iters <= 0 means
- * 10*n_s per system.  tuning NULL = the autotuned schedule (cached per
- * handle).  b, x: device FP64 of total rows; iters, rel_res, status: device
- * arrays of nsys entries. */
+ * Sec. 2.5).  With a tuning all systems run in one persistent launch.  tuning
+ * NULL runs them by size: systems of at most 1024 rows and 28 entries per row
+ * with their matrix in registers, one launch per size class (64, 128, ...,
+ * 1024 rows), the others by the autotuned schedule (cached per handle) or the
+ * default one; all of them by the autotuned schedule when mxl_batch_autotune
+ * found that faster, or when the batch has no ELL copy.  crit->max_iters <= 0
+ * means 10*n_s per system.  b, x: device FP64 of total rows; iters, rel_res,
+ * status: device arrays of nsys entries. */
 mxl_status mxl_batch_solve(const mxl_op *B, const mxl_criteria *crit,
                            const mxl_tuning *tuning, const double *b,
                            double *x, int32_t *iters, double *rel_res,
                            uint8_t *status);
 
 /* Autotune the batched schedule: times each candidate (reps launches each)
- * and stores the best on the handle; best may be NULL. */
+ * and stores the best on the handle, and whether the solve by size classes is
+ * faster still; best may be NULL. */
 mxl_status mxl_batch_autotune(const mxl_op *B, const mxl_criteria *crit,
                               const double *b, double *x_scratch, int reps,
                               mxl_tuning *best, double *best_ms);

@@ -50,7 +50,23 @@ struct BatchImpl {
     int w_max = 0;
     int64_t ell_slots = 0;
     BufPtr ell_val, ell_col, ell_off, ell_w;
+    // The size-class schedule (with the ELL copy): systems a workgroup can
+    // hold in registers, by class and largest first, and the others.
+    BufPtr desc, order_rest;
+    int64_t cls_begin[6] = {0};  // class k: desc[cls_begin[k]] .. desc[cls_begin[k + 1] - 1]
+    int64_t nrest = 0;
+    bool cls_best = true;        // the schedule of calls without one (autotuning may find another faster)
 };
+
+// One system of the size-class schedule.
+struct BatchDesc {
+    int32_t sys, r0, n, w;
+    int64_t off;
+    int64_t pad;
+};
+constexpr int kClsN[5] = {64, 128, 256, 512, 1024};  // rows of the classes
+constexpr int kClsR[5] = {1, 2, 2, 2, 2};            // rows per thread
+constexpr int kClsW = 28;                            // entries per row held in registers
 
 template <int B>
 __device__ __forceinline__ double wg_sum(double v, double *red) {
@@ -323,6 +339,235 @@ __global__ __launch_bounds__(B) void k_batch_pcg_ell(
             status_out[s] = (uint8_t)stop;
         }
         __syncthreads();
+    }
+}
+
+// Sums over lanes by moves inside the vector unit (a shuffle through LDS
+// costs about 100 cycles a step): lanes of a 16-lane row are rotated, rows
+// and halves of the wave exchanged.  Every step adds the same two values in
+// both partners, so all lanes end with the same bits.
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+constexpr int kDppXor1 = 0xB1, kDppRor1 = 0x121, kDppRor2 = 0x122, kDppRor4 = 0x124, kDppRor8 = 0x128;
+// v plus its value 16 (HALF: 32) lanes away
+template <bool HALF>
+__device__ __forceinline__ double swap_add(double v) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned l = (unsigned)b, h = (unsigned)(b >> 32);
+    unsigned l0, l1, h0, h1;
+    if constexpr (HALF) {
+        const auto x = __builtin_amdgcn_permlane32_swap(l, l, false, false);
+        const auto y = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+        l0 = x[0]; l1 = x[1]; h0 = y[0]; h1 = y[1];
+    } else {
+        const auto x = __builtin_amdgcn_permlane16_swap(l, l, false, false);
+        const auto y = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+        l0 = x[0]; l1 = x[1]; h0 = y[0]; h1 = y[1];
+    }
+    return __longlong_as_double((long long)((unsigned long long)h0 << 32 | l0)) +
+           __longlong_as_double((long long)((unsigned long long)h1 << 32 | l1));
+}
+
+// Sum over the B-thread workgroup (at most 8 waves), in every thread; red: 8
+// doubles not in use by another sum since the barrier before the last one.
+template <int B>
+__device__ __forceinline__ double cls_sum(double v, double *red) {
+    constexpr int NW = B / kWave;
+    v += dpp_move<kDppRor8>(v);
+    v += dpp_move<kDppRor4>(v);
+    v += dpp_move<kDppRor2>(v);
+    v += dpp_move<kDppXor1>(v);
+    v = swap_add<true>(swap_add<false>(v));
+    if constexpr (NW > 1) {
+        const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+        if (lane == 0) red[wid] = v;
+        __syncthreads();
+        v = red[lane % NW];
+        if constexpr (NW > 4) v += dpp_move<kDppRor4>(v);
+        if constexpr (NW > 2) v += dpp_move<kDppRor2>(v);
+        v += dpp_move<kDppRor1>(v);
+    }
+    return v;
+}
+
+// Two sums at once: after one exchange even lanes carry u and odd lanes v, so
+// the two cost little more than one.  red: 16 doubles.
+template <int B>
+__device__ __forceinline__ void cls_sum2(double &u, double &v, double *red) {
+    constexpr int NW = B / kWave;
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    const bool odd = lane & 1;
+    double t = odd ? v : u;
+    t += dpp_move<kDppXor1>(odd ? u : v);
+    t += dpp_move<kDppRor8>(t);
+    t += dpp_move<kDppRor4>(t);
+    t += dpp_move<kDppRor2>(t);
+    t = swap_add<true>(swap_add<false>(t));
+    if constexpr (NW > 1) {
+        if (lane < 2) red[2 * wid + lane] = t;
+        __syncthreads();
+        t = red[lane % (2 * NW)];
+        if constexpr (NW > 4) t += dpp_move<kDppRor8>(t);
+        if constexpr (NW > 2) t += dpp_move<kDppRor4>(t);
+        t += dpp_move<kDppRor2>(t);
+    }
+    const double o = dpp_move<kDppXor1>(t);
+    u = odd ? o : t;
+    v = odd ? t : o;
+}
+
+// Jacobi-PCG of the systems of one size class, a workgroup each, with nothing
+// but p outside the registers: a thread holds its one or two rows of the
+// matrix (at most kClsW entries, two 16-bit LDS offsets to a register), of x,
+// r, p and 1/a_ii, so an iteration reads p from LDS, reduces twice and touches
+// no memory.  The matrices are read once.
+//
+// What bounds it: vector instructions (an FMA, an LDS address and a share of
+// two reductions per entry) and the latency of an iteration's three barriers,
+// with two waves per SIMD (28 entries of two rows take 244 registers).  Two
+// rows per thread halve what every wave repeats (reductions, quotients):
+// 730 -> 610 us for 10,000 banded systems of 32 to 1,024 rows, widths 5 to 27;
+// reductions by lane moves instead of LDS shuffles and eight LDS reads under
+// way: 610 -> 553 us (156 us of it is the one pass over the matrices, 20 us an
+// iteration).  The persistent kernels above, which stream the matrices from
+// the caches in every iteration: 4,040 us in the default schedule, 2,740 us in
+// the best one.  Narrower shapes for narrow bands (12 entries, twice the
+// waves) gained nothing: 693 us with the extra launches.
+template <int B, int RPT, int W>
+__global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(RPT * W > 32 ? 2 : 4))) void k_batch_pcg_cls(
+    const BatchDesc *__restrict__ desc, const double *__restrict__ ell_val, const short *__restrict__ ell_col,
+    const double *__restrict__ dinv, const double *__restrict__ bvec, double *__restrict__ xout,
+    int *__restrict__ iters_out, double *__restrict__ rel_out, uint8_t *__restrict__ status_out, double red_factor,
+    int64_t max_iters_fixed, int iter_factor, int chk) {
+    constexpr int G = W <= 12 ? 6 : 8;     // slots read from LDS at a time
+    __shared__ double p_lds[B * RPT + 1];  // p, and a zero for the padding slots
+    __shared__ double redA[8], redB[16], redC[16];
+    const BatchDesc d = desc[blockIdx.x];
+    const int n = d.n, w = d.w;
+    double v[RPT][W];
+    unsigned c[RPT][W / 2];
+    double x[RPT], r[RPT], p[RPT], q[RPT], di[RPT];
+    double rho = 0.0, bb = 0.0;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        const int i = threadIdx.x + j * B;
+        const bool own = i < n;
+        const double *vp = ell_val + d.off + i;
+        const short *cp = ell_col + d.off + i;
+#pragma unroll
+        for (int e = 0; e < W; e += 2) {
+            double v0 = 0.0, v1 = 0.0;
+            int c0 = -1, c1 = -1;
+            if (own && e < w) {
+                v0 = __builtin_nontemporal_load(vp + (int64_t)e * n);
+                c0 = __builtin_nontemporal_load(cp + (int64_t)e * n);
+            }
+            if (own && e + 1 < w) {
+                v1 = __builtin_nontemporal_load(vp + (int64_t)(e + 1) * n);
+                c1 = __builtin_nontemporal_load(cp + (int64_t)(e + 1) * n);
+            }
+            v[j][e] = v0;
+            v[j][e + 1] = v1;
+            c[j][e / 2] = (unsigned)(c0 < 0 ? n : c0) * 8u | (unsigned)(c1 < 0 ? n : c1) * 8u << 16;
+        }
+        const double bi = own ? bvec[d.r0 + i] : 0.0;
+        di[j] = own ? dinv[d.r0 + i] : 0.0;
+        // x = 0, r = b, p = z = D^{-1} r
+        x[j] = 0.0;
+        r[j] = bi;
+        p[j] = di[j] * bi;
+        if (own) p_lds[i] = p[j];
+        rho += r[j] * p[j];
+        bb += bi * bi;
+    }
+    if (threadIdx.x == 0) p_lds[n] = 0.0;
+    cls_sum2<B>(rho, bb, redC);
+    const double nb = sqrt(bb), tol = red_factor * nb;
+    // sqrt(rr) <= tol without the root: the largest rr that meets it
+    double top = tol * tol;
+    const bool by_top = top > 1e-290 && top < 1e290;
+    if (by_top) {
+        while (sqrt(top) > tol) top = __longlong_as_double(__double_as_longlong(top) - 1);
+        for (double up = __longlong_as_double(__double_as_longlong(top) + 1); sqrt(up) <= tol;
+             up = __longlong_as_double(__double_as_longlong(up) + 1))
+            top = up;
+    }
+    auto met = [&](double rr) { return by_top ? rr <= top : sqrt(rr) <= tol; };
+    const int64_t maxit = max_iters_fixed > 0 ? max_iters_fixed : (int64_t)iter_factor * n;
+    int stop = ST_RUN;
+    int64_t k = 0;
+    double rr = bb;
+    if (bb == 0.0 || met(rr)) stop = ST_CONVERGED;
+    while (stop == ST_RUN && k < maxit) {
+        __syncthreads();  // p complete
+        double eta = 0.0;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) q[j] = 0.0;
+#pragma unroll
+        for (int e = 0; e < W; e += G)
+            if (e < w) {
+                double pv[RPT][G];
+#pragma unroll
+                for (int j = 0; j < RPT; ++j)
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        if (e + u >= W) continue;
+                        const unsigned o = (u & 1) ? c[j][(e + u) / 2] >> 16 : c[j][(e + u) / 2] & 0xffffu;
+                        pv[j][u] = *(const double *)((const char *)p_lds + o);
+                    }
+#pragma unroll
+                for (int u = 0; u < G; ++u)
+#pragma unroll
+                    for (int j = 0; j < RPT; ++j)
+                        if (e + u < W) q[j] += v[j][e + u] * pv[j][u];
+            }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) eta += p[j] * q[j];
+        eta = cls_sum<B>(eta, redA);
+        if (chk && !finite_d(eta)) { stop = ST_NONFINITE; break; }
+        if (eta <= 0.0) { stop = ST_BREAKDOWN; break; }
+        const double alpha = rho / eta;
+        double rz = 0.0;
+        rr = 0.0;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const bool own = (int)threadIdx.x + j * B < n;
+            x[j] += alpha * p[j];
+            r[j] = own ? r[j] - alpha * q[j] : 0.0;  // lanes past the last row stay out of the sums whatever alpha is
+            q[j] = di[j] * r[j];                     // z
+            rz += r[j] * q[j];
+            rr += r[j] * r[j];
+        }
+        cls_sum2<B>(rz, rr, redB);
+        ++k;
+        if (chk && !finite_d(rr)) { stop = ST_NONFINITE; break; }
+        if (met(rr)) { stop = ST_CONVERGED; break; }
+        if (chk && !finite_d(rz)) { stop = ST_NONFINITE; break; }
+        if (rz == 0.0) { stop = ST_BREAKDOWN; break; }
+        const double beta = rz / rho;
+        rho = rz;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const int i = threadIdx.x + j * B;
+            p[j] = q[j] + beta * p[j];
+            if (i < n) p_lds[i] = p[j];
+        }
+    }
+    if (stop == ST_RUN) stop = ST_MAX_ITERS;
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+        const int i = threadIdx.x + j * B;
+        if (i < n) xout[d.r0 + i] = x[j];
+    }
+    if (threadIdx.x == 0) {
+        iters_out[d.sys] = (int)k;
+        rel_out[d.sys] = nb > 0.0 ? sqrt(rr) / nb : 0.0;
+        status_out[d.sys] = (uint8_t)stop;
     }
 }
 
@@ -770,9 +1015,10 @@ bool use_ell(const BatchImpl &Bt, const mxl_tuning &t) { return t.format == 2 ||
 hipError_t launch_batch_on(const BatchImpl &Bt, const mxl_tuning &t, const mxl_criteria &c,
                            const double *b, double *x, int32_t *iters, double *rel, uint8_t *status,
                            int lds_cap, int64_t ell_budget, hipStream_t s, unsigned *queue, double *scr,
-                           int use_x0 = 0) {
+                           int use_x0 = 0, bool rest = false) {
     const int G = t.wgs_per_cu * Bt.ctx->num_cu;
-    const int *order = (const int *)(t.order ? Bt.order_big->p : Bt.order_input->p);
+    const int *order = (const int *)(rest ? Bt.order_rest->p : t.order ? Bt.order_big->p : Bt.order_input->p);
+    const int64_t nsys = rest ? Bt.nrest : Bt.nsys;
     hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, queue);
     const int chk = c.nonfinite_check;
     const double red = c.reduction;
@@ -782,7 +1028,7 @@ hipError_t launch_batch_on(const BatchImpl &Bt, const mxl_tuning &t, const mxl_c
         const int64_t stride = scr ? (int64_t)5 * Bt.max_n : 0;
 #define MXL_BATCH_ELL_CASE(BB)                                                                       \
     case BB:                                                                                         \
-        hipLaunchKernelGGL(k_batch_pcg_ell<BB>, dim3(G), dim3(BB), shm, s, Bt.nsys,                  \
+        hipLaunchKernelGGL(k_batch_pcg_ell<BB>, dim3(G), dim3(BB), shm, s, nsys,                     \
                            (const int *)Bt.sys_ptr->p, (const int64_t *)Bt.ell_off->p,              \
                            (const int *)Bt.ell_w->p, (const double *)Bt.ell_val->p,                 \
                            (const short *)Bt.ell_col->p, (const double *)Bt.dinv->p, b, x, iters,   \
@@ -801,7 +1047,7 @@ hipError_t launch_batch_on(const BatchImpl &Bt, const mxl_tuning &t, const mxl_c
     const int64_t stride = scr ? (int64_t)4 * Bt.max_n : 0;
 #define MXL_BATCH_CASE(BB)                                                                          \
     case BB:                                                                                        \
-        hipLaunchKernelGGL(k_batch_pcg<BB>, dim3(G), dim3(BB), shm, s, Bt.nsys,                     \
+        hipLaunchKernelGGL(k_batch_pcg<BB>, dim3(G), dim3(BB), shm, s, nsys,                        \
                            (const int *)Bt.sys_ptr->p, (const int *)Bt.row_ptr->p,                 \
                            (const int *)Bt.col->p, (const double *)Bt.val->p,                      \
                            (const double *)Bt.dinv->p, b, x, iters, rel, status, order,            \
@@ -813,6 +1059,33 @@ hipError_t launch_batch_on(const BatchImpl &Bt, const mxl_tuning &t, const mxl_c
     }
 #undef MXL_BATCH_CASE
     return hipGetLastError();
+}
+
+// The size-class schedule: a launch per class, largest first, then the
+// systems that no class holds (t: their schedule, as launch_batch_on).
+template <int K>
+void launch_class(const BatchImpl &Bt, const mxl_criteria &c, const double *b, double *x, int32_t *iters,
+                  double *rel, uint8_t *status, hipStream_t s) {
+    const int64_t cnt = Bt.cls_begin[K + 1] - Bt.cls_begin[K];
+    if (cnt > 0)
+        hipLaunchKernelGGL((k_batch_pcg_cls<kClsN[K] / kClsR[K], kClsR[K], kClsW>), dim3((unsigned)cnt),
+                           dim3(kClsN[K] / kClsR[K]), 0, s,
+                           (const BatchDesc *)Bt.desc->p + Bt.cls_begin[K], (const double *)Bt.ell_val->p,
+                           (const short *)Bt.ell_col->p, (const double *)Bt.dinv->p, b, x, iters, rel, status,
+                           c.reduction, c.max_iters, 10, c.nonfinite_check);
+}
+
+hipError_t launch_classes(const BatchImpl &Bt, const mxl_tuning &t, const mxl_criteria &c, const double *b,
+                          double *x, int32_t *iters, double *rel, uint8_t *status, int lds_cap, int64_t ell_budget,
+                          hipStream_t s, unsigned *queue, double *scr) {
+    launch_class<4>(Bt, c, b, x, iters, rel, status, s);
+    launch_class<3>(Bt, c, b, x, iters, rel, status, s);
+    launch_class<2>(Bt, c, b, x, iters, rel, status, s);
+    launch_class<1>(Bt, c, b, x, iters, rel, status, s);
+    launch_class<0>(Bt, c, b, x, iters, rel, status, s);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || Bt.nrest == 0) return e;
+    return launch_batch_on(Bt, t, c, b, x, iters, rel, status, lds_cap, ell_budget, s, queue, scr, 0, true);
 }
 
 // The handle's own queue counter and (lazily allocated) spill region.
@@ -943,6 +1216,35 @@ extern "C" mxl_status mxl_batch_csr_create(mxl_ctx *ctx, int64_t nsys, const int
         Bt->ell = true;
         Bt->w_max = w_max;
         Bt->ell_slots = slots;
+        // size classes, each largest first (big is sorted by size); the rest
+        // in the same order
+        std::vector<BatchDesc> de;
+        std::vector<int32_t> rest;
+        de.reserve((size_t)nsys);
+        auto cls_of = [&](int sy) {
+            const int n = Bt->sys_ptr_h[sy + 1] - Bt->sys_ptr_h[sy];
+            int k = 0;
+            while (k < 5 && n > kClsN[k]) ++k;
+            return w_h[sy] <= kClsW ? k : 5;
+        };
+        for (int k = 0; k <= 5; ++k) {
+            Bt->cls_begin[k] = (int64_t)de.size();
+            for (int32_t sy : big) {
+                if (cls_of(sy) != k) continue;
+                if (k == 5) rest.push_back(sy);
+                else de.push_back({sy, Bt->sys_ptr_h[sy], Bt->sys_ptr_h[sy + 1] - Bt->sys_ptr_h[sy], w_h[sy], off_h[sy], 0});
+            }
+        }
+        Bt->nrest = (int64_t)rest.size();
+        Bt->desc = alloc(de.size() * sizeof(BatchDesc));
+        Bt->order_rest = alloc(rest.size() * 4);
+        if (!Bt->desc || !Bt->order_rest) return set_error(MXL_ERR_OUT_OF_MEMORY, "batch size classes");
+        if ((!de.empty() && hipMemcpyAsync(Bt->desc->p, de.data(), de.size() * sizeof(BatchDesc), hipMemcpyHostToDevice,
+                                           s) != hipSuccess) ||
+            (!rest.empty() && hipMemcpyAsync(Bt->order_rest->p, rest.data(), rest.size() * 4, hipMemcpyHostToDevice,
+                                             s) != hipSuccess) ||
+            hipStreamSynchronize(s) != hipSuccess)  // the host lists end here
+            return set_error(MXL_ERR_DEVICE, "upload size classes");
     }
     badh = INT_MAX;
     if (hipMemcpyAsync(bad->p, &badh, 4, hipMemcpyHostToDevice, s) != hipSuccess)
@@ -1034,10 +1336,11 @@ static mxl_status allow_lds(const SchedPlan &p, const mxl_tuning &t) {
 
 static mxl_status run_schedule(BatchImpl &Bt, const mxl_tuning &t, const mxl_criteria &c,
                                const double *b, double *x, int32_t *iters, double *rel,
-                               uint8_t *status) {
+                               uint8_t *status, bool classes = false) {
     SchedPlan p;
     mxl_status st;
     if ((st = plan_schedule(Bt, t, p)) != MXL_OK) return st;
+    if (classes && Bt.nrest == 0) p.spill_elems = 0;
     if (p.spill_elems > 0 && Bt.scratch_elems < p.spill_elems) {
         auto d = std::make_shared<DevBuf>();
         if (hipMalloc(&d->p, p.spill_elems * 8) != hipSuccess)
@@ -1048,9 +1351,16 @@ static mxl_status run_schedule(BatchImpl &Bt, const mxl_tuning &t, const mxl_cri
         Bt.scratch_elems = p.spill_elems;
     }
     if ((st = allow_lds(p, t)) != MXL_OK) return st;
-    hipError_t e = launch_batch(Bt, t, c, b, x, iters, rel, status, p.cap, p.ell_budget, Bt.ctx->stream);
+    hipError_t e = classes ? launch_classes(Bt, t, c, b, x, iters, rel, status, p.cap, p.ell_budget, Bt.ctx->stream,
+                                            (unsigned *)Bt.queue->p, Bt.scratch ? (double *)Bt.scratch->p : nullptr)
+                           : launch_batch(Bt, t, c, b, x, iters, rel, status, p.cap, p.ell_budget, Bt.ctx->stream);
     if (e != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string("batched launch: ") + hipGetErrorString(e));
     return MXL_OK;
+}
+
+// Whether calls without a schedule run by size class.
+static bool by_class(const BatchImpl &Bt) {
+    return Bt.ell && Bt.cls_best && Bt.cls_begin[5] > 0;
 }
 
 static mxl_tuning default_tuning() {
@@ -1071,7 +1381,7 @@ extern "C" mxl_status mxl_batch_solve(const mxl_op *Bop, const mxl_criteria *cri
     mxl_status st;
     if ((st = batch_args(*Bt, b, x, iters, rel_res, status)) != MXL_OK) return st;
     mxl_tuning t = tuning ? *tuning : (Bt->tuned ? Bt->best : default_tuning());
-    if ((st = run_schedule(*Bt, t, *crit, b, x, iters, rel_res, status)) != MXL_OK) return st;
+    if ((st = run_schedule(*Bt, t, *crit, b, x, iters, rel_res, status, !tuning && by_class(*Bt))) != MXL_OK) return st;
     if (hipStreamSynchronize(Bt->ctx->stream) != hipSuccess)
         return set_error(MXL_ERR_DEVICE, "batched solve");
     return MXL_OK;
@@ -1088,8 +1398,10 @@ extern "C" mxl_status mxl_batch_solve_noalloc(const mxl_op *Bop, const mxl_crite
     mxl_status st;
     if ((st = batch_args(*Bt, b, x, iters, rel_res, status)) != MXL_OK) return st;
     const mxl_tuning t = tuning ? *tuning : (Bt->tuned ? Bt->best : default_tuning());
+    const bool classes = !tuning && by_class(*Bt);
     SchedPlan p;
     if ((st = plan_schedule(*Bt, t, p)) != MXL_OK) return st;
+    if (classes && Bt->nrest == 0) p.spill_elems = 0;
     const size_t need = kNoAllocQueueBytes + (size_t)p.spill_elems * 8;
     if (need > kNoAllocScratchBytes)
         return set_error(MXL_ERR_INVALID_ARG,
@@ -1099,8 +1411,10 @@ extern "C" mxl_status mxl_batch_solve_noalloc(const mxl_op *Bop, const mxl_crite
     if (!base) return set_error(MXL_ERR_DEVICE, "static scratch address not available on this device");
     if ((st = allow_lds(p, t)) != MXL_OK) return st;
     double *spill = p.spill_elems > 0 ? (double *)(base + kNoAllocQueueBytes) : nullptr;
-    hipError_t e = launch_batch_on(*Bt, t, *crit, b, x, iters, rel_res, status, p.cap, p.ell_budget,
-                                   Bt->ctx->stream, (unsigned *)base, spill);
+    hipError_t e = classes ? launch_classes(*Bt, t, *crit, b, x, iters, rel_res, status, p.cap, p.ell_budget,
+                                            Bt->ctx->stream, (unsigned *)base, spill)
+                           : launch_batch_on(*Bt, t, *crit, b, x, iters, rel_res, status, p.cap, p.ell_budget,
+                                             Bt->ctx->stream, (unsigned *)base, spill);
     if (e != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string("batched launch: ") + hipGetErrorString(e));
     return MXL_OK;
 } catch (...) {
@@ -1125,9 +1439,24 @@ extern "C" mxl_status mxl_batch_autotune(const mxl_op *Bop, const mxl_criteria *
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);
     (void)hipEventCreate(&e1);
-    double best = 1e300;
+    double best = 1e300, cls_ms = 1e300;
     mxl_tuning bt = default_tuning();
     st = MXL_OK;
+    // one schedule, timed reps times after a run that warms the caches
+    auto timed = [&](const mxl_tuning &t, bool classes) {
+        std::vector<float> ts;
+        for (int r = 0; r < reps + 1 && st == MXL_OK; ++r) {
+            (void)hipEventRecord(e0, s);
+            st = run_schedule(*Bt, t, *crit, b, x_scratch, (int32_t *)it, (double *)rl, (uint8_t *)stt, classes);
+            (void)hipEventRecord(e1, s);
+            (void)hipEventSynchronize(e1);
+            float ms = 0.f;
+            (void)hipEventElapsedTime(&ms, e0, e1);
+            if (r > 0) ts.push_back(ms);
+        }
+        std::sort(ts.begin(), ts.end());
+        return ts.empty() ? 1e300 : (double)ts[ts.size() / 2];
+    };
     std::vector<int> fmts{1};
     if (Bt->ell) fmts.push_back(2);
     for (int fmt : fmts) {
@@ -1137,19 +1466,8 @@ extern "C" mxl_status mxl_batch_autotune(const mxl_op *Bop, const mxl_criteria *
             if (B * wpc > 2048) continue;  // at most 32 waves per CU
             for (int ord : {0, 1}) {
                 mxl_tuning t{B, wpc, ord, fmt};
-                std::vector<float> ts;
-                for (int r = 0; r < reps + 1 && st == MXL_OK; ++r) {
-                    (void)hipEventRecord(e0, s);
-                    st = run_schedule(*Bt, t, *crit, b, x_scratch, (int32_t *)it, (double *)rl, (uint8_t *)stt);
-                    (void)hipEventRecord(e1, s);
-                    (void)hipEventSynchronize(e1);
-                    float ms = 0.f;
-                    (void)hipEventElapsedTime(&ms, e0, e1);
-                    if (r > 0) ts.push_back(ms);  // the first run warms caches
-                }
+                const double med = timed(t, false);
                 if (st != MXL_OK) break;
-                std::sort(ts.begin(), ts.end());
-                double med = ts[ts.size() / 2];
                 if (med < best) { best = med; bt = t; }
             }
             if (st != MXL_OK) break;
@@ -1157,10 +1475,13 @@ extern "C" mxl_status mxl_batch_autotune(const mxl_op *Bop, const mxl_criteria *
         if (st != MXL_OK) break;
     }
     }
+    // the size-class schedule, with the best of them for the systems no class holds
+    if (st == MXL_OK && Bt->ell && Bt->cls_begin[5] > 0) cls_ms = timed(bt, true);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     (void)hipFree(it); (void)hipFree(rl); (void)hipFree(stt);
     if (st != MXL_OK) return st;
+    Bt->cls_best = cls_ms <= best;
     Bt->best = bt;
     Bt->tuned = true;
     if (best_out) *best_out = bt;
