@@ -123,6 +123,7 @@ struct MatrixImpl {
     int format = MXL_FMT_CSR;
     int variant = MXL_CSR_VECTOR;
     int vw = 32;                       // CSR vector lanes per row
+    int csr_rows = 0;                  // rows per wave of the staged CSR kernel; 0: vw lanes a row
     BufPtr row_ptr, col, val;          // canonical CSR (always present)
     BufPtr coo_row;                    // COO
     BufPtr ell_col, ell_val, ell_win;  // ELL / HYB ELL part
@@ -291,6 +292,7 @@ struct SpmvArgs {
 // ------------------------------------------------------------- spmv.hip
 void spmv_plan(MatrixImpl &A);
 int spmv_slots(const MatrixImpl &A);
+int csr_rows_per_wave(int64_t n, int64_t nnz);
 int64_t merge_tiles(int64_t n, int64_t nnz);
 int64_t coo_tiles(int64_t nnz);
 int64_t carry_bytes(int64_t ntiles);

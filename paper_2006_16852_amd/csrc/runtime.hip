@@ -317,6 +317,7 @@ mxl_status mxl_csr_create(mxl_ctx *ctx, mxl_dtype dtype, int64_t nrows, int64_t 
     A->format = MXL_FMT_CSR;
     A->variant = MXL_CSR_VECTOR;
     A->vw = auto_vector_width(nrows, nnz);
+    A->csr_rows = csr_rows_per_wave(nrows, nnz);
     compute_stored_bytes(*A);
     finish_matrix(*A);
     *Aout = wrap_matrix(A);
@@ -401,6 +402,7 @@ mxl_status mxl_convert(const mxl_op *Aop, mxl_format fmt, const mxl_format_param
             if (w != 2 && w != 4 && w != 8 && w != 16 && w != 32 && w != 64)
                 return fail(MXL_ERR_INVALID_ARG, "vector_width must be 2, 4, 8, 16, 32 or 64");
             A->vw = w;
+            if (prm.vector_width <= 0) A->csr_rows = csr_rows_per_wave(S.nrows, S.nnz);
         } else if (prm.variant == MXL_CSR_MERGE) {
             if ((st = build_merge(*A)) != MXL_OK) return st;
         } else if (prm.variant == MXL_CSR_STREAM) {

@@ -145,6 +145,170 @@ __global__ __launch_bounds__(kWG) void k_csr_vector(int64_t n, const int *__rest
     }
 }
 
+constexpr int kStreamK = 8;  // entries per lane in flight of the swept rows
+
+// -------------------------------------------------------- staged CSR rows
+// The operator as wrapped: nothing is known of its rows beyond their mean
+// length and nothing is prepared.  A wave takes `rw` consecutive rows and cuts
+// them, by their row pointers, into runs of at most kRowsCap entries, whose
+// columns and values it loads as kRowsK independent coalesced loads a lane.
+//
+//  * A run of m rows of similar length is parked in LDS as it is and walked by
+//    rows, g = 64 / m lanes to a row: one gather then covers the same position
+//    of neighbouring rows, in a stencil consecutive x, and not the 64
+//    consecutive entries of two or three rows, far apart in x.
+//  * In a run of unequal rows every lane gathers for the entries it loaded and
+//    the products are parked; g lanes sum each row.  A long row then costs
+//    LDS reads, where the walk would gather with a few lanes active.
+//  * A row longer than kRowsCap is swept by the whole wave.
+//
+// Loads past the end of a run or row repeat its last entry and are left out of
+// the sum: a load under a lane mask makes the compiler wait for it before the
+// next.
+//
+// Bound by the matrix stream and, per run, its chain row pointers - entries -
+// gathers - sum, which only other waves hide: 24 a CU with kRowsK = 8 (6 KB of
+// LDS a wave in FP64).  kRowsK = 12 and 16 hold fewer and take 91 and 110 us on
+// the 7-point matrix, g rounded to a power of two 174 us on the 27-point one.
+// W lanes a row (k_csr_vector) -> this, us:
+//   27-point 128^3         FP64 235 -> 157 (4.4 TB/s)   FP32 195 -> 110
+//   7-point 160^3          FP64 112 -> 79               FP32  91 -> 58
+//   power law, n = 450,001, 10.2 M entries, rows up to 7,100:  222 -> 80
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kRowsK = 8;                  // entries a lane loads at a time
+constexpr int kRowsCap = kRowsK * kWave;   // entries of a run
+
+template <typename V, bool DOT>
+__global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *__restrict__ rp,
+                                                  const int *__restrict__ col, const V *__restrict__ val,
+                                                  SpmvK<V> p) {
+    if (p.stop && *p.stop) return;
+    constexpr int WPG = kWG / kWave;
+    __shared__ V s_val[WPG][kRowsCap];
+    __shared__ int s_col[WPG][kRowsCap];
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    V *sv = s_val[wid];
+    int *sc = s_col[wid];
+    const int G = (int)gridDim.x, nw = G * WPG;
+    const int vid = (G % kNumXcd == 0)
+                        ? ((int)(blockIdx.x / kNumXcd) * WPG + wid) * kNumXcd + (int)(blockIdx.x % kNumXcd)
+                        : (int)blockIdx.x * WPG + wid;
+    int64_t b0, b1;
+    int bs;
+    band_walk((n + rw - 1) / rw, vid, nw, b0, b1, bs);
+    double dacc = 0.0;
+    auto store = [&](int64_t row, V acc) {
+        const V out = combine(p, acc, row);
+        p.y[row] = out;
+        if (DOT) dacc += (double)p.w[row] * (double)out;
+    };
+    for (int64_t b = b0; b < b1; b += bs) {
+        const int64_t r0 = b * rw;
+        const int nr = (int)(n - r0 < rw ? n - r0 : rw);
+        const int64_t rl = r0 + (lane < nr ? lane : nr - 1);
+        const int rs = rp[rl], re = rp[rl + 1];
+        for (int i = 0; i < nr;) {  // a run of rows i .. i + m - 1 of the block
+            const int k0 = __builtin_amdgcn_readlane(rs, i);
+            // row ends ascend, so the rows that fit are consecutive from i
+            const int m = __popcll(__ballot(lane < nr && lane >= i && re - k0 <= kRowsCap));
+            const int k1 = __builtin_amdgcn_readlane(re, m ? i + m - 1 : i), tot = k1 - k0;
+            // the offsets below are cheaper to form again than to keep in
+            // registers across the loop
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            if (m == 0) {
+                V acc = 0;
+                for (uint32_t kb = (uint32_t)k0; kb < (uint32_t)k1; kb += kStreamK * kWave) {
+                    int c[kStreamK];
+                    V v[kStreamK];
+#pragma unroll
+                    for (int j = 0; j < kStreamK; ++j) {
+                        const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)k1 - 1 - kb);
+                        c[j] = ld_stream(col + kb + k);
+                        v[j] = ld_stream(val + kb + k);
+                    }
+#pragma unroll
+                    for (int j = 0; j < kStreamK; ++j) {
+                        const V t = v[j] * p.x[(uint32_t)c[j]];
+                        acc += kb + ln + kWave * j < (uint32_t)k1 ? t : (V)0;
+                    }
+                }
+                acc = wave_sum(acc);
+                if (lane == 0) store(r0 + i, acc);
+                ++i;
+                continue;
+            }
+            V acc = 0;
+            const int g = kWave / m;
+            const int row = (ln * (65536 / g + 1)) >> 16, part = ln - row * g;  // ln / g, ln % g
+            if (tot > 0) {
+                int c[kRowsK];
+                V v[kRowsK];
+#pragma unroll
+                for (int j = 0; j < kRowsK; ++j) {
+                    const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)(tot - 1));
+                    c[j] = ld_stream(col + k0 + k);
+                    v[j] = ld_stream(val + k0 + k);
+                }
+                const int src = row < m ? i + row : i;
+                const int q0 = __shfl(rs, src, kWave) - k0, qe = __shfl(re, src, kWave) - k0;  // by all lanes
+                const int q1 = row < m ? qe : q0;
+                // unequal rows: one has more than 3/2 of the run's mean length
+                const bool uneven = __any((q1 - q0) * m > tot + tot / 2 + 8);
+                if (uneven) {
+#pragma unroll
+                    for (int j = 0; j < kRowsK; ++j) sv[ln + kWave * j] = v[j] * p.x[(uint32_t)c[j]];
+                    wave_lds_fence();
+                    for (int q = q0 + part; q < q1; q += g) acc += sv[q];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < kRowsK; ++j) {
+                        sc[ln + kWave * j] = c[j];
+                        sv[ln + kWave * j] = v[j];
+                    }
+                    wave_lds_fence();
+                    constexpr int U = 9;  // gathers a lane has in flight
+                    for (int q = q0 + part; __any(q < q1); q += U * g) {
+                        int cc[U];
+                        V vv[U], xv[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const int e = q + u * g, ec = e < q1 ? e : kRowsCap - 1;
+                            cc[u] = sc[ec];
+                            vv[u] = sv[ec];
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) xv[u] = p.x[(uint32_t)cc[u]];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const V t = vv[u] * xv[u];
+                            acc += q + u * g < q1 ? t : (V)0;
+                        }
+                    }
+                }
+                for (int h = g; h > 1;) {  // g is any number: fold the upper half onto the lower
+                    const int up = (h + 1) / 2;
+                    const V t = __shfl_down(acc, up, kWave);
+                    if (part + up < h) acc += t;
+                    h = up;
+                }
+            }
+            if (row < m && part == 0) store(r0 + i + row, acc);
+            __builtin_amdgcn_wave_barrier();  // reads done before the next run's writes
+            i += m;
+        }
+    }
+    if (DOT) {
+        double vv[1] = {dacc};
+        publish<1>(vv, p.partials, p.slot_base + (int)blockIdx.x);
+    }
+}
+
 // ------------------------------------------------------- row-block CSR
 // Rows are cut (once, at conversion) into blocks of at most kStreamRows
 // consecutive rows holding at most kStreamK*64 nonzeros; a row longer than
@@ -155,7 +319,6 @@ __global__ __launch_bounds__(kWG) void k_csr_vector(int64_t n, const int *__rest
 // l sums the products of row first+l in order.  A long row is swept by the
 // whole wave and reduced by shuffles.  No workgroup barrier is involved:
 // every wave walks its own blocks.
-constexpr int kStreamK = 8;
 constexpr int kStreamRows = 63;  // a lane reads the next row's start from its neighbour
 
 template <typename V, bool DOT>
@@ -1091,6 +1254,21 @@ static int walker_grid(int64_t units, int cap) {
 // points hold 181 registers and take 30.6 us), else one.
 static int stencil_rpt(const MatrixImpl &A) { return A.nx % 2 == 0 ? 2 : 1; }
 
+// Rows per wave of the staged CSR kernel, or 0: W lanes a row.  Short rows fill
+// a tenth of a run and leave nothing to stage (us, W lanes / staged, n = 10^6:
+// 1 entry a row FP64 8.1 / 14.0, 2: 12.3 / 17.0, 3: 20.1 / 18.0 and FP32 11.8 /
+// 12.3, 4: 23.4 / 19.2 and 13.2 / 14.7, 5 (a 5-point 1024^2): 27.5 / 19.7 and
+// 22.2 / 14.8), so the line is above 4 a row.  64 rows fill their runs with rows
+// of any length; fewer are taken while that leaves waves idle (27-point 50^3
+// FP64: 16.1 us with 64, 12.7 with 32, 12.0 with 16), but below 8 only rows that
+// fill the runs by themselves.
+int csr_rows_per_wave(int64_t n, int64_t nnz) {
+    if (nnz <= 4 * n) return 0;
+    int rw = kWave;
+    while (rw > 1 && n / rw < 4096 && (rw > 8 || (double)rw * (double)nnz > (double)kRowsCap * (double)n)) rw /= 2;
+    return rw;
+}
+
 void spmv_plan(MatrixImpl &A) {
     const int cap = spmv_grid_cap(A);
     A.grid_main = A.grid_tail = 0;
@@ -1098,6 +1276,8 @@ void spmv_plan(MatrixImpl &A) {
     switch (A.format) {
     case MXL_FMT_CSR:
         if (A.variant == MXL_CSR_SCALAR) A.grid_main = grid_for((A.nrows + kWG - 1) / kWG, cap);
+        else if (A.variant == MXL_CSR_VECTOR && A.csr_rows)
+            A.grid_main = walker_grid((A.nrows + A.csr_rows - 1) / A.csr_rows, cap);
         else if (A.variant == MXL_CSR_VECTOR)
             A.grid_main = grid_for((A.nrows + kWG / A.vw - 1) / (kWG / A.vw), cap);
         else if (A.variant == MXL_CSR_STREAM) A.grid_main = walker_grid(A.ntiles, cap);
@@ -1186,6 +1366,11 @@ static hipError_t spmv_typed(const MatrixImpl &A, const SpmvArgs &a, hipStream_t
         if (A.variant == MXL_CSR_SCALAR) {
             if (dot) hipLaunchKernelGGL((k_csr_scalar<V, true>), dim3(A.grid_main), blk, 0, s, n, rp, col, val, p);
             else hipLaunchKernelGGL((k_csr_scalar<V, false>), dim3(A.grid_main), blk, 0, s, n, rp, col, val, p);
+        } else if (A.variant == MXL_CSR_VECTOR && A.csr_rows) {
+            // without partials to bound the grid, a block of rows a wave: whoever is done takes the next
+            const dim3 gr(dot ? A.grid_main : walker_grid((n + A.csr_rows - 1) / A.csr_rows, 1 << 20));
+            if (dot) hipLaunchKernelGGL((k_csr_rows<V, true>), gr, blk, 0, s, n, A.csr_rows, rp, col, val, p);
+            else hipLaunchKernelGGL((k_csr_rows<V, false>), gr, blk, 0, s, n, A.csr_rows, rp, col, val, p);
         } else if (A.variant == MXL_CSR_VECTOR) {
 #define MXL_VEC_CASE(WW)                                                                                   \
     case WW:                                                                                               \
