@@ -76,7 +76,9 @@ enum {
 
 typedef struct {
     int32_t variant;       /* MXL_CSR_* / MXL_ELL_* ... */
-    int32_t vector_width;  /* CSR vector: lanes per row (0 = from mean row length);
+    int32_t vector_width;  /* CSR vector: lanes per row (0, and a CSR operator as wrapped =
+                              from the mean row length; runs of rows staged in LDS above
+                              4 entries a row);
                               ELL/HYB: rows per thread 1, 2 or 4 (0 = 2) */
     double  hyb_quantile;  /* HYB: ELL width = nearest-rank quantile of row lengths (0 = 0.9) */
 } mxl_format_params;
