@@ -373,8 +373,8 @@ __device__ __forceinline__ double swap_add(double v) {
            __longlong_as_double((long long)((unsigned long long)h1 << 32 | l1));
 }
 
-// Sum over the B-thread workgroup (at most 8 waves), in every thread; red: 8
-// doubles not in use by another sum since the barrier before the last one.
+// Sum over the B-thread workgroup (at most 16 waves), in every thread; red:
+// B / 64 doubles not in use by another sum since the barrier before the last one.
 template <int B>
 __device__ __forceinline__ double cls_sum(double v, double *red) {
     constexpr int NW = B / kWave;
@@ -388,6 +388,7 @@ __device__ __forceinline__ double cls_sum(double v, double *red) {
         if (lane == 0) red[wid] = v;
         __syncthreads();
         v = red[lane % NW];
+        if constexpr (NW > 8) v += dpp_move<kDppRor8>(v);
         if constexpr (NW > 4) v += dpp_move<kDppRor4>(v);
         if constexpr (NW > 2) v += dpp_move<kDppRor2>(v);
         v += dpp_move<kDppRor1>(v);
@@ -396,7 +397,7 @@ __device__ __forceinline__ double cls_sum(double v, double *red) {
 }
 
 // Two sums at once: after one exchange even lanes carry u and odd lanes v, so
-// the two cost little more than one.  red: 16 doubles.
+// the two cost little more than one.  red: B / 32 doubles.
 template <int B>
 __device__ __forceinline__ void cls_sum2(double &u, double &v, double *red) {
     constexpr int NW = B / kWave;
@@ -412,6 +413,7 @@ __device__ __forceinline__ void cls_sum2(double &u, double &v, double *red) {
         if (lane < 2) red[2 * wid + lane] = t;
         __syncthreads();
         t = red[lane % (2 * NW)];
+        if constexpr (NW > 8) t = swap_add<false>(t);
         if constexpr (NW > 4) t += dpp_move<kDppRor8>(t);
         if constexpr (NW > 2) t += dpp_move<kDppRor4>(t);
         t += dpp_move<kDppRor2>(t);
@@ -419,6 +421,20 @@ __device__ __forceinline__ void cls_sum2(double &u, double &v, double *red) {
     const double o = dpp_move<kDppXor1>(t);
     u = odd ? o : t;
     v = odd ? t : o;
+}
+
+// The largest rr with sqrt(rr) <= tol, so that a criterion on the norm is one
+// compare; ok = false where tol^2 leaves the normal range.
+__device__ __forceinline__ double norm2_bound(double tol, bool &ok) {
+    double top = tol * tol;
+    ok = top > 1e-290 && top < 1e290;
+    if (ok) {
+        while (sqrt(top) > tol) top = __longlong_as_double(__double_as_longlong(top) - 1);
+        for (double up = __longlong_as_double(__double_as_longlong(top) + 1); sqrt(up) <= tol;
+             up = __longlong_as_double(__double_as_longlong(up) + 1))
+            top = up;
+    }
+    return top;
 }
 
 // Jacobi-PCG of the systems of one size class, a workgroup each, with nothing
@@ -488,15 +504,8 @@ __global__ __launch_bounds__(B) __attribute__((amdgpu_waves_per_eu(RPT * W > 32 
     if (threadIdx.x == 0) p_lds[n] = 0.0;
     cls_sum2<B>(rho, bb, redC);
     const double nb = sqrt(bb), tol = red_factor * nb;
-    // sqrt(rr) <= tol without the root: the largest rr that meets it
-    double top = tol * tol;
-    const bool by_top = top > 1e-290 && top < 1e290;
-    if (by_top) {
-        while (sqrt(top) > tol) top = __longlong_as_double(__double_as_longlong(top) - 1);
-        for (double up = __longlong_as_double(__double_as_longlong(top) + 1); sqrt(up) <= tol;
-             up = __longlong_as_double(__double_as_longlong(up) + 1))
-            top = up;
-    }
+    bool by_top;
+    const double top = norm2_bound(tol, by_top);  // sqrt(rr) <= tol without the root
     auto met = [&](double rr) { return by_top ? rr <= top : sqrt(rr) <= tol; };
     const int64_t maxit = max_iters_fixed > 0 ? max_iters_fixed : (int64_t)iter_factor * n;
     int stop = ST_RUN;
@@ -599,174 +608,179 @@ __global__ void k_batch_to_ell(const int *__restrict__ sys_ptr, const int *__res
     }
 }
 
-// Whole Jacobi-PCG of one small system in one workgroup with the matrix
-// held in registers: thread t owns rows t + j*B (j < RPT) and keeps their
-// (at most W) entries, r and p in registers; p, which the product gathers,
-// is mirrored in LDS.  x and dinv stay in global memory for the large
-// shapes (register budget) and in registers when REG; a one-wave shape
-// (B = 64) reduces with lane shuffles only.  An iteration is the product,
-// two reductions and the updates.
-template <int B, int RPT, int W, bool REG>
+// The rows of a single-workgroup system, thread t owning rows t + j*B (j < RPT):
+// their (at most W) entries in registers, the vector they are multiplied with in
+// LDS (byte offsets; n <= 7680, so two fit a register, PACK).  Slot 0 holds the
+// diagonal where the row stores one: its factor is the thread's own element, in
+// a register, not an LDS read.
+template <int B, int RPT, int W, bool PACK>
+struct SmallRows {
+    static constexpr int NC = PACK ? W / 2 : W - 1;
+    double v[RPT][W];
+    unsigned c[RPT][NC], c0[(RPT + 1) / 2];
+    bool any0;  // a row of this wave has another entry in slot 0
+
+    __device__ __forceinline__ void load(int n, const int *__restrict__ rp, const int *__restrict__ col,
+                                         const double *__restrict__ val) {
+        bool other = false;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            const int i = (int)threadIdx.x + j * B;
+            const bool own = i < n;
+            const int e0 = own ? rp[i] : 0, e1 = own ? rp[i + 1] : 0;
+            // padding points at the thread's own row (value 0): SPD systems
+            // store their diagonal, so padding adds no new dependency
+            const unsigned self = 8u * (unsigned)(own ? i : 0);
+            int d = 0;
+#pragma unroll
+            for (int e = W - 1; e > 0; --e)
+                if (e0 + e < e1 && col[e0 + e] == i) d = e;
+            if (e0 < e1 && col[e0] == i) d = 0;
+            unsigned t = self;
+#pragma unroll
+            for (int e = 0; e < W; ++e) {  // entry d to slot 0, the others in their order
+                const int k = e0 + (e == 0 ? d : (e <= d ? e - 1 : e));
+                const unsigned o = k < e1 ? 8u * (unsigned)col[k] : self;
+                v[j][e] = k < e1 ? val[k] : 0.0;
+                if (e == 0) t = o;
+                else if constexpr (!PACK) c[j][e - 1] = o;
+                else c[j][(e - 1) / 2] = (e - 1) & 1 ? c[j][(e - 1) / 2] | o << 16 : o;
+            }
+            c0[j / 2] = j & 1 ? c0[j / 2] | t << 16 : t;
+            other |= t != self;
+        }
+        any0 = __any(other);
+    }
+    // q = A u for the thread's rows; own: the thread's elements of u, which
+    // also stands in LDS
+    __device__ __forceinline__ void product(const double (&own)[RPT], const double *u, double (&q)[RPT]) {
+        const char *lds = (const char *)u;
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) q[j] = v[j][0] * own[j];
+        if (any0) {
+#pragma unroll
+            for (int j = 0; j < RPT; ++j)
+                q[j] = v[j][0] * *(const double *)(lds + (j & 1 ? c0[j / 2] >> 16 : c0[j / 2] & 0xffffu));
+        }
+#pragma unroll
+        for (int j = 0; j < RPT; ++j)
+#pragma unroll
+            for (int e = 0; e < W - 1; ++e) {
+                unsigned o;
+                if constexpr (PACK) {
+                    // unpacked ahead of the iterations they would take twice the registers
+                    if (!(e & 1)) asm volatile("" : "+v"(c[j][e / 2]));
+                    o = e & 1 ? c[j][e / 2] >> 16 : c[j][e / 2] & 0xffffu;
+                } else o = c[j][e];
+                q[j] += v[j][e + 1] * *(const double *)(lds + o);
+            }
+    }
+};
+
+// Whole Jacobi-PCG of one small system in one workgroup: the rows, x, r, p and
+// dinv in registers; p, which the product gathers, is mirrored in LDS.  An
+// iteration is the product, two reductions and the updates, and touches no
+// memory.
+//
+// Bound by one CU's iteration: vector instructions (61% of the cycles at 4096
+// rows), the LDS reads of the product, three barriers, two reductions (lane
+// moves, no LDS shuffles) and two quotients.  5-point systems, us a solve, with
+// x and dinv in global memory and shuffles -> this: 64^2 734 -> 374 (1.85 an
+// iteration), 32^2 303 -> 146, 16^2 162 -> 84.  1024 threads of four rows take
+// 529 at 64^2 (twice the waves repeat the reductions), dots summed by halves
+// 391.
+template <int B, int RPT, int W>
 __global__ __launch_bounds__(B) void k_small_pcg(int n, const int *__restrict__ rp,
                                                  const int *__restrict__ col,
                                                  const double *__restrict__ val,
                                                  const double *__restrict__ dinv,
                                                  const double *__restrict__ b,
                                                  double *__restrict__ xio, double red_factor,
-                                                 int64_t maxit, int chk, int use_x0,
-                                                 void *__restrict__ out3) {
-    extern __shared__ double p_lds[];
+                                                 int64_t maxit, int chk, void *__restrict__ out3) {
+    __shared__ double p_lds[B * RPT];  // rows past n hold zeros that nobody reads
     constexpr int NW = B / kWave;
-    __shared__ double redA[NW], redB[2 * NW], redC[3 * NW];
-    const int tid = threadIdx.x, lane = tid % kWave, wid = tid / kWave;
-    int c[RPT][W];
-    double v[RPT][W];
-    double r[RPT], pr[RPT];
-    double xr[REG ? RPT : 1], dv[REG ? RPT : 1];
+    __shared__ double redA[NW], redB[2 * NW], redC[2 * NW], redD[NW];
+    const int tid = threadIdx.x;
+    SmallRows<B, RPT, W, (W > 8)> A;
+    double x[RPT], r[RPT], pr[RPT], dv[RPT], q[RPT];
+    A.load(n, rp, col, val);
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
         const int i = tid + j * B;
         const bool own = i < n;
-        if constexpr (REG) {
-            dv[j] = own ? dinv[i] : 0.0;
-            xr[j] = own && use_x0 ? xio[i] : 0.0;
-        }
-        const int e0 = own ? rp[i] : 0, e1 = own ? rp[i + 1] : 0;
-#pragma unroll
-        for (int e = 0; e < W; ++e) {
-            const bool in = e0 + e < e1;
-            // padding points at the thread's own row (value 0): SPD systems
-            // store their diagonal, so padding adds no new dependency
-            c[j][e] = in ? col[e0 + e] : (own ? i : 0);
-            v[j][e] = in ? val[e0 + e] : 0.0;
-        }
-        if (own) p_lds[i] = use_x0 ? xio[i] : 0.0;
+        dv[j] = own ? dinv[i] : 0.0;
+        x[j] = own ? xio[i] : 0.0;
+        p_lds[i] = x[j];
     }
     __syncthreads();
-    double rz = 0.0, rr = 0.0, bb = 0.0;
+    A.product(x, p_lds, q);
+    double rho = 0.0, rr = 0.0, bb = 0.0;
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
         const int i = tid + j * B;
-        double ax = 0.0;
-        if (use_x0) {
-#pragma unroll
-            for (int e = 0; e < W; ++e) ax += v[j][e] * p_lds[c[j][e]];
-        }
-        const bool own = i < n;
-        const double bi = own ? b[i] : 0.0;
-        r[j] = bi - ax;
-        if constexpr (REG) pr[j] = dv[j] * r[j];
-        else pr[j] = own ? dinv[i] * r[j] : 0.0;
-        rz += r[j] * pr[j];
+        const double bi = i < n ? b[i] : 0.0;
+        r[j] = bi - q[j];
+        pr[j] = dv[j] * r[j];
+        rho += r[j] * pr[j];
         rr += r[j] * r[j];
         bb += bi * bi;
     }
     __syncthreads();  // the initial guess in p_lds is consumed
 #pragma unroll
-    for (int j = 0; j < RPT; ++j) {
-        const int i = tid + j * B;
-        if (i < n) {
-            p_lds[i] = pr[j];
-            if (!REG && !use_x0) xio[i] = 0.0;
-        }
-    }
-    rz = wave_sum(rz);
-    rr = wave_sum(rr);
-    bb = wave_sum(bb);
-    if constexpr (NW > 1) {
-        if (lane == 0) { redC[wid] = rz; redC[NW + wid] = rr; redC[2 * NW + wid] = bb; }
-        __syncthreads();
-        rz = rr = bb = 0.0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) { rz += redC[w]; rr += redC[NW + w]; bb += redC[2 * NW + w]; }
-    } else {
-        __syncthreads();  // p_lds complete before the first product
-    }
-    const double nb = sqrt(bb);
+    for (int j = 0; j < RPT; ++j) p_lds[tid + j * B] = pr[j];
+    cls_sum2<B>(rho, rr, redC);
+    bb = cls_sum<B>(bb, redD);
+    const double nb = sqrt(bb), tol = red_factor * nb;
+    bool by_top;
+    const double top = norm2_bound(tol, by_top);
+    auto met = [&](double s) { return by_top ? s <= top : sqrt(s) <= tol; };
     int stop = ST_RUN;
     int64_t k = 0;
     if (bb == 0.0) {
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            if constexpr (REG) xr[j] = 0.0;
-            else if (tid + j * B < n) xio[tid + j * B] = 0.0;
-        }
+        for (int j = 0; j < RPT; ++j) x[j] = 0.0;
         stop = ST_CONVERGED;
-    } else if (sqrt(rr) <= red_factor * nb) {
+    } else if (met(rr)) {
         stop = ST_CONVERGED;
     }
-    double rho = rz;
     while (stop == ST_RUN && k < maxit) {
-        double q[RPT];
-        double pq = 0.0;
-#pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            double a = 0.0;
-#pragma unroll
-            for (int e = 0; e < W; ++e) a += v[j][e] * p_lds[c[j][e]];
-            q[j] = a;
-            pq += pr[j] * a;
-        }
-        pq = wave_sum(pq);
+        __syncthreads();  // p complete
+        A.product(pr, p_lds, q);
         double eta = 0.0;
-        if constexpr (NW > 1) {
-            if (lane == 0) redA[wid] = pq;
-            __syncthreads();
 #pragma unroll
-            for (int w = 0; w < NW; ++w) eta += redA[w];
-        } else {
-            eta = pq;
-        }
+        for (int j = 0; j < RPT; ++j) eta += pr[j] * q[j];
+        eta = cls_sum<B>(eta, redA);
         if (chk && !finite_d(eta)) { stop = ST_NONFINITE; break; }
         if (eta <= 0.0) { stop = ST_BREAKDOWN; break; }
         const double alpha = rho / eta;
-        double rzn = 0.0, rrn = 0.0;
-        double z[RPT];
+        double rzn = 0.0;
+        rr = 0.0;
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
-            const int i = tid + j * B;
-            const bool own = i < n;
+            x[j] += alpha * pr[j];
             r[j] -= alpha * q[j];
-            if constexpr (REG) {
-                xr[j] += alpha * pr[j];
-                z[j] = dv[j] * r[j];
-            } else {
-                if (own) xio[i] += alpha * pr[j];
-                z[j] = own ? dinv[i] * r[j] : 0.0;
-            }
-            rzn += r[j] * z[j];
-            rrn += r[j] * r[j];
+            q[j] = dv[j] * r[j];  // z
+            rzn += r[j] * q[j];
+            rr += r[j] * r[j];
         }
-        rzn = wave_sum(rzn);
-        rrn = wave_sum(rrn);
-        if constexpr (NW > 1) {
-            if (lane == 0) { redB[wid] = rzn; redB[NW + wid] = rrn; }
-            __syncthreads();
-            rzn = rrn = 0.0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) { rzn += redB[w]; rrn += redB[NW + w]; }
-        }
+        cls_sum2<B>(rzn, rr, redB);
         ++k;
-        rr = rrn;
         if (chk && !finite_d(rr)) { stop = ST_NONFINITE; break; }
-        if (sqrt(rr) <= red_factor * nb) { stop = ST_CONVERGED; break; }
+        if (met(rr)) { stop = ST_CONVERGED; break; }
         if (chk && !finite_d(rzn)) { stop = ST_NONFINITE; break; }
         if (rzn == 0.0) { stop = ST_BREAKDOWN; break; }
         const double beta = rzn / rho;
         rho = rzn;
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
-            pr[j] = z[j] + beta * pr[j];
-            if (tid + j * B < n) p_lds[tid + j * B] = pr[j];
+            pr[j] = q[j] + beta * pr[j];
+            p_lds[tid + j * B] = pr[j];
         }
-        __syncthreads();
     }
     if (stop == ST_RUN) stop = ST_MAX_ITERS;
-    if constexpr (REG) {
 #pragma unroll
-        for (int j = 0; j < RPT; ++j)
-            if (tid + j * B < n) xio[tid + j * B] = xr[j];
-    }
+    for (int j = 0; j < RPT; ++j)
+        if (tid + j * B < n) xio[tid + j * B] = x[j];
     if (tid == 0) {
         *(int32_t *)out3 = (int32_t)k;
         *(double *)((char *)out3 + 8) = nb > 0.0 ? sqrt(rr) / nb : 0.0;
@@ -776,10 +790,12 @@ __global__ __launch_bounds__(B) void k_small_pcg(int n, const int *__restrict__ 
 
 // Whole Jacobi-BiCGSTAB of one small system in one workgroup, the steps
 // and checks of the per-step solver in its order (right preconditioning,
-// half-step exit x += alpha p_hat when ||s|| meets the criterion).  Thread t
-// owns rows t + j*B (j < RPT): their entries and r, r_hat, p, v, x and dinv
-// stay in registers; the vector the product gathers (p_hat, then s_hat) is
-// mirrored in LDS.  out3: iterations (int32 at 0), relative residual
+// half-step exit x += alpha p_hat when ||s|| meets the criterion; rho of the
+// next iteration is summed together with the residual norm).  The rows and r,
+// r_hat, p, v, x and dinv stay in registers; the vector the product gathers
+// (p_hat, then s_hat) is mirrored in LDS.  Between two writes of it lie the
+// barriers of at least one reduction, as between two uses of a reduction's
+// array.  out3: iterations (int32 at 0), relative residual
 // (double at 8), status (byte 16), half step (byte 17).
 template <int B, int RPT, int W>
 __global__ __launch_bounds__(B) void k_small_bicgstab(int n, const int *__restrict__ rp,
@@ -789,81 +805,69 @@ __global__ __launch_bounds__(B) void k_small_bicgstab(int n, const int *__restri
                                                       const double *__restrict__ b,
                                                       double *__restrict__ xio, double red_factor,
                                                       int64_t maxit, int chk, void *__restrict__ out3) {
-    extern __shared__ double pl[];
-    __shared__ double red[2 * (B / kWave)];
+    __shared__ double pl[B * RPT];  // rows past n hold zeros that nobody reads
+    constexpr int NW = B / kWave;
+    __shared__ double redA[NW], redB[NW], redC[2 * NW], redD[2 * NW], redE[2 * NW], redF[NW];
     const int tid = threadIdx.x;
-    int c[RPT][W];
-    double a[RPT][W];
-    double r[RPT], rh[RPT], p[RPT], v[RPT], x[RPT], dv[RPT];
+    SmallRows<B, RPT, W, (RPT * W > 32)> A;
+    double r[RPT], rh[RPT], p[RPT], v[RPT], x[RPT], dv[RPT], h[RPT];
+    A.load(n, rp, col, val);
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
         const int i = tid + j * B;
         const bool own = i < n;
         dv[j] = own ? dinv[i] : 0.0;
         x[j] = own ? xio[i] : 0.0;
-        const int e0 = own ? rp[i] : 0, e1 = own ? rp[i + 1] : 0;
-#pragma unroll
-        for (int e = 0; e < W; ++e) {
-            const bool in = e0 + e < e1;
-            c[j][e] = in ? col[e0 + e] : (own ? i : 0);  // padding: own row, value 0
-            a[j][e] = in ? val[e0 + e] : 0.0;
-        }
-        if (own) pl[i] = x[j];
+        pl[i] = x[j];
     }
     __syncthreads();
-    double rr = 0.0, bb = 0.0;
+    A.product(x, pl, v);
+    double rr = 0.0, bb = 0.0, rho = 0.0;
 #pragma unroll
     for (int j = 0; j < RPT; ++j) {
         const int i = tid + j * B;
-        double ax = 0.0;
-#pragma unroll
-        for (int e = 0; e < W; ++e) ax += a[j][e] * pl[c[j][e]];
         const double bi = i < n ? b[i] : 0.0;
-        r[j] = bi - ax;
+        r[j] = bi - v[j];
         rh[j] = r[j];
         p[j] = 0.0;
         v[j] = 0.0;
         rr += r[j] * r[j];
         bb += bi * bi;
     }
-    wg_sum2<B>(rr, bb, red);
+    rho = rr;  // r_hat = r
+    cls_sum2<B>(rho, rr, redE);
+    bb = cls_sum<B>(bb, redF);
     const double nb = sqrt(bb);
     const double tol = red_factor * nb;
+    bool by_top;
+    const double top = norm2_bound(tol, by_top);
+    auto met = [&](double s) { return by_top ? s <= top : sqrt(s) <= tol; };
     int stop = ST_RUN, half = 0;
     int64_t k = 0;
     if (bb == 0.0) {
 #pragma unroll
         for (int j = 0; j < RPT; ++j) x[j] = 0.0;
         stop = ST_CONVERGED;
-    } else if (sqrt(rr) <= tol) {
+    } else if (met(rr)) {
         stop = ST_CONVERGED;
     }
     double rho_old = 1.0, alpha = 1.0, omega = 1.0;
     while (stop == ST_RUN && k < maxit) {
-        double rho = 0.0;
-#pragma unroll
-        for (int j = 0; j < RPT; ++j) rho += rh[j] * r[j];
-        rho = wg_sum<B>(rho, red);
         if (chk && !finite_d(rho)) { stop = ST_NONFINITE; break; }
         if (rho == 0.0) { stop = ST_BREAKDOWN; break; }
         const double beta = (rho / rho_old) * (alpha / omega);
-        __syncthreads();  // the previous product's reads of pl are done
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
             p[j] = r[j] + beta * (p[j] - omega * v[j]);
-            if (tid + j * B < n) pl[tid + j * B] = dv[j] * p[j];
+            h[j] = dv[j] * p[j];
+            pl[tid + j * B] = h[j];
         }
         __syncthreads();
+        A.product(h, pl, v);
         double rv = 0.0;
 #pragma unroll
-        for (int j = 0; j < RPT; ++j) {
-            double q = 0.0;
-#pragma unroll
-            for (int e = 0; e < W; ++e) q += a[j][e] * pl[c[j][e]];
-            v[j] = q;
-            rv += rh[j] * q;
-        }
-        rv = wg_sum<B>(rv, red);
+        for (int j = 0; j < RPT; ++j) rv += rh[j] * v[j];
+        rv = cls_sum<B>(rv, redA);
         if (chk && !finite_d(rv)) { stop = ST_NONFINITE; break; }
         if (rv == 0.0) { stop = ST_BREAKDOWN; break; }
         alpha = rho / rv;
@@ -874,8 +878,8 @@ __global__ __launch_bounds__(B) void k_small_bicgstab(int n, const int *__restri
             ss += r[j] * r[j];
         }
         ++k;
-        ss = wg_sum<B>(ss, red);
-        if (sqrt(ss) <= tol) {
+        ss = cls_sum<B>(ss, redB);
+        if (met(ss)) {
 #pragma unroll
             for (int j = 0; j < RPT; ++j) x[j] += alpha * (dv[j] * p[j]);
             rr = ss;
@@ -883,38 +887,38 @@ __global__ __launch_bounds__(B) void k_small_bicgstab(int n, const int *__restri
             stop = ST_CONVERGED;
             break;
         }
-        __syncthreads();  // all reads of p_hat done
-#pragma unroll
-        for (int j = 0; j < RPT; ++j)
-            if (tid + j * B < n) pl[tid + j * B] = dv[j] * r[j];
-        __syncthreads();
-        double tt = 0.0, ts = 0.0, t[RPT];
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
-            double q = 0.0;
-#pragma unroll
-            for (int e = 0; e < W; ++e) q += a[j][e] * pl[c[j][e]];
-            t[j] = q;
-            tt += q * q;
-            ts += q * r[j];
+            h[j] = dv[j] * r[j];
+            pl[tid + j * B] = h[j];
         }
-        wg_sum2<B>(tt, ts, red);
+        __syncthreads();
+        double tt = 0.0, ts = 0.0, t[RPT];
+        A.product(h, pl, t);
+#pragma unroll
+        for (int j = 0; j < RPT; ++j) {
+            tt += t[j] * t[j];
+            ts += t[j] * r[j];
+        }
+        cls_sum2<B>(tt, ts, redC);
         if (chk && (!finite_d(tt) || !finite_d(ts))) { stop = ST_NONFINITE; break; }
         if (tt == 0.0) { stop = ST_BREAKDOWN; break; }
         omega = ts / tt;
         double rn = 0.0;
+        rho_old = rho;
+        rho = 0.0;
 #pragma unroll
         for (int j = 0; j < RPT; ++j) {
             x[j] += alpha * (dv[j] * p[j]) + omega * (dv[j] * r[j]);
             r[j] = r[j] - omega * t[j];
             rn += r[j] * r[j];
+            rho += rh[j] * r[j];
         }
-        rn = wg_sum<B>(rn, red);
+        cls_sum2<B>(rn, rho, redD);
         rr = rn;
         if (chk && !finite_d(rn)) { stop = ST_NONFINITE; break; }
-        if (sqrt(rn) <= tol) { stop = ST_CONVERGED; break; }
+        if (met(rn)) { stop = ST_CONVERGED; break; }
         if (omega == 0.0) { stop = ST_BREAKDOWN; break; }
-        rho_old = rho;
     }
     if (stop == ST_RUN) stop = ST_MAX_ITERS;
 #pragma unroll
@@ -1537,28 +1541,40 @@ std::shared_ptr<BatchImpl> batch_from_matrix(const MatrixImpl &A, const void *di
 
 // The whole CG of one system in one workgroup (x holds the initial guess).
 // Register-cached single-workgroup shapes: (threads, rows per thread,
-// entries per row).  The first that holds the system is used.
+// entries per row), by rising work an iteration.  The first that holds the
+// system is used.
 struct SmallShape {
     int B, RPT, W;
 };
-static const SmallShape kSmallShapes[] = {{64, 2, 8}, {512, 8, 5}, {512, 4, 8}, {256, 4, 32}};
+static const SmallShape kSmallShapes[] = {{64, 2, 8},  {256, 2, 8}, {512, 2, 5},  {512, 2, 8},
+                                          {512, 4, 5}, {512, 4, 8}, {512, 2, 32}, {512, 8, 5}};
+
+// Index of the first shape that holds n rows of at most maxlen entries (ns: none).
+static int small_fit(const SmallShape *shapes, int ns, int n, int maxlen) {
+    for (int k = 0; k < ns; ++k)
+        if (n <= shapes[k].B * shapes[k].RPT && maxlen <= shapes[k].W) return k;
+    return ns;
+}
 
 static hipError_t launch_small(const SmallShape &sh, int n, const BatchImpl &Bt, const mxl_criteria &c,
                                const double *b, double *x, void *out3) {
-    const size_t shm = (size_t)n * sizeof(double);
     hipStream_t s = Bt.ctx->stream;
 #define MXL_SMALL(BB, RR, WW)                                                                        \
     if (sh.B == BB && sh.RPT == RR && sh.W == WW) {                                                  \
-        hipLaunchKernelGGL((k_small_pcg<BB, RR, WW, (BB == 64)>), dim3(1), dim3(BB), shm, s, n,       \
+        hipLaunchKernelGGL((k_small_pcg<BB, RR, WW>), dim3(1), dim3(BB), 0, s, n,                    \
                            (const int *)Bt.row_ptr->p, (const int *)Bt.col->p,                       \
                            (const double *)Bt.val->p, (const double *)Bt.dinv->p, b, x,              \
-                           c.reduction, c.max_iters, c.nonfinite_check, 1, out3);                    \
+                           c.reduction, c.max_iters, c.nonfinite_check, out3);                       \
         return hipGetLastError();                                                                    \
     }
     MXL_SMALL(64, 2, 8)
-    MXL_SMALL(512, 8, 5)
+    MXL_SMALL(256, 2, 8)
+    MXL_SMALL(512, 2, 5)
+    MXL_SMALL(512, 2, 8)
+    MXL_SMALL(512, 4, 5)
     MXL_SMALL(512, 4, 8)
-    MXL_SMALL(256, 4, 32)
+    MXL_SMALL(512, 2, 32)
+    MXL_SMALL(512, 8, 5)
 #undef MXL_SMALL
     return hipErrorInvalidValue;
 }
@@ -1566,7 +1582,7 @@ static hipError_t launch_small(const SmallShape &sh, int n, const BatchImpl &Bt,
 // The whole BiCGSTAB of one system in one workgroup, when a register shape
 // holds it (returns false otherwise; the caller then runs the per-step
 // solver).  x holds the initial guess.
-static const SmallShape kSmallBiShapes[] = {{64, 2, 8}, {256, 4, 8}, {512, 8, 5}};
+static const SmallShape kSmallBiShapes[] = {{64, 2, 8}, {256, 2, 8}, {512, 2, 8}, {512, 4, 5}, {512, 8, 5}};
 
 bool batch_single_bicgstab(BatchImpl &Bt, const mxl_criteria &c, const double *b, double *x, void *out3,
                            int64_t *iters, double *rel, int *stop, int *half, mxl_status *st) {
@@ -1582,26 +1598,21 @@ bool batch_single_bicgstab(BatchImpl &Bt, const mxl_criteria &c, const double *b
         }
         int maxlen = 0;
         for (int i = 0; i < n; ++i) maxlen = std::max(maxlen, rp[i + 1] - rp[i]);
-        Bt.small_bi_shape = NS;
-        for (int k = 0; k < NS; ++k)
-            if (n <= kSmallBiShapes[k].B * kSmallBiShapes[k].RPT && maxlen <= kSmallBiShapes[k].W &&
-                (size_t)n * 8 <= 60 * 1024) {
-                Bt.small_bi_shape = k;
-                break;
-            }
+        Bt.small_bi_shape = small_fit(kSmallBiShapes, NS, n, maxlen);
     }
     if (Bt.small_bi_shape >= NS) return false;
     const SmallShape &sh = kSmallBiShapes[Bt.small_bi_shape];
-    const size_t shm = (size_t)n * sizeof(double);
     hipStream_t s = Bt.ctx->stream;
 #define MXL_SMALL_BI(BB, RR, WW)                                                                     \
     if (sh.B == BB && sh.RPT == RR && sh.W == WW)                                                    \
-        hipLaunchKernelGGL((k_small_bicgstab<BB, RR, WW>), dim3(1), dim3(BB), shm, s, n,              \
+        hipLaunchKernelGGL((k_small_bicgstab<BB, RR, WW>), dim3(1), dim3(BB), 0, s, n,                \
                            (const int *)Bt.row_ptr->p, (const int *)Bt.col->p,                       \
                            (const double *)Bt.val->p, (const double *)Bt.dinv->p, b, x,              \
                            c.reduction, c.max_iters, c.nonfinite_check, out3);
     MXL_SMALL_BI(64, 2, 8)
-    MXL_SMALL_BI(256, 4, 8)
+    MXL_SMALL_BI(256, 2, 8)
+    MXL_SMALL_BI(512, 2, 8)
+    MXL_SMALL_BI(512, 4, 5)
     MXL_SMALL_BI(512, 8, 5)
 #undef MXL_SMALL_BI
     hipError_t e = hipGetLastError();
@@ -1624,6 +1635,7 @@ bool batch_single_bicgstab(BatchImpl &Bt, const mxl_criteria &c, const double *b
 mxl_status batch_single_solve(BatchImpl &Bt, const mxl_criteria &c, const double *b, double *x,
                               void *out3, int64_t *iters, double *rel, int *stop) {
     const int n = (int)Bt.rows;
+    constexpr int NS = (int)(sizeof(kSmallShapes) / sizeof(kSmallShapes[0]));
     if (Bt.small_shape < 0) {  // pick once: the maximum row length needs the row pointers
         std::vector<int32_t> rp(n + 1);
         if (hipMemcpyAsync(rp.data(), Bt.row_ptr->p, (n + 1) * 4, hipMemcpyDeviceToHost, Bt.ctx->stream) != hipSuccess ||
@@ -1631,15 +1643,9 @@ mxl_status batch_single_solve(BatchImpl &Bt, const mxl_criteria &c, const double
             return set_error(MXL_ERR_DEVICE, "row pointer read");
         int maxlen = 0;
         for (int i = 0; i < n; ++i) maxlen = std::max(maxlen, rp[i + 1] - rp[i]);
-        Bt.small_shape = (int)(sizeof(kSmallShapes) / sizeof(kSmallShapes[0]));
-        for (int k = 0; k < (int)(sizeof(kSmallShapes) / sizeof(kSmallShapes[0])); ++k)
-            if (n <= kSmallShapes[k].B * kSmallShapes[k].RPT && maxlen <= kSmallShapes[k].W &&
-                (size_t)n * 8 <= 60 * 1024) {
-                Bt.small_shape = k;
-                break;
-            }
+        Bt.small_shape = small_fit(kSmallShapes, NS, n, maxlen);
     }
-    if (Bt.small_shape < (int)(sizeof(kSmallShapes) / sizeof(kSmallShapes[0]))) {
+    if (Bt.small_shape < NS) {
         hipError_t e = launch_small(kSmallShapes[Bt.small_shape], n, Bt, c, b, x, out3);
         if (e != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string("small CG: ") + hipGetErrorString(e));
         char h[24];
