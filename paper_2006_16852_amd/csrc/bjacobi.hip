@@ -1,5 +1,5 @@
-// bjacobi.hip -- block-Jacobi preconditioner (Sec. 3.2): batched
-// Gauss-Jordan inversion of the diagonal blocks (one wave per block),
+// bjacobi.hip -- block-Jacobi preconditioner (Sec. 3.2): batched in-place
+// Gauss-Jordan inversion of the diagonal blocks (4 to 64 blocks a wave),
 // adaptive storage precision of each inverse (binary16/32/64 chosen from
 // the block's condition number and exponent range), the product z = M r,
 // and the CG steps that use it (the r update fused with z = M r and the
@@ -23,6 +23,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "device_common.hpp"
@@ -48,24 +49,6 @@ __device__ __forceinline__ double round_f16(double x) {
     return copysign(rint(a / quantum) * quantum, x);
 }
 
-// Lane l's value of v, as a wave-uniform scalar (l uniform).
-__device__ __forceinline__ double lane_value(double v, int l) {
-    const long long bits = __double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)bits, l);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(bits >> 32), l);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// One wave inverts one diagonal block (the 32-row shape, whose two
-// register columns per lane leave no room for a second block).  Lane j holds column j of D and of
-// its inverse I in registers (the block is staged through LDS once, row by
-// row, to turn rows into columns); the pivot column's entries reach every
-// lane as uniform scalars, so an elimination step is register arithmetic
-// with no barrier.  Every element sees the same operations in the same
-// order as a sequential Gauss-Jordan elimination with partial pivoting
-// (first row of largest magnitude), with no multiply-add contraction, so
-// the inverse, its condition number and the precision decision are
-// reproducible.
 // Rows of the block in slot `slot` of a launch: uniform blocks are slots
 // themselves (b = slot, rows b*BS ..); with variable sizes the slot indexes
 // a list of block ids of one size class and bptr gives the rows.
@@ -73,6 +56,7 @@ struct BlockSel {
     const int *list;      // variable sizes: block ids of this launch's class
     const int *bptr;      // variable sizes: block boundaries
     const int64_t *toff;  // variable sizes: offset of block b's m x m inverse in the output
+    int64_t every;        // uniform: slot s is block s * every
 };
 
 template <int BS, bool VAR>
@@ -83,302 +67,394 @@ __device__ __forceinline__ void block_rows(int64_t slot, int64_t n, const BlockS
         r0 = sel.bptr[b];
         m = sel.bptr[b + 1] - (int)r0;
     } else {
-        b = slot;
+        b = slot * sel.every;
         r0 = b * BS;
         m = (int)(n - r0 < BS ? n - r0 : BS);
     }
 }
 
-// Row i of block b's inverse (lane j holds column j): uniform blocks are
-// written BS x BS (zeros outside a short last block), variable ones m x m.
-template <int BS, bool VAR>
-__device__ __forceinline__ void store_inverse(double *__restrict__ inv, const BlockSel &sel, int64_t b, int m,
-                                              int j, const double (&I)[BS], int p) {
-#pragma unroll
-    for (int i = 0; i < BS; ++i) {
-        double x = I[i];
-        if (p == BJ_P32) x = (double)(float)x;
-        else if (p == BJ_P16) x = round_f16(x);
-        if constexpr (VAR) {
-            if (i < m && j < m) inv[sel.toff[b] + (int64_t)i * m + j] = x;
-        } else {
-            inv[(b * BS + i) * BS + j] = x;
-        }
-    }
+// Where the inverses of a launch go.  Variable sizes: inv, m x m at toff, FP64
+// rounded to the block's precision.  Uniform: inv, BS x BS at b, not rounded; or
+// packed into store, block b at b * stride, on the assumption that all blocks
+// take the precision `want`; or, with neither, nowhere (a look at the
+// precisions).  A block that takes another one sets *mixed, and workgroups that
+// start later leave at once.
+struct BlockOut {
+    double *inv;
+    unsigned char *store;
+    int64_t stride;
+    int want;
+    int *mixed;
+    int *redo;  // set if a step met an infinity or NaN: the result is to be had from the strict variant
+};
+
+// Bytes of a uniform block's inverse: padded to 16 (vector row loads).
+__host__ __device__ constexpr int64_t bj_stride(int bs, int prec) {
+    return ((int64_t)bs * bs * (prec == BJ_P16 ? 2 : prec == BJ_P32 ? 4 : 8) + 15) / 16 * 16;
 }
 
-template <int BS, bool VAR>
-__global__ __launch_bounds__(kWave) void k_bj_invert1(int64_t n, const int *__restrict__ rp,
-                                                     const int *__restrict__ col,
-                                                     const double *__restrict__ val, int adaptive,
-                                                     double accuracy, double *__restrict__ inv,
-                                                     double *__restrict__ cond, int *__restrict__ prec,
-                                                     int *__restrict__ bad, BlockSel sel) {
-#pragma clang fp contract(off)
-    __shared__ double L[BS][BS + 1];
-    int64_t b, r0;
-    int m;
-    block_rows<BS, VAR>(blockIdx.x, n, sel, b, r0, m);
-    const int j = threadIdx.x;
-    for (int e = j; e < BS * BS; e += kWave) L[e / BS][e % BS] = 0.0;
-    __syncthreads();
-    if (j < m)  // lane j loads row j of the block
-        for (int k = rp[r0 + j]; k < rp[r0 + j + 1]; ++k) {
-            const int64_t c = (int64_t)col[k] - r0;
-            if (c >= 0 && c < m) L[j][c] = val[k];
-        }
-    __syncthreads();
-    double D[BS], I[BS];
-#pragma unroll
-    for (int i = 0; i < BS; ++i) {
-        D[i] = j < BS ? L[i][j] : 0.0;
-        I[i] = (i == j && j < m) ? 1.0 : 0.0;
+// Lane l's value (l a constant) within every group of LPB lanes.
+template <int LPB, typename T>
+__device__ __forceinline__ T group_lane(T v, int l) {
+    static_assert(LPB == 1 || LPB == 2 || LPB == 4 || LPB == 8 || LPB == 16, "");
+    typedef typename std::conditional<sizeof(T) == 8, long long, int>::type U;
+    U u;
+    __builtin_memcpy(&u, &v, sizeof u);
+#define MXL_BC16(N) case N: u = __builtin_amdgcn_update_dpp((U)0, u, 0x150 + N, 0xf, 0xf, true); break;
+#define MXL_BC8(N)                                                                        \
+    case N: {                                                                             \
+        const U w = __builtin_amdgcn_update_dpp((U)0, u, 0x150 + N, 0xf, 0xf, true);      \
+        u = __builtin_amdgcn_update_dpp(w, u, 0x158 + N, 0xf, 0xc, false);                \
+        break;                                                                            \
     }
-    auto norm1 = [&](const double (&M)[BS]) {
-        double s = 0.0;
-        if (j < m) {
-#pragma unroll
-            for (int i = 0; i < BS; ++i)
-                if (i < m) s += fabs(M[i]);
+    if constexpr (LPB == 16) {
+        switch (l) {
+            MXL_BC16(0) MXL_BC16(1) MXL_BC16(2) MXL_BC16(3) MXL_BC16(4) MXL_BC16(5) MXL_BC16(6) MXL_BC16(7)
+            MXL_BC16(8) MXL_BC16(9) MXL_BC16(10) MXL_BC16(11) MXL_BC16(12) MXL_BC16(13) MXL_BC16(14) MXL_BC16(15)
         }
-        return wave_max(s);
-    };
-    const double nD = norm1(D);
-    bool singular = false;
-#pragma clang loop unroll(full)
-    for (int c = 0; c < BS; ++c) {
-        if (singular || c >= m) continue;
-        // pivot: the first row i >= c of largest |D[i][c]|, found by lane c
-        double best = -1.0;
-        int pv = c;
-#pragma clang loop unroll(full)
-        for (int i = c; i < BS; ++i)
-            if (i < m) {
-                const double a = fabs(D[i]);
-                if (a > best) {
-                    best = a;
-                    pv = i;
-                }
-            }
-        const double mx = lane_value(best, c);
-        const int piv = __builtin_amdgcn_readlane(pv, c);
-        if (!(mx > 0.0)) {  // singular block (zero column below the diagonal)
-            singular = true;
-            continue;
+    } else if constexpr (LPB == 8) {
+        switch (l) {
+            MXL_BC8(0) MXL_BC8(1) MXL_BC8(2) MXL_BC8(3) MXL_BC8(4) MXL_BC8(5) MXL_BC8(6) MXL_BC8(7)
         }
-        if (piv != c && j < m) {
-            const double dc = D[c], ic = I[c];
-#pragma clang loop unroll(full)
-            for (int i = c + 1; i < BS; ++i)
-                if (i == piv) {
-                    D[c] = D[i];
-                    I[c] = I[i];
-                    D[i] = dc;
-                    I[i] = ic;
-                }
-        }
-        const double d = lane_value(D[c], c);
-        if (j < m) {  // columns beyond a short last block stay zero
-            D[c] = D[c] / d;
-            I[c] = I[c] / d;
-        }
-#pragma clang loop unroll(full)
-        for (int r = 0; r < BS; ++r) {
-            if (r == c || r >= m) continue;
-            const double f = lane_value(D[r], c);
-            if (f == 0.0) continue;
-            if (j < m) {
-                const double pd = f * D[c];
-                const double pi = f * I[c];
-                D[r] = D[r] - pd;
-                I[r] = I[r] - pi;
-            }
-        }
+    } else if constexpr (LPB > 1) {
+        v = __shfl(v, (int)(threadIdx.x % kWave) / LPB * LPB + l, kWave);
+        return v;
     }
-    if (singular) {
-        if (j == 0) atomicMin(bad, (int)(b < INT_MAX ? b : INT_MAX));
-        return;
-    }
-    const double nI = norm1(I);
-    const double kappa = nD * nI;
-    int p = BJ_P64;
-    if (adaptive) {
-        double lo = __builtin_inf(), hi = 0.0;
-        if (j < m) {
-#pragma unroll
-            for (int i = 0; i < BS; ++i) {
-                if (i >= m) continue;
-                const double a = fabs(I[i]);
-                if (a == 0.0) continue;
-                lo = a < lo ? a : lo;
-                hi = a > hi ? a : hi;
-            }
-        }
-        lo = -wave_max(-lo);
-        hi = wave_max(hi);
-        if (hi == 0.0) lo = hi = 1.0;
-        if (kappa * ldexp(1.0, -11) <= accuracy && lo >= ldexp(1.0, -14) && hi <= 65504.0) p = BJ_P16;
-        else if (kappa * ldexp(1.0, -24) <= accuracy && lo >= ldexp(1.0, -126) && hi <= 3.4028234663852886e38)
-            p = BJ_P32;
-    }
-    if (j < BS) store_inverse<BS, VAR>(inv, sel, b, m, j, I, p);
-    if (j == 0) {
-        cond[b] = kappa;
-        prec[b] = p;
-    }
+#undef MXL_BC8
+#undef MXL_BC16
+    __builtin_memcpy(&v, &u, sizeof u);
+    return v;
 }
 
-// Maximum over the BS lanes of a lane group (BS a power of two dividing
-// the wave), with wave_max's comparison.
-template <int BS, typename T>
+template <int LPB, typename T>
 __device__ __forceinline__ T group_max(T v) {
 #pragma unroll
-    for (int off = BS / 2; off > 0; off >>= 1) {
+    for (int off = LPB / 2; off > 0; off >>= 1) {
         T o = __shfl_xor(v, off, kWave);
         v = o > v ? o : v;
     }
     return v;
 }
 
-// One wave inverts 64/BS diagonal blocks, one per group of BS lanes: lane
-// j of a group holds column j of its block D and of the inverse I in
-// registers (the blocks are staged through LDS once, row by row, to turn
-// rows into columns; the loops over pivots and rows are unrolled).  Lane c
-// of a group finds the pivot of column c and every entry of that column
-// reaches the group's lanes by a lane shuffle, so an elimination step is
-// register arithmetic with no barrier; a step that is zero in every block
-// of the wave is skipped as a whole.  Every element sees the same
-// operations in the same order as a sequential Gauss-Jordan elimination
-// with partial pivoting (first row of largest magnitude), with no
-// multiply-add contraction, so the inverse, its condition number and the
-// precision decision are reproducible.
-template <int BS, bool VAR>
-__global__ __launch_bounds__(kWave) void k_bj_invert(int64_t n, const int *__restrict__ rp,
+// binary16 of a double that is zero or within its normal range, nearest even.
+__device__ __forceinline__ _Float16 narrow_f16(double x) {
+    unsigned long long u = (unsigned long long)__double_as_longlong(x);
+    u += ((1ull << 41) - 1) + ((u >> 42) & 1);
+    u &= ~((1ull << 42) - 1);
+    return (_Float16)(float)(x == x ? __longlong_as_double((long long)u) : x);
+}
+
+// One wave inverts P diagonal blocks, one per group of LPB lanes, in place:
+// lane l of a group holds S columns of its block in registers (col = S*l + s;
+// the block is staged through LDS once, 16 rows at a time, to turn rows into
+// columns), and step c turns column c of the block into the column of the
+// inverse that belongs to row c's original row (rows are swapped by partial
+// pivoting).  Column c's entries reach the group by a lane broadcast inside the
+// vector unit, so a step is register arithmetic with no barrier; a row whose
+// entry is zero in every block of the wave is skipped.  Every element of the
+// inverse sees the same operations in the same order as a sequential
+// Gauss-Jordan elimination of (D | I) with partial pivoting (first row of
+// largest magnitude), with no multiply-add contraction, so the inverse, its
+// condition number and the precision decision are reproducible.
+//
+// Bound by vector instructions (busy 68% of the cycles at two waves a SIMD; D is
+// 128 registers): 2 of FP64 per element and step and a broadcast per row.
+// 128,000 blocks of 32: 4.4 ms with D and I side by side, one block a wave and
+// scalar broadcasts -> 1.05 ms.
+//
+// A zero entry times a finite row changes nothing, so the rows are updated
+// without looking at their entries: branches or selects cost more than the
+// arithmetic.  Where a row holds an infinity or a NaN the sequential
+// elimination skips zero entries all the same; STRICT does that, and the other
+// variant only reports the case.
+template <int BS, bool VAR, bool STRICT>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2))) void k_bj_invert(int64_t n, const int *__restrict__ rp,
                                                      const int *__restrict__ col,
                                                      const double *__restrict__ val, int adaptive,
-                                                     double accuracy, double *__restrict__ inv,
-                                                     double *__restrict__ cond, int *__restrict__ prec,
-                                                     int *__restrict__ bad, BlockSel sel, int64_t nslots) {
+                                                     double accuracy, double *__restrict__ cond,
+                                                     int *__restrict__ prec, int *__restrict__ bad, BlockSel sel,
+                                                     int64_t nslots, BlockOut out) {
 #pragma clang fp contract(off)
-    constexpr int P = kWave / BS;
-    __shared__ double L[P][BS][BS + 1];
-    const int lane = threadIdx.x, q = lane / BS, j = lane % BS;
-    const int src0 = q * BS;  // first lane of this lane's group
+    constexpr int LPB = BS < 16 ? BS : 16, S = BS / LPB, P = kWave / LPB;
+    __shared__ double L[P][LPB][BS + 1];
+    const int lane = threadIdx.x, q = lane / LPB, l = lane % LPB;
     const int64_t slot = (int64_t)blockIdx.x * P + q;
+    if (!VAR && !out.inv && __hip_atomic_load(out.mixed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
     const bool live = slot < nslots;
     int64_t b = 0, r0 = 0;
     int m = 0;
     if (live) block_rows<BS, VAR>(slot, n, sel, b, r0, m);
-    for (int e = lane; e < P * BS * BS; e += kWave) L[e / (BS * BS)][(e / BS) % BS][e % BS] = 0.0;
-    __syncthreads();
-    if (j < m)  // lane j loads row j of its block
-        for (int k = rp[r0 + j]; k < rp[r0 + j + 1]; ++k) {
-            const int64_t c = (int64_t)col[k] - r0;
-            if (c >= 0 && c < m) L[q][j][c] = val[k];
-        }
-    __syncthreads();
-    double D[BS], I[BS];
+    double D[S][BS];
+    int id[S];  // original row of row S*l + s; of column S*l + s once it is eliminated
 #pragma unroll
-    for (int i = 0; i < BS; ++i) {
-        D[i] = L[q][i][j];
-        I[i] = (i == j && j < m) ? 1.0 : 0.0;
+    for (int h = 0; h < S; ++h) {  // rows h*LPB ..: lane l loads row h*LPB + l
+#pragma unroll
+        for (int e = lane; e < P * LPB * BS; e += kWave) L[e / (LPB * BS)][(e / BS) % LPB][e % BS] = 0.0;
+        __syncthreads();
+        const int i = h * LPB + l;
+        if (i < m) {
+            const int k1 = rp[r0 + i + 1];
+            for (int k = rp[r0 + i]; k < k1; k += 4) {
+                int c[4];
+                double v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int ku = k + u < k1 ? k + u : k1 - 1;
+                    c[u] = col[ku];
+                    v[u] = val[ku];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int64_t cu = (int64_t)c[u] - r0;
+                    if (k + u < k1 && cu >= 0 && cu < m) L[q][l][cu] = v[u];
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i2 = 0; i2 < LPB; ++i2)
+#pragma unroll
+            for (int s = 0; s < S; ++s) D[s][h * LPB + i2] = L[q][i2][S * l + s];
+        __syncthreads();
     }
-    auto norm1 = [&](const double (&M)[BS]) {
-        double s = 0.0;
-        if (j < m) {
 #pragma unroll
-            for (int i = 0; i < BS; ++i)
-                if (i < m) s += fabs(M[i]);
+    for (int s = 0; s < S; ++s) id[s] = S * l + s;
+    // rows and columns past a short last block hold zeros, which change no sum,
+    // maximum or pivot
+    auto norm1 = [&]() {
+        double best = 0.0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            double t = 0.0;
+#pragma unroll
+            for (int i = 0; i < BS; ++i) t += fabs(D[s][i]);
+            best = t > best || t != t ? t : best;  // a NaN stays, as in a lane of its own
         }
-        return group_max<BS>(s);
+        return group_max<LPB>(best);
     };
-    const double nD = norm1(D);
-    bool singular = false;
+    const double nD = norm1();
+    bool singular = false, odd = false;
 #pragma clang loop unroll(full)
     for (int c = 0; c < BS; ++c) {
-        // pivot: the first row i >= c of largest |D[i][c]|, found by lane c of the group
-        double best = -1.0;
-        int pv = c;
+        const int cl = c / S, cs = c % S;  // the lane and slot of column c
+        const bool mine = l == cl;
+        // the diagonal is the pivot unless something below it is larger
+        // (a NaN never is)
+        double below = 0.0;
 #pragma clang loop unroll(full)
-        for (int i = c; i < BS; ++i)
-            if (i < m) {
-                const double a = fabs(D[i]);
-                if (a > best) {
-                    best = a;
-                    pv = i;
+        for (int i = c + 1; i < BS; ++i) below = __builtin_fmax(below, fabs(D[cs][i]));
+        const double dcc = fabs(D[cs][c]);
+        if (__builtin_expect(__any(mine && c < m && !singular && !(dcc > 0.0 && !(below > dcc))), 0)) {
+            // pivot: the first row i >= c of largest |D[i][c]|
+            const double best = __builtin_fmax(below, dcc);
+            int pv = c;
+#pragma clang loop unroll(full)
+            for (int i = BS - 1; i >= c; --i) pv = fabs(D[cs][i]) == best ? i : pv;
+            const double mx = group_lane<LPB>(best, cl);
+            const int piv = group_lane<LPB>(pv, cl);
+            if (!singular && c < m && !(mx > 0.0)) singular = true;  // zero column below the diagonal
+            if (!singular && c < m && piv != c) {
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const double dc = D[s][c];
+#pragma clang loop unroll(full)
+                    for (int i = c + 1; i < BS; ++i)
+                        if (i == piv) {
+                            asm volatile("");
+                            D[s][c] = D[s][i];
+                            D[s][i] = dc;
+                        }
                 }
             }
-        const double mx = __shfl(best, src0 + c, kWave);
-        const int piv = __shfl(pv, src0 + c, kWave);
-        bool act = !singular && c < m;
-        if (act && !(mx > 0.0)) {  // singular block (zero column below the diagonal)
-            singular = true;
-            act = false;
-        }
-        if (act && piv != c && j < m) {
-            const double dc = D[c], ic = I[c];
-#pragma clang loop unroll(full)
-            for (int i = c + 1; i < BS; ++i)
-                if (i == piv) {
-                    D[c] = D[i];
-                    I[c] = I[i];
-                    D[i] = dc;
-                    I[i] = ic;
-                }
-        }
-        const double d = __shfl(D[c], src0 + c, kWave);
-        if (act && j < m) {  // columns beyond a short last block stay zero
-            D[c] = D[c] / d;
-            I[c] = I[c] / d;
-        }
-#pragma clang loop unroll(full)
-        for (int r = 0; r < BS; ++r) {
-            if (r == c) continue;
-            const double f = __shfl(D[r], src0 + c, kWave);
-            const bool upd = act && r < m && f != 0.0;
-            if (!__any(upd)) continue;
-            if (upd && j < m) {
-                const double pd = f * D[c];
-                const double pi = f * I[c];
-                D[r] = D[r] - pd;
-                I[r] = I[r] - pi;
+            int idp = 0;  // rows c and piv trade names
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int t = __shfl(id[s], q * LPB + piv / S, kWave);
+                if (piv % S == s) idp = t;
+            }
+            const int idc = group_lane<LPB>(id[cs], cl);
+            if (!singular && c < m) {
+                if (mine) id[cs] = idp;
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+                    if (piv != c && S * l + s == piv) id[s] = idc;
             }
         }
+        const bool act = !singular && c < m;
+        const double d = group_lane<LPB>(D[cs][c], cl);
+        double row[S];  // row c of the result; column c starts from the identity
+#pragma unroll
+        for (int s = 0; s < S; ++s) row[s] = (s == cs && mine ? 1.0 : D[s][c]) / d;
+        if constexpr (!STRICT) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                odd = odd || (act && !__builtin_isfinite(row[s]));
+                row[s] = act ? row[s] : 0.0;
+            }
+        }
+        constexpr int G = BS < 8 ? BS : 8;  // broadcasts ahead of their use
+#pragma clang loop unroll(full)
+        for (int g = 0; g < BS; g += G) {
+            double f[G];
+#pragma clang loop unroll(full)
+            for (int r = g; r < g + G; ++r) f[r - g] = group_lane<LPB>(D[cs][r], cl);
+            if (act && mine) {
+                asm volatile("");  // stays a branch: selects would cost as much as the update
+#pragma clang loop unroll(full)
+                for (int r = g; r < g + G; ++r)
+                    if (r != c) D[cs][r] = 0.0;
+            }
+#pragma clang loop unroll(full)
+            for (int r = g; r < g + G; ++r) {
+                if (r == c || (STRICT && (!act || f[r - g] == 0.0))) continue;
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    const double pd = f[r - g] * row[s];
+                    D[s][r] = D[s][r] - pd;
+                }
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < S; ++s) D[s][c] = act ? row[s] : D[s][c];
     }
-    if (singular && j == 0) atomicMin(bad, (int)(b < INT_MAX ? b : INT_MAX));
-    const double nI = norm1(I);
+    if (!STRICT && __any(odd)) {
+        if (lane == 0) *out.redo = 1;
+        return;
+    }
+    if (singular && l == 0) atomicMin(bad, (int)(b < INT_MAX ? b : INT_MAX));
+    const double nI = norm1();
     const double kappa = nD * nI;
     int p = BJ_P64;
     if (adaptive) {
         double lo = __builtin_inf(), hi = 0.0;
-        if (j < m) {
+#pragma unroll
+        for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int i = 0; i < BS; ++i) {
-                if (i >= m) continue;
-                const double a = fabs(I[i]);
-                if (a == 0.0) continue;
-                lo = a < lo ? a : lo;
-                hi = a > hi ? a : hi;
+                const double a = fabs(D[s][i]);
+                lo = __builtin_fmin(lo, a == 0.0 ? lo : a);
+                hi = __builtin_fmax(hi, a);
             }
-        }
-        lo = -group_max<BS>(-lo);
-        hi = group_max<BS>(hi);
+        lo = -group_max<LPB>(-lo);
+        hi = group_max<LPB>(hi);
         if (hi == 0.0) lo = hi = 1.0;
         if (kappa * ldexp(1.0, -11) <= accuracy && lo >= ldexp(1.0, -14) && hi <= 65504.0) p = BJ_P16;
         else if (kappa * ldexp(1.0, -24) <= accuracy && lo >= ldexp(1.0, -126) && hi <= 3.4028234663852886e38)
             p = BJ_P32;
     }
-    if (live && !singular) {
-        store_inverse<BS, VAR>(inv, sel, b, m, j, I, p);
-        if (j == 0) {
-            cond[b] = kappa;
-            prec[b] = p;
+    p = group_lane<LPB>(p, 0);  // lanes differ if the block holds a NaN
+    if (!live || singular) return;
+    if (l == 0) {
+        cond[b] = kappa;
+        prec[b] = p;
+    }
+    if constexpr (VAR) {
+#pragma unroll
+        for (int i = 0; i < BS; ++i)
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                double x = D[s][i];
+                if (p == BJ_P32) x = (double)(float)x;
+                else if (p == BJ_P16) x = round_f16(x);
+                if (i < m && S * l + s < m) out.inv[sel.toff[b] + (int64_t)i * m + id[s]] = x;
+            }
+    } else {
+        if (!out.inv && p != out.want) {
+            if (l == 0) *out.mixed = 1;
+            return;
         }
+        if (!out.inv && !out.store) return;
+        const bool whole = m == BS;
+        bool in_place = S > 1;
+#pragma unroll
+        for (int s = 0; s < S; ++s) in_place = in_place && id[s] == S * l + s;
+        in_place = __all(in_place);
+        auto put = [&](auto *o, auto narrow) {
+            typedef decltype(narrow(0.0)) T;
+            typedef T TS __attribute__((ext_vector_type(S == 1 ? 2 : S)));
+#pragma unroll
+            for (int i = 0; i < BS; ++i) {
+                T t[S];
+#pragma unroll
+                for (int s = 0; s < S; ++s)  // zeros outside a short last block
+                    t[s] = narrow(whole || (i < m && S * l + s < m) ? D[s][i] : 0.0);
+                if constexpr (S > 1) {
+                    if (in_place) {
+                        TS w;
+#pragma unroll
+                        for (int s = 0; s < S; ++s) w[s] = t[s];
+                        *(TS *)(o + i * BS + S * l) = w;
+                        continue;
+                    }
+                }
+#pragma unroll
+                for (int s = 0; s < S; ++s) o[i * BS + id[s]] = t[s];
+            }
+        };
+        unsigned char *base = out.store + b * out.stride;
+        if (out.inv) put(out.inv + b * BS * BS, [](double x) { return x; });
+        else if (p == BJ_P16) put((_Float16 *)base, [](double x) { return narrow_f16(x); });
+        else put((double *)base, [](double x) { return x; });
     }
 }
 
-// Packs the rounded inverses into their storage precision (the values are
-// already representable, so the conversions are exact).
+// Offsets of blocks of mixed precisions: the exclusive sums of their sizes, and
+// the total.  Workgroup g owns blocks [g * chunk, (g + 1) * chunk): the first
+// kernel sums every chunk, the second adds the sums before its own and scans it
+// kScanWG blocks at a time.
+constexpr int kScanWG = 1024, kScanGrid = 256;
+
+__device__ __forceinline__ int64_t scan_wg(int64_t v, int64_t &all) {  // inclusive sum over the workgroup
+    __shared__ int64_t part[kScanWG / kWave];
+    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int64_t u = __shfl_up(v, o, kWave);
+        if (lane >= o) v += u;
+    }
+    if (lane == kWave - 1) part[wid] = v;
+    __syncthreads();
+    all = 0;
+    for (int w = 0; w < kScanWG / kWave; ++w) {
+        v += w < wid ? part[w] : 0;
+        all += part[w];
+    }
+    __syncthreads();
+    return v;
+}
+
+__global__ __launch_bounds__(kScanWG) void k_bj_sizes(int64_t nb, int64_t chunk, int bs, const int *__restrict__ prec,
+                                                      int64_t *__restrict__ sums) {
+    const int64_t b0 = blockIdx.x * chunk, b1 = b0 + chunk < nb ? b0 + chunk : nb;
+    int64_t v = 0, all;
+    for (int64_t b = b0 + threadIdx.x; b < b1; b += kScanWG) v += bj_stride(bs, prec[b]);
+    (void)scan_wg(v, all);
+    if (threadIdx.x == 0) sums[blockIdx.x] = all;
+}
+
+__global__ __launch_bounds__(kScanWG) void k_bj_scan(int64_t nb, int64_t chunk, int bs, const int *__restrict__ prec,
+                                                     const int64_t *__restrict__ sums, int64_t *__restrict__ off,
+                                                     int64_t *__restrict__ total) {
+    const int64_t b0 = blockIdx.x * chunk, b1 = b0 + chunk < nb ? b0 + chunk : nb;
+    int64_t base, all;
+    (void)scan_wg(threadIdx.x < blockIdx.x ? sums[threadIdx.x] : 0, base);
+    for (int64_t t = b0; t < b1; t += kScanWG) {
+        const int64_t b = t + threadIdx.x;
+        const int64_t sz = b < b1 ? bj_stride(bs, prec[b]) : 0;
+        const int64_t v = scan_wg(sz, all);
+        if (b < b1) off[b] = base + v - sz;
+        base += all;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = base;
+}
+
+// Offsets of blocks of one size.
+__global__ void k_bj_offsets(int64_t nb, int64_t stride, int64_t *__restrict__ off) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b < nb) off[b] = b * stride;
+}
+
+// Rounds inverses of mixed precisions into their storage (what takes binary16
+// lies in its normal range).
 template <int BS>
 __global__ void k_bj_pack(int64_t nb, const double *__restrict__ inv, const int *__restrict__ prec,
                           const int64_t *__restrict__ off, unsigned char *__restrict__ store) {
@@ -388,7 +464,7 @@ __global__ void k_bj_pack(int64_t nb, const double *__restrict__ inv, const int 
     unsigned char *base = store + off[b];
     const double x = inv[e];
     switch (prec[b]) {
-    case BJ_P16: ((_Float16 *)base)[k] = (_Float16)x; break;
+    case BJ_P16: ((_Float16 *)base)[k] = narrow_f16(x); break;
     case BJ_P32: ((float *)base)[k] = (float)x; break;
     default: ((double *)base)[k] = x; break;
     }
@@ -886,26 +962,19 @@ hipError_t bj_apply(const mxl_ctx *ctx, const JacobiImpl &P, int64_t n, double a
     return hipGetLastError();
 }
 
-static hipError_t bj_invert(const MatrixImpl &A, int bs, int adaptive, double accuracy, double *inv,
-                            double *cond, int *prec, int *bad, hipStream_t s) {
-    const int64_t nb = (A.nrows + bs - 1) / bs;
-    const BlockSel none{nullptr, nullptr, nullptr};
-    if (bs == 32)
-        hipLaunchKernelGGL((k_bj_invert1<32, false>), dim3((unsigned)nb), dim3(kWave), 0, s, A.nrows,
-                           (const int *)A.row_ptr->p, (const int *)A.col->p, (const double *)A.val->p, adaptive,
-                           accuracy, inv, cond, prec, bad, none);
-    else {
-#define MXL_BJ_INV(BSV)                                                                                     \
-    case BSV:                                                                                               \
-        hipLaunchKernelGGL((k_bj_invert<BSV, false>), dim3((unsigned)((nb + kWave / BSV - 1) / (kWave / BSV))), \
-                           dim3(kWave), 0, s, A.nrows, (const int *)A.row_ptr->p, (const int *)A.col->p,     \
-                           (const double *)A.val->p, adaptive, accuracy, inv, cond, prec, bad, none, nb);   \
-        break;
-        switch (bs) {
-            MXL_BJ_INV(1) MXL_BJ_INV(2) MXL_BJ_INV(4) MXL_BJ_INV(8) MXL_BJ_INV(16)
-        default: return hipErrorInvalidValue;
-        }
-#undef MXL_BJ_INV
+static hipError_t bj_invert(const MatrixImpl &A, int bs, int adaptive, double accuracy, double *cond, int *prec,
+                            int *bad, const BlockOut &out, bool strict, int64_t nb, int64_t every, hipStream_t s) {
+    const BlockSel none{nullptr, nullptr, nullptr, every};
+    const int per = kWave / (bs < 16 ? bs : 16);  // blocks of a wave
+    const dim3 g((unsigned)((nb + per - 1) / per));
+    const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p;
+    const double *val = (const double *)A.val->p;
+    if (strict) {
+        MXL_BS_SWITCH(bs, hipLaunchKernelGGL((k_bj_invert<BS, false, true>), g, dim3(kWave), 0, s, A.nrows, rp, col, val,
+                                             adaptive, accuracy, cond, prec, bad, none, nb, out));
+    } else {
+        MXL_BS_SWITCH(bs, hipLaunchKernelGGL((k_bj_invert<BS, false, false>), g, dim3(kWave), 0, s, A.nrows, rp, col, val,
+                                             adaptive, accuracy, cond, prec, bad, none, nb, out));
     }
     return hipGetLastError();
 }
@@ -947,54 +1016,99 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     J->block = true;
     J->bs = bs;
     J->nblocks = nb;
-    hipError_t e = hipSuccess;
-    BufPtr tmp, bad;
-    auto mk = [&](size_t bytes) {
+    // One precision for all blocks is the common outcome (binary16 for blocks
+    // worth preconditioning with, binary64 without the adaptive choice): the
+    // inverses are packed where they will stay on that assumption.  The first
+    // block that takes another precision ends that pass; the inverses then go
+    // through a binary64 copy, as their places follow from all precisions.  Without
+    // the copy 128,000 blocks of 32 take 0.26 GB of new memory instead of 1.3 GB.
+    // A large storage is not allocated before some blocks have been looked at:
+    // that costs about 50 us, allocating and freeing it in vain 300.
+    Arena ar;
+    BufPtr flags;
+    ar.want(J->bcond, (size_t)nb * 8);
+    ar.want(J->boff, (size_t)nb * 8);
+    ar.want(J->bprec, (size_t)nb * 4);
+    // lowest singular block, whether precisions differ, whether to invert strictly; then the offsets' sums
+    ar.want(flags, (kScanGrid + 1) * 8);
+    auto mk = [&](int64_t bytes) {
         auto d = std::make_shared<DevBuf>();
-        if (hipMalloc(&d->p, bytes ? bytes : 16) != hipSuccess) return BufPtr();
-        d->bytes = bytes;
+        if (hipMalloc(&d->p, (size_t)bytes) != hipSuccess) return BufPtr();
+        d->bytes = (size_t)bytes;
         d->owned = true;
         return d;
     };
-    tmp = mk((size_t)nb * bs * bs * 8);
-    J->bcond = mk((size_t)nb * 8);
-    J->bprec = mk((size_t)nb * 4);
-    J->boff = mk((size_t)nb * 8);
-    bad = mk(4);
-    if (!tmp || !J->bcond || !J->bprec || !J->boff || !bad)
-        return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi workspace");
-    int none = INT_MAX;
-    if ((e = hipMemcpyAsync(bad->p, &none, 4, hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = bj_invert(*A, bs, adaptive ? 1 : 0, accuracy, (double *)tmp->p, (double *)J->bcond->p,
-                       (int *)J->bprec->p, (int *)bad->p, s)) != hipSuccess)
-        return set_error(MXL_ERR_DEVICE, std::string("block inversion: ") + hipGetErrorString(e));
-    int hb = INT_MAX;
-    std::vector<int> hp((size_t)nb);
-    if (hipMemcpyAsync(&hb, bad->p, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(hp.data(), J->bprec->p, (size_t)nb * 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return set_error(MXL_ERR_DEVICE, "block inversion read-back");
-    if (hb != INT_MAX) {
+    BlockOut out{};
+    out.want = adaptive ? BJ_P16 : BJ_P64;
+    out.stride = bj_stride(bs, out.want);
+    if (!ar.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi workspace");
+    int *fl = (int *)flags->p, *prec = (int *)J->bprec->p;
+    int64_t *off = (int64_t *)J->boff->p;
+    int hf[3];
+    out.mixed = fl + 1;
+    out.redo = fl + 2;
+    hipError_t e = hipSuccess;
+    auto pass = [&](bool strict, int64_t blocks, int64_t every) -> mxl_status {
+        hf[0] = INT_MAX;
+        hf[1] = hf[2] = 0;
+        if ((e = hipMemcpyAsync(fl, hf, 12, hipMemcpyHostToDevice, s)) != hipSuccess ||
+            (e = bj_invert(*A, bs, adaptive ? 1 : 0, accuracy, (double *)J->bcond->p, prec, fl, out, strict, blocks,
+                           every, s)) != hipSuccess)
+            return set_error(MXL_ERR_DEVICE, std::string("block inversion: ") + hipGetErrorString(e));
+        if (out.store) hipLaunchKernelGGL(k_bj_offsets, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, nb,
+                                          out.stride, off);
+        if ((e = hipGetLastError()) != hipSuccess ||
+            (e = hipMemcpyAsync(hf, fl, 12, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+            (e = hipStreamSynchronize(s)) != hipSuccess)
+            return set_error(MXL_ERR_DEVICE, std::string("block inversion read-back: ") + hipGetErrorString(e));
+        return MXL_OK;
+    };
+    constexpr int64_t kLook = 1024;
+    mxl_status st = MXL_OK;
+    BufPtr tmp;
+    bool mixed = false;
+    if (adaptive && nb > 4 * kLook && nb * out.stride >= (int64_t)16 << 20) {
+        if ((st = pass(false, kLook, nb / kLook)) != MXL_OK) return st;
+        mixed = hf[1] != 0;
+    }
+    for (bool strict = false;;) {
+        if (mixed && !tmp) {
+            J->bstore.reset();
+            out.store = nullptr;
+            if (!(tmp = mk(nb * bs * bs * 8))) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi workspace");
+            out.inv = (double *)tmp->p;
+        } else if (!mixed && !J->bstore) {
+            J->bstore_bytes = nb * out.stride;
+            if (!(J->bstore = mk(J->bstore_bytes))) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi storage");
+            out.store = (unsigned char *)J->bstore->p;
+        }
+        if ((st = pass(strict, nb, 1)) != MXL_OK) return st;
+        if (hf[2] && !strict) strict = true;
+        else if (hf[1] && !mixed) mixed = true;
+        else break;
+    }
+    if (hf[0] != INT_MAX) {
         char msg[96];
-        snprintf(msg, sizeof msg, "diagonal block %d is singular", hb);
+        snprintf(msg, sizeof msg, "diagonal block %d is singular", hf[0]);
         return set_error(MXL_ERR_ZERO_DIAG, msg);
     }
-    // byte offsets: each block padded to a multiple of 16 bytes (vector row loads)
-    std::vector<int64_t> ho((size_t)nb);
-    int64_t total = 0;
-    for (int64_t b = 0; b < nb; ++b) {
-        ho[b] = total;
-        const int64_t sz = (int64_t)bs * bs * (hp[b] == BJ_P16 ? 2 : hp[b] == BJ_P32 ? 4 : 8);
-        total += (sz + 15) / 16 * 16;
+    if (tmp) {
+        int64_t total = 0;
+        const int g = (int)std::min<int64_t>(kScanGrid, (nb + kScanWG - 1) / kScanWG);
+        const int64_t chunk = (nb + g - 1) / g;
+        int64_t *sums = (int64_t *)fl;  // the chunks' sums, then the total
+        hipLaunchKernelGGL(k_bj_sizes, dim3(g), dim3(kScanWG), 0, s, nb, chunk, bs, prec, sums);
+        hipLaunchKernelGGL(k_bj_scan, dim3(g), dim3(kScanWG), 0, s, nb, chunk, bs, prec, sums, off, sums + kScanGrid);
+        if ((e = hipGetLastError()) != hipSuccess ||
+            (e = hipMemcpyAsync(&total, sums + kScanGrid, 8, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+            (e = hipStreamSynchronize(s)) != hipSuccess)
+            return set_error(MXL_ERR_DEVICE, std::string("block Jacobi offsets: ") + hipGetErrorString(e));
+        if (!(J->bstore = mk(total))) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi storage");
+        J->bstore_bytes = total;
+        if ((e = bj_pack(bs, nb, (const double *)tmp->p, prec, off, (unsigned char *)J->bstore->p, s)) != hipSuccess ||
+            (e = hipStreamSynchronize(s)) != hipSuccess)
+            return set_error(MXL_ERR_DEVICE, std::string("block Jacobi packing: ") + hipGetErrorString(e));
     }
-    J->bstore = mk((size_t)total);
-    if (!J->bstore) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi storage");
-    J->bstore_bytes = total;
-    if ((e = hipMemcpyAsync(J->boff->p, ho.data(), (size_t)nb * 8, hipMemcpyHostToDevice, s)) != hipSuccess ||
-        (e = bj_pack(bs, nb, (const double *)tmp->p, (const int *)J->bprec->p, (const int64_t *)J->boff->p,
-                     (unsigned char *)J->bstore->p, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
-        return set_error(MXL_ERR_DEVICE, std::string("block Jacobi packing: ") + hipGetErrorString(e));
     auto *op = new mxl_op;
     op->kind = MXL_OP_JACOBI;
     op->jac = J;
@@ -1071,57 +1185,67 @@ mxl_status bj_generate_var(const std::shared_ptr<MatrixImpl> &A, std::vector<int
     J->bs = 0;
     J->nblocks = nb;
     BufPtr dlist = dev_buf(list.size() * 4), dtoff = dev_buf((size_t)(nb + 1) * 8),
-           tmp = dev_buf((size_t)toff[(size_t)nb] * 8), bad = dev_buf(4);
+           tmp = dev_buf((size_t)toff[(size_t)nb] * 8), flags = dev_buf(8);
     J->bptr_d = dev_buf((size_t)(nb + 1) * 4);
     J->rblk = dev_buf((size_t)A->nrows * 4);
     J->bcond = dev_buf((size_t)nb * 8);
     J->bprec = dev_buf((size_t)nb * 4);
     J->boff = dev_buf((size_t)nb * 8);
-    if (!dlist || !dtoff || !tmp || !bad || !J->bptr_d || !J->rblk || !J->bcond || !J->bprec || !J->boff)
+    if (!dlist || !dtoff || !tmp || !flags || !J->bptr_d || !J->rblk || !J->bcond || !J->bprec || !J->boff)
         return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi workspace");
     hipError_t e;
-    const int none = INT_MAX;
     if ((e = hipMemcpyAsync(dlist->p, list.data(), list.size() * 4, hipMemcpyHostToDevice, s)) != hipSuccess ||
         (e = hipMemcpyAsync(dtoff->p, toff.data(), (size_t)(nb + 1) * 8, hipMemcpyHostToDevice, s)) != hipSuccess ||
         (e = hipMemcpyAsync(J->bptr_d->p, bp.data(), (size_t)(nb + 1) * 4, hipMemcpyHostToDevice, s)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(bad->p, &none, 4, hipMemcpyHostToDevice, s)) != hipSuccess)
+            hipSuccess)
         return set_error(MXL_ERR_DEVICE, std::string("block Jacobi upload: ") + hipGetErrorString(e));
     const int *rp = (const int *)A->row_ptr->p, *col = (const int *)A->col->p;
     const double *val = (const double *)A->val->p;
-    double *inv = (double *)tmp->p, *cond = (double *)J->bcond->p;
-    int *prec = (int *)J->bprec->p, *badp = (int *)bad->p;
-    for (int c = 0; c < 6; ++c) {
-        const int64_t cnt = cstart[c + 1] - cstart[c];
-        if (cnt == 0) continue;
-        const BlockSel sel{(const int *)dlist->p + cstart[c], (const int *)J->bptr_d->p,
-                           (const int64_t *)dtoff->p};
-        switch (kClass[c]) {
-        case 32:
-            hipLaunchKernelGGL((k_bj_invert1<32, true>), dim3((unsigned)cnt), dim3(kWave), 0, s, A->nrows, rp, col,
-                               val, adaptive, accuracy, inv, cond, prec, badp, sel);
-            break;
-#define MXL_BJV(BSV)                                                                                         \
-    case BSV:                                                                                                \
-        hipLaunchKernelGGL((k_bj_invert<BSV, true>), dim3((unsigned)((cnt + kWave / BSV - 1) / (kWave / BSV))), \
-                           dim3(kWave), 0, s, A->nrows, rp, col, val, adaptive, accuracy, inv, cond, prec, badp,  \
-                           sel, cnt);                                                                        \
-        break;
-            MXL_BJV(1) MXL_BJV(2) MXL_BJV(4) MXL_BJV(8) MXL_BJV(16)
-#undef MXL_BJV
-        }
-        if ((e = hipGetLastError()) != hipSuccess)
-            return set_error(MXL_ERR_DEVICE, std::string("block inversion: ") + hipGetErrorString(e));
-    }
-    hipLaunchKernelGGL(k_bj_rowmap, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, nb,
-                       (const int *)J->bptr_d->p, (int *)J->rblk->p);
-    int hb = INT_MAX;
+    double *cond = (double *)J->bcond->p;
+    int *prec = (int *)J->bprec->p, *fl = (int *)flags->p;
+    BlockOut out{};
+    out.inv = (double *)tmp->p;
+    out.redo = fl + 1;
+    int hf[2];  // lowest singular block, whether to invert strictly
     std::vector<int> hp((size_t)nb);
-    if ((e = hipGetLastError()) != hipSuccess ||
-        hipMemcpyAsync(&hb, bad->p, 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipMemcpyAsync(hp.data(), J->bprec->p, (size_t)nb * 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return set_error(MXL_ERR_DEVICE, "block inversion read-back");
+    for (int strict = 0; strict < 2; ++strict) {
+        hf[0] = INT_MAX;
+        hf[1] = 0;
+        if ((e = hipMemcpyAsync(fl, hf, 8, hipMemcpyHostToDevice, s)) != hipSuccess)
+            return set_error(MXL_ERR_DEVICE, std::string("block Jacobi upload: ") + hipGetErrorString(e));
+        for (int c = 0; c < 6; ++c) {
+            const int64_t cnt = cstart[c + 1] - cstart[c];
+            if (cnt == 0) continue;
+            const BlockSel sel{(const int *)dlist->p + cstart[c], (const int *)J->bptr_d->p,
+                               (const int64_t *)dtoff->p, 1};
+            const int per = kWave / (kClass[c] < 16 ? kClass[c] : 16);  // blocks of a wave
+            const dim3 g((unsigned)((cnt + per - 1) / per));
+            auto run = [&]() -> hipError_t {
+                if (strict) {
+                    MXL_BS_SWITCH(kClass[c], hipLaunchKernelGGL((k_bj_invert<BS, true, true>), g, dim3(kWave), 0, s,
+                                                                A->nrows, rp, col, val, adaptive, accuracy, cond, prec,
+                                                                fl, sel, cnt, out));
+                } else {
+                    MXL_BS_SWITCH(kClass[c], hipLaunchKernelGGL((k_bj_invert<BS, true, false>), g, dim3(kWave), 0, s,
+                                                                A->nrows, rp, col, val, adaptive, accuracy, cond, prec,
+                                                                fl, sel, cnt, out));
+                }
+                return hipGetLastError();
+            };
+            if ((e = run()) != hipSuccess)
+                return set_error(MXL_ERR_DEVICE, std::string("block inversion: ") + hipGetErrorString(e));
+        }
+        if (!strict)
+            hipLaunchKernelGGL(k_bj_rowmap, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, nb,
+                               (const int *)J->bptr_d->p, (int *)J->rblk->p);
+        if ((e = hipGetLastError()) != hipSuccess ||
+            hipMemcpyAsync(hf, fl, 8, hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipMemcpyAsync(hp.data(), J->bprec->p, (size_t)nb * 4, hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess)
+            return set_error(MXL_ERR_DEVICE, "block inversion read-back");
+        if (!hf[1]) break;
+    }
+    const int hb = hf[0];
     if (hb != INT_MAX) {
         char msg[96];
         snprintf(msg, sizeof msg, "diagonal block %d is singular", hb);
