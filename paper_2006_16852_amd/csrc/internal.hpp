@@ -123,6 +123,7 @@ struct MatrixImpl {
     int format = MXL_FMT_CSR;
     int variant = MXL_CSR_VECTOR;
     int vw = 32;                       // CSR vector lanes per row
+    bool stream_short = false;         // CSR stream: blocks of several rows hold at most 320 entries
     int csr_rows = 0;                  // rows per wave of the staged CSR kernel; 0: vw lanes a row
     BufPtr row_ptr, col, val;          // canonical CSR (always present)
     BufPtr coo_row;                    // COO
@@ -298,7 +299,7 @@ int64_t coo_tiles(int64_t nnz);
 int64_t carry_bytes(int64_t ntiles);
 // Row blocks of the streaming CSR kernel from host row pointers: (first
 // row, first nonzero) of every block plus the terminator (n, nnz).
-void stream_blocks(const std::vector<int32_t> &rp, std::vector<int32_t> &out);
+bool stream_blocks(const std::vector<int32_t> &rp, std::vector<int32_t> &out);
 int ell_lds_cap();
 hipError_t merge_partition(const MatrixImpl &A, hipStream_t s);
 hipError_t spmv_launch(const MatrixImpl &A, const SpmvArgs &a, hipStream_t s);

@@ -408,7 +408,7 @@ mxl_status mxl_convert(const mxl_op *Aop, mxl_format fmt, const mxl_format_param
         } else if (prm.variant == MXL_CSR_STREAM) {
             std::vector<int32_t> rp, bk;
             if ((st = to_host(ctx, S.row_ptr, rp, (size_t)S.nrows + 1)) != MXL_OK) return st;
-            stream_blocks(rp, bk);
+            A->stream_short = stream_blocks(rp, bk);
             A->ntiles = (int64_t)bk.size() / 2 - 1;
             A->part = alloc(bk.size() * 4, &e);
             if (!A->part) return hip_fail(e, "alloc row blocks");

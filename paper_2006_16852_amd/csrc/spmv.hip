@@ -145,13 +145,14 @@ __global__ __launch_bounds__(kWG) void k_csr_vector(int64_t n, const int *__rest
     }
 }
 
-constexpr int kStreamK = 8;  // entries per lane in flight of the swept rows
+constexpr int kStreamK = 8;      // entries per lane in flight
+constexpr int kStreamShort = 5;  // the same where runs or blocks hold few entries (64 rows of a 5-point stencil)
 
 // -------------------------------------------------------- staged CSR rows
 // The operator as wrapped: nothing is known of its rows beyond their mean
 // length and nothing is prepared.  A wave takes `rw` consecutive rows and cuts
-// them, by their row pointers, into runs of at most kRowsCap entries, whose
-// columns and values it loads as kRowsK independent coalesced loads a lane.
+// them, by their row pointers, into runs of at most 64 K entries, whose
+// columns and values it loads as K independent coalesced loads a lane.
 //
 //  * A run of m rows of similar length is parked in LDS as it is and walked by
 //    rows, g = 64 / m lanes to a row: one gather then covers the same position
@@ -160,16 +161,16 @@ constexpr int kStreamK = 8;  // entries per lane in flight of the swept rows
 //  * In a run of unequal rows every lane gathers for the entries it loaded and
 //    the products are parked; g lanes sum each row.  A long row then costs
 //    LDS reads, where the walk would gather with a few lanes active.
-//  * A row longer than kRowsCap is swept by the whole wave.
+//  * A row longer than 64 K is swept by the whole wave.
 //
 // Loads past the end of a run or row repeat its last entry and are left out of
 // the sum: a load under a lane mask makes the compiler wait for it before the
 // next.
 //
 // Bound by the matrix stream and, per run, its chain row pointers - entries -
-// gathers - sum, which only other waves hide: 24 a CU with kRowsK = 8 (6 KB of
-// LDS a wave in FP64).  kRowsK = 12 and 16 hold fewer and take 91 and 110 us on
-// the 7-point matrix, g rounded to a power of two 174 us on the 27-point one.
+// gathers - sum, which only other waves hide: 24 a CU with K = 8 (6 KB of LDS a
+// wave in FP64).  K = 12 and 16 hold fewer and take 91 and 110 us on the 7-point
+// matrix, g rounded to a power of two 174 us on the 27-point one.
 // W lanes a row (k_csr_vector) -> this, us:
 //   27-point 128^3         FP64 235 -> 157 (4.4 TB/s)   FP32 195 -> 110
 //   7-point 160^3          FP64 112 -> 79               FP32  91 -> 58
@@ -180,14 +181,12 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int kRowsK = 8;                  // entries a lane loads at a time
-constexpr int kRowsCap = kRowsK * kWave;   // entries of a run
-
-template <typename V, bool DOT>
+template <typename V, bool DOT, int K>  // K: entries a lane loads at a time
 __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *__restrict__ rp,
                                                   const int *__restrict__ col, const V *__restrict__ val,
                                                   SpmvK<V> p) {
     if (p.stop && *p.stop) return;
+    constexpr int kRowsCap = K * kWave;  // entries of a run
     constexpr int WPG = kWG / kWave;
     __shared__ V s_val[WPG][kRowsCap];
     __shared__ int s_col[WPG][kRowsCap];
@@ -247,38 +246,40 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
             const int g = kWave / m;
             const int row = (ln * (65536 / g + 1)) >> 16, part = ln - row * g;  // ln / g, ln % g
             if (tot > 0) {
-                int c[kRowsK];
-                V v[kRowsK];
-#pragma unroll
-                for (int j = 0; j < kRowsK; ++j) {
-                    const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)(tot - 1));
-                    c[j] = ld_stream(col + k0 + k);
-                    v[j] = ld_stream(val + k0 + k);
-                }
                 const int src = row < m ? i + row : i;
                 const int q0 = __shfl(rs, src, kWave) - k0, qe = __shfl(re, src, kWave) - k0;  // by all lanes
                 const int q1 = row < m ? qe : q0;
                 // unequal rows: one has more than 3/2 of the run's mean length
                 const bool uneven = __any((q1 - q0) * m > tot + tot / 2 + 8);
+                int c[K];
+                V v[K];
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)(tot - 1));
+                    c[j] = ld_stream(col + k0 + k);
+                    v[j] = ld_stream(val + k0 + k);
+                }
                 if (uneven) {
 #pragma unroll
-                    for (int j = 0; j < kRowsK; ++j) sv[ln + kWave * j] = v[j] * p.x[(uint32_t)c[j]];
-                    wave_lds_fence();
-                    for (int q = q0 + part; q < q1; q += g) acc += sv[q];
+                    for (int j = 0; j < K; ++j) sv[ln + kWave * j] = v[j] * p.x[(uint32_t)c[j]];
                 } else {
 #pragma unroll
-                    for (int j = 0; j < kRowsK; ++j) {
+                    for (int j = 0; j < K; ++j) {
                         sc[ln + kWave * j] = c[j];
                         sv[ln + kWave * j] = v[j];
                     }
-                    wave_lds_fence();
+                }
+                wave_lds_fence();
+                if (uneven) {
+                    for (int q = q0 + part; q < q1; q += g) acc += sv[q];
+                } else {
                     constexpr int U = 9;  // gathers a lane has in flight
                     for (int q = q0 + part; __any(q < q1); q += U * g) {
                         int cc[U];
                         V vv[U], xv[U];
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
-                            const int e = q + u * g, ec = e < q1 ? e : kRowsCap - 1;
+                            const int e = q + u * g, ec = e < q1 ? e : 0;
                             cc[u] = sc[ec];
                             vv[u] = sv[ec];
                         }
@@ -318,16 +319,18 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
 // loads, gather x, and park the products in the wave's LDS slice; then lane
 // l sums the products of row first+l in order.  A long row is swept by the
 // whole wave and reduced by shuffles.  No workgroup barrier is involved:
-// every wave walks its own blocks.
+// every wave walks its own blocks.  Loads past a block's end repeat its last
+// entry, as in k_csr_rows, and are not summed (power law, n = 450,001: 90 -> 67
+// us FP64, 74 -> 48 FP32; 27-point 128^3 FP64 177 -> 156).
 constexpr int kStreamRows = 63;  // a lane reads the next row's start from its neighbour
 
-template <typename V, bool DOT>
+template <typename V, bool DOT, int K>  // K: no block but of one long row holds more than 64 K entries
 __global__ __launch_bounds__(kWG) void k_csr_stream(int64_t nblk, const int2 *__restrict__ blk,
                                                     const int *__restrict__ rp,
                                                     const int *__restrict__ col,
                                                     const V *__restrict__ val, SpmvK<V> p) {
     if (p.stop && *p.stop) return;
-    __shared__ V s_prod[kWG / kWave][kStreamK * kWave];
+    __shared__ V s_prod[kWG / kWave][K * kWave];
     const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
     constexpr int WPG = kWG / kWave;
     // walkers: 4 waves per workgroup; when the grid is a multiple of 8 the
@@ -355,22 +358,25 @@ __global__ __launch_bounds__(kWG) void k_csr_stream(int64_t nblk, const int2 *__
             e1 = blk[bn + 1];
         }
         const int r0 = d0.x, k0 = d0.y, nr = d1.x - d0.x, k1 = d1.y;
-        if (k1 - k0 > kStreamK * kWave) {  // one long row, kStreamK loads per lane in flight
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // offsets formed again for every block, not kept in registers
+        if (k1 - k0 > K * kWave) {  // one long row, kStreamK loads per lane in flight
             V acc = 0;
-            for (int kb = k0; kb < k1; kb += kStreamK * kWave) {
+            for (uint32_t kb = (uint32_t)k0; kb < (uint32_t)k1; kb += kStreamK * kWave) {
                 int c[kStreamK];
                 V v[kStreamK];
 #pragma unroll
                 for (int j = 0; j < kStreamK; ++j) {
-                    const int k = kb + lane + kWave * j;
-                    const bool in = k < k1;
-                    c[j] = in ? ld_stream(col + k) : -1;
-                    v[j] = in ? ld_stream(val + k) : (V)0;
+                    const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)k1 - 1 - kb);
+                    c[j] = ld_stream(col + kb + k);
+                    v[j] = ld_stream(val + kb + k);
                 }
                 // same order as one entry at a time: k = lane, lane + 64, ...
 #pragma unroll
-                for (int j = 0; j < kStreamK; ++j)
-                    if (c[j] >= 0) acc += v[j] * p.x[c[j]];
+                for (int j = 0; j < kStreamK; ++j) {
+                    const V q = v[j] * p.x[(uint32_t)c[j]];
+                    acc += kb + ln + kWave * j < (uint32_t)k1 ? q : (V)0;
+                }
             }
 #pragma unroll
             for (int off = kWave / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, kWave);
@@ -381,17 +387,18 @@ __global__ __launch_bounds__(kWG) void k_csr_stream(int64_t nblk, const int2 *__
             }
         } else {
             const int rs = lane <= nr ? rp[r0 + lane] : 0;
-            int c[kStreamK];
-            V v[kStreamK];
+            if (k1 > k0) {
+                int c[K];
+                V v[K];
 #pragma unroll
-            for (int j = 0; j < kStreamK; ++j) {
-                const int k = k0 + lane + kWave * j;
-                const bool in = k < k1;
-                c[j] = in ? ld_stream(col + k) : -1;
-                v[j] = in ? ld_stream(val + k) : (V)0;
+                for (int j = 0; j < K; ++j) {
+                    const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)(k1 - k0 - 1));
+                    c[j] = ld_stream(col + k0 + k);
+                    v[j] = ld_stream(val + k0 + k);
+                }
+#pragma unroll
+                for (int j = 0; j < K; ++j) sp[ln + kWave * j] = v[j] * p.x[(uint32_t)c[j]];
             }
-#pragma unroll
-            for (int j = 0; j < kStreamK; ++j) sp[lane + kWave * j] = c[j] >= 0 ? v[j] * p.x[c[j]] : (V)0;
             // each row of the block gets g = 2^lg lanes (as many as 64 / nr
             // allows, at most 8): lane l sums every g-th product of row l >> lg
             // from offset l & (g - 1), and the g partial sums meet by shuffles
@@ -594,23 +601,26 @@ __global__ __launch_bounds__(kWG) void k_coo_wave(int64_t n, int64_t nnz, const 
         const int64_t e0 = tile * kCooWaveItems;
         const int ne = (int)((nnz - e0) < kCooWaveItems ? (nnz - e0) : kCooWaveItems);
         int rr[kCooWaveIPL], cc[kCooWaveIPL];
-        V vv[kCooWaveIPL];
-#pragma unroll
-        for (int j = 0; j < kCooWaveIPL; ++j) {
-            const int i = lane + kWave * j;
-            const bool in = i < ne;
-            rr[j] = in ? ld_stream(row + e0 + i) : 0;
-            cc[j] = in ? ld_stream(col + e0 + i) : -1;
-            vv[j] = in ? ld_stream(val + e0 + i) : (V)0;
-        }
+        V vv[kCooWaveIPL], xv[kCooWaveIPL];
         const int next = (e0 + ne < nnz) ? row[e0 + ne] : nrow;  // row after the tile ("all end" at nnz)
+        // items past the tile's end repeat its last one and are not used: a load
+        // under a lane mask makes the compiler wait for it before the next (power
+        // law, n = 1,000,003: FP32 109 -> 89 us; 27-point 128^3 217 -> 190)
+        int ln = lane;
+        asm volatile("" : "+v"(ln));  // offsets formed again for every tile, not kept in registers
 #pragma unroll
         for (int j = 0; j < kCooWaveIPL; ++j) {
-            const int i = lane + kWave * j;
-            if (i < ne) {
-                sr[i] = rr[j];
-                sv[i] = vv[j] * p.x[cc[j]];
-            }
+            const uint32_t i = min((uint32_t)(ln + kWave * j), (uint32_t)(ne - 1));
+            cc[j] = ld_stream(col + e0 + i);
+            rr[j] = ld_stream(row + e0 + i);
+            vv[j] = ld_stream(val + e0 + i);
+        }
+#pragma unroll
+        for (int j = 0; j < kCooWaveIPL; ++j) xv[j] = p.x[(uint32_t)cc[j]];
+#pragma unroll
+        for (int j = 0; j < kCooWaveIPL; ++j) {
+            sr[ln + kWave * j] = rr[j];
+            sv[ln + kWave * j] = vv[j] * xv[j];
         }
         if (lane == 0) sr[ne] = next;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1265,7 +1275,7 @@ static int stencil_rpt(const MatrixImpl &A) { return A.nx % 2 == 0 ? 2 : 1; }
 int csr_rows_per_wave(int64_t n, int64_t nnz) {
     if (nnz <= 4 * n) return 0;
     int rw = kWave;
-    while (rw > 1 && n / rw < 4096 && (rw > 8 || (double)rw * (double)nnz > (double)kRowsCap * (double)n)) rw /= 2;
+    while (rw > 1 && n / rw < 4096 && (rw > 8 || (double)rw * (double)nnz > (double)(kStreamK * kWave) * (double)n)) rw /= 2;
     return rw;
 }
 
@@ -1308,7 +1318,7 @@ int spmv_slots(const MatrixImpl &A) {
     return (A.format == MXL_FMT_ELL ? A.grid_dot : A.grid_main) + A.grid_tail;
 }
 
-void stream_blocks(const std::vector<int32_t> &rp, std::vector<int32_t> &out) {
+bool stream_blocks(const std::vector<int32_t> &rp, std::vector<int32_t> &out) {
     const int64_t n = (int64_t)rp.size() - 1;
     out.clear();
     int64_t r = 0;
@@ -1322,6 +1332,10 @@ void stream_blocks(const std::vector<int32_t> &rp, std::vector<int32_t> &out) {
     }
     out.push_back((int32_t)n);
     out.push_back(n >= 0 ? rp[n] : 0);
+    // whether the blocks of several rows are small enough for kStreamShort
+    for (size_t b = 0; b + 3 < out.size(); b += 2)
+        if (out[b + 2] - out[b] > 1 && out[b + 3] - out[b + 1] > kStreamShort * kWave) return false;
+    return true;
 }
 
 int64_t merge_tiles(int64_t n, int64_t nnz) { return (n + nnz + kMergeItems - 1) / kMergeItems; }
@@ -1369,8 +1383,17 @@ static hipError_t spmv_typed(const MatrixImpl &A, const SpmvArgs &a, hipStream_t
         } else if (A.variant == MXL_CSR_VECTOR && A.csr_rows) {
             // without partials to bound the grid, a block of rows a wave: whoever is done takes the next
             const dim3 gr(dot ? A.grid_main : walker_grid((n + A.csr_rows - 1) / A.csr_rows, 1 << 20));
-            if (dot) hipLaunchKernelGGL((k_csr_rows<V, true>), gr, blk, 0, s, n, A.csr_rows, rp, col, val, p);
-            else hipLaunchKernelGGL((k_csr_rows<V, false>), gr, blk, 0, s, n, A.csr_rows, rp, col, val, p);
+#define MXL_ROWS(D, K) hipLaunchKernelGGL((k_csr_rows<V, D, K>), gr, blk, 0, s, n, A.csr_rows, rp, col, val, p)
+            // 64 rows of at most 5 entries fill runs of 320 (5-point 1024^2 against 512:
+            // FP64 19.8 -> 17.9 us, FP32 14.8 -> 13.1)
+            if (A.nnz <= kStreamShort * n) {
+                if (dot) MXL_ROWS(true, kStreamShort);
+                else MXL_ROWS(false, kStreamShort);
+            } else {
+                if (dot) MXL_ROWS(true, kStreamK);
+                else MXL_ROWS(false, kStreamK);
+            }
+#undef MXL_ROWS
         } else if (A.variant == MXL_CSR_VECTOR) {
 #define MXL_VEC_CASE(WW)                                                                                   \
     case WW:                                                                                               \
@@ -1384,8 +1407,16 @@ static hipError_t spmv_typed(const MatrixImpl &A, const SpmvArgs &a, hipStream_t
 #undef MXL_VEC_CASE
         } else if (A.variant == MXL_CSR_STREAM) {
             const int2 *bk = (const int2 *)A.part->p;
-            if (dot) hipLaunchKernelGGL((k_csr_stream<V, true>), dim3(A.grid_main), blk, 0, s, A.ntiles, bk, rp, col, val, p);
-            else hipLaunchKernelGGL((k_csr_stream<V, false>), dim3(A.grid_main), blk, 0, s, A.ntiles, bk, rp, col, val, p);
+#define MXL_STREAM(D, K) \
+    hipLaunchKernelGGL((k_csr_stream<V, D, K>), dim3(A.grid_main), blk, 0, s, A.ntiles, bk, rp, col, val, p)
+            if (A.stream_short) {  // 5-point 1024^2 without: FP64 21.3 against 18.2 us, FP32 15.0 against 13.6
+                if (dot) MXL_STREAM(true, kStreamShort);
+                else MXL_STREAM(false, kStreamShort);
+            } else {
+                if (dot) MXL_STREAM(true, kStreamK);
+                else MXL_STREAM(false, kStreamK);
+            }
+#undef MXL_STREAM
         } else {
             Carry *cr = (Carry *)A.carries->p;
             const int2 *part = (const int2 *)A.part->p;

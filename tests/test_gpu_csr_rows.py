@@ -1,7 +1,8 @@
-"""The CSR operator as wrapped (runs of rows staged in LDS) at the edges of its
-runs, against the FP64 oracle: rows of exactly, just under and just over the
-512 entries of a run, runs cut inside a block of rows, equal and unequal rows,
-empty rows, a last block that is not full.
+"""The CSR operator as wrapped (runs of rows staged in LDS), as row blocks and as
+COO at the edges of runs, blocks and tiles, against the FP64 oracle: rows of
+exactly, just under and just over the 320 or 512 entries of a run, runs cut
+inside a block of rows, equal and unequal rows, empty rows, a last block that
+is not full.
 
 Tolerance per row: 1e-12 (FP64), 1e-5 (FP32) of |alpha| sum |a||x| + |beta||y|.
 """
@@ -35,16 +36,22 @@ LENGTHS = {
     # 64 rows a wave (262,144 rows and more): several runs in a block of rows
     "runs_in_block_equal": [27] * (64 * 4096 + 5),
     "runs_in_block_unequal": list(np.random.default_rng(3).integers(0, 40, 64 * 4096 + 70)),
+    # at most 5 entries a row: runs of 320
+    "short_runs": [5] * (64 * 4096 + 3),
+    "short_runs_long": ([320, 321, 319, 513] + [3, 4, 5, 6] * 40 + [0] * 300) * 6,
     "runs_in_block_long": [20] * 130000 + [700, 513, 512] + [20] * 135000,
 }
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("op", ["wrapped", "row_blocks", "coo"])
 @pytest.mark.parametrize("name", LENGTHS)
-def test_csr_rows_edges(name, dtype):
+def test_csr_rows_edges(name, op, dtype):
     import paper_2006_16852_amd as mxl
     A = _rows(LENGTHS[name], 5003, 11)
-    op = matrix(mxl, mxl.Context(0), A, dtype)
+    A0 = matrix(mxl, mxl.Context(0), A, dtype)
+    op = {"wrapped": lambda: A0, "row_blocks": lambda: A0.convert("csr", variant=mxl.CSR_STREAM),
+          "coo": lambda: A0.convert("coo")}[op]()
     rng = np.random.default_rng(7)
     x, y0 = rng.uniform(-1, 1, A.ncols), rng.uniform(-1, 1, A.nrows)
     fp32 = dtype == torch.float32
