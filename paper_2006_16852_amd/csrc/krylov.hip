@@ -380,26 +380,29 @@ __global__ __launch_bounds__(kWG) void k_bi_pupdate(int64_t n, const V *__restri
 }
 
 // Consumes rhat.v (fused into the SpMV): alpha = rho_k / rhat.v; s = r - alpha v
-// and s_hat = D^{-1} s (not stored when shat is NULL).
+// and s_hat = D^{-1} s (not stored when shat is NULL).  512 threads, as the CG
+// updates: it gathers a partial per product tile (4,096 of them at 128^3: 21.0 ->
+// 18.4 us); its neighbours, which gather 2,048 or hold six operands, are faster
+// with 256 (x update 21 against 23.7 us).
 template <typename V>
-__global__ __launch_bounds__(kWG) void k_bi_supdate(int64_t n, const V *__restrict__ r,
+__global__ __launch_bounds__(kCgWG) void k_bi_supdate(int64_t n, const V *__restrict__ r,
                                                     const V *__restrict__ v, V *__restrict__ s,
                                                     V *__restrict__ shat,
                                                     const V *__restrict__ dinv, SolverState *st,
                                                     const double *__restrict__ rv_parts, int rv_slots,
                                                     double *__restrict__ parts, int k) {
     if (st->stop) return;
-    MXL_RANGE(n)
+    MXL_RANGE_B(n, kCgWG)
     V r_[kPf], v_[kPf], d_[kPf];
 #pragma unroll
     for (int u = 0; u < kPf; ++u) {
-        MXL_PF_INDEX(u, n)
+        MXL_PF_INDEX_B(u, n, kCgWG)
         r_[u] = in_u ? r[i_u] : (V)0;
         v_[u] = in_u ? v[i_u] : (V)0;
         d_[u] = in_u && dinv ? dinv[i_u] : (V)1;
     }
     double rv[1];
-    gather_all<1>(rv_parts, rv_slots, rv);
+    gather_all<1, kCgWG>(rv_parts, rv_slots, rv);
     const bool chk = st->nonfinite_check != 0;
     const bool nonfin = chk && !finite_d(rv[0]);
     if (nonfin || rv[0] == 0.0) {
@@ -420,13 +423,13 @@ __global__ __launch_bounds__(kWG) void k_bi_supdate(int64_t n, const V *__restri
     };
 #pragma unroll
     for (int u = 0; u < kPf; ++u) {
-        MXL_PF_INDEX(u, n)
+        MXL_PF_INDEX_B(u, n, kCgWG)
         if (in_u) step(i_u, r_[u], v_[u], d_[u]);
     }
     for (int64_t t_ = tb_ + (int64_t)kPf * ts_; t_ < te_; t_ += ts_)
-        if (const int64_t i = t_ * kWG + threadIdx.x; i < n) step(i, r[i], v[i], dinv ? dinv[i] : (V)1);
+        if (const int64_t i = t_ * kCgWG + threadIdx.x; i < n) step(i, r[i], v[i], dinv ? dinv[i] : (V)1);
     double a[1] = {ss};
-    publish<1>(a, parts, L);
+    publish<1, kCgWG>(a, parts, L);
 }
 
 // Consumes s.s: half-step criterion; otherwise t.s and t.t.
@@ -716,16 +719,17 @@ static unsigned gs(int64_t n) {
 }
 
 // Launch KERNEL<double> or KERNEL<float>; arguments of type `VP` are cast.
-#define MXL_LAUNCH_V(dtype, KERNEL, GRID, ...)                                                     \
+#define MXL_LAUNCH_VB(dtype, KERNEL, GRID, B, ...)                                                 \
     do {                                                                                           \
         if ((dtype) == MXL_F64) {                                                                  \
             using V = double;                                                                      \
-            hipLaunchKernelGGL(KERNEL<V>, dim3(GRID), dim3(kWG), 0, s, __VA_ARGS__);               \
+            hipLaunchKernelGGL(KERNEL<V>, dim3(GRID), dim3(B), 0, s, __VA_ARGS__);                 \
         } else {                                                                                   \
             using V = float;                                                                       \
-            hipLaunchKernelGGL(KERNEL<V>, dim3(GRID), dim3(kWG), 0, s, __VA_ARGS__);               \
+            hipLaunchKernelGGL(KERNEL<V>, dim3(GRID), dim3(B), 0, s, __VA_ARGS__);                 \
         }                                                                                          \
     } while (0)
+#define MXL_LAUNCH_V(dtype, KERNEL, GRID, ...) MXL_LAUNCH_VB(dtype, KERNEL, GRID, kWG, __VA_ARGS__)
 
 hipError_t launch_finalize(int nv, const double *parts, int slots, SolverState *st, int op, int k,
                            int max_iters, double *hist, hipStream_t s) {
@@ -845,7 +849,7 @@ hipError_t bi_pupdate(const mxl_ctx *ctx, int dtype, int64_t n, const void *r, v
 hipError_t bi_supdate(const mxl_ctx *ctx, int dtype, int64_t n, const void *r, const void *v,
                       void *sv, void *shat, const void *dinv, SolverState *st,
                       const double *rv_parts, int rv_slots, double *parts, int k, hipStream_t s) {
-    MXL_LAUNCH_V(dtype, k_bi_supdate, vec_grid(ctx, n), n, (const V *)r, (const V *)v, (V *)sv,
+    MXL_LAUNCH_VB(dtype, k_bi_supdate, cg_update_grid(ctx, n), kCgWG, n, (const V *)r, (const V *)v, (V *)sv,
                  (V *)shat, (const V *)dinv, st, rv_parts, rv_slots, parts, k);
     return hipGetLastError();
 }

@@ -1165,7 +1165,7 @@ mxl_status solve_bicgstab(const SolverImpl &S, const void *b, void *x, mxl_solve
     const int64_t n = A.nrows;
     auto *st = (SolverState *)S.state->p;
     double *pA = region(S, 0), *pB = region(S, 1), *pC = region(S, 2), *pD = region(S, 3);
-    const int gv = vec_grid(ctx, n), gs = spmv_slots(A);
+    const int gv = vec_grid(ctx, n), gu = cg_update_grid(ctx, n), gs = spmv_slots(A);
     double *hist = (double *)S.hist->p;
     const void *dinv = S.P && S.P->dinv ? S.P->dinv->p : nullptr;
     const mxl_criteria &c = S.crit;
@@ -1213,7 +1213,7 @@ mxl_status solve_bicgstab(const SolverImpl &S, const void *b, void *x, mxl_solve
         t.y = S.t->p;
         t.stop = &st->stop;
         HIP_TRY(spmv_launch(A, t, s));
-        HIP_TRY(bi_tdots(ctx, dt, n, S.t->p, S.s->p, st, pB, gv, pD, (int)k, hist, s));
+        HIP_TRY(bi_tdots(ctx, dt, n, S.t->p, S.s->p, st, pB, gu, pD, (int)k, hist, s));
         HIP_TRY(bi_xupdate(ctx, dt, n, x, S.r->p, phat, shat, S.s->p, S.t->p, S.rhat->p, st, pD, gv, pC,
                            (int)k, s));
         if (k % c.check_every == 0 || k == c.max_iters) {
