@@ -115,7 +115,10 @@ typedef struct {
                               Time criterion and no history; CG n <= 16384,
                               BiCGSTAB n <= 4096 with <= 5 entries per row
                               (<= 8 for n <= 1024), else per step); auto
-                              picks 2 for n <= 8192.  GMRES: 1 launches every
+                              picks 2 for n <= 8192, for CG only up to 35,000
+                              stored entries or where registers hold the
+                              system (n <= 4096 with <= 5 entries per row,
+                              2048 with 8, 1024 with 32).  GMRES: 1 launches every
                               kernel of every step; otherwise systems with
                               n <= 1024 and krylov_dim <= 128 (point Jacobi or
                               none, no Time criterion) run whole in one

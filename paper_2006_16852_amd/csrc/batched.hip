@@ -1632,20 +1632,34 @@ bool batch_single_bicgstab(BatchImpl &Bt, const mxl_criteria &c, const double *b
     return true;
 }
 
+static constexpr int kNumSmall = (int)(sizeof(kSmallShapes) / sizeof(kSmallShapes[0]));
+
+// Whether a register shape holds the system (decided once: the longest row
+// needs the row pointers).
+bool batch_single_fits(BatchImpl &Bt, mxl_status *st) {
+    *st = MXL_OK;
+    const int n = (int)Bt.rows;
+    if (Bt.small_shape < 0) {
+        std::vector<int32_t> rp(n + 1);
+        if (hipMemcpyAsync(rp.data(), Bt.row_ptr->p, (n + 1) * 4, hipMemcpyDeviceToHost, Bt.ctx->stream) != hipSuccess ||
+            hipStreamSynchronize(Bt.ctx->stream) != hipSuccess) {
+            *st = set_error(MXL_ERR_DEVICE, "row pointer read");
+            return false;
+        }
+        int maxlen = 0;
+        for (int i = 0; i < n; ++i) maxlen = std::max(maxlen, rp[i + 1] - rp[i]);
+        Bt.small_shape = small_fit(kSmallShapes, kNumSmall, n, maxlen);
+    }
+    return Bt.small_shape < kNumSmall;
+}
+
 mxl_status batch_single_solve(BatchImpl &Bt, const mxl_criteria &c, const double *b, double *x,
                               void *out3, int64_t *iters, double *rel, int *stop) {
     const int n = (int)Bt.rows;
-    constexpr int NS = (int)(sizeof(kSmallShapes) / sizeof(kSmallShapes[0]));
-    if (Bt.small_shape < 0) {  // pick once: the maximum row length needs the row pointers
-        std::vector<int32_t> rp(n + 1);
-        if (hipMemcpyAsync(rp.data(), Bt.row_ptr->p, (n + 1) * 4, hipMemcpyDeviceToHost, Bt.ctx->stream) != hipSuccess ||
-            hipStreamSynchronize(Bt.ctx->stream) != hipSuccess)
-            return set_error(MXL_ERR_DEVICE, "row pointer read");
-        int maxlen = 0;
-        for (int i = 0; i < n; ++i) maxlen = std::max(maxlen, rp[i + 1] - rp[i]);
-        Bt.small_shape = small_fit(kSmallShapes, NS, n, maxlen);
-    }
-    if (Bt.small_shape < NS) {
+    mxl_status fit;
+    const bool small = batch_single_fits(Bt, &fit);
+    if (fit != MXL_OK) return fit;
+    if (small) {
         hipError_t e = launch_small(kSmallShapes[Bt.small_shape], n, Bt, c, b, x, out3);
         if (e != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string("small CG: ") + hipGetErrorString(e));
         char h[24];

@@ -275,6 +275,7 @@ constexpr size_t kNoAllocScratchBytes = (size_t)96 << 20;
 // device's copy of that scratch.
 hipError_t noalloc_scratch_init(int device, void **out);
 std::shared_ptr<BatchImpl> batch_from_matrix(const MatrixImpl &A, const void *dinv);
+bool batch_single_fits(BatchImpl &Bt, mxl_status *st);
 mxl_status batch_single_solve(BatchImpl &Bt, const mxl_criteria &c, const double *b, double *x,
                               void *out3, int64_t *iters, double *rel, int *stop);
 // One-workgroup BiCGSTAB; false when no register shape holds the system.

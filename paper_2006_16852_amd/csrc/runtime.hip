@@ -1000,20 +1000,36 @@ bool single_launch_ok(const SolverImpl &S, const mxl_solve_info *info) {
     return c.launch_mode == 2 || S.A->nrows <= kSingleAutoN;
 }
 
-mxl_status solve_cg_single(SolverImpl &S, const void *b, void *x, mxl_solve_info *info) {
+// CG in one workgroup beyond the register shapes streams the matrix through one
+// CU every iteration, 0.8 to 0.9 us per 1,000 stored entries (5-point 65^2 16 us
+// an iteration, 76^2 22, 90^2 30, 27-point 12^3 36, 20^3 177), where the per-step
+// kernels, bound by their launches, take 20 to 26: the line.
+constexpr int64_t kSingleStreamNnz = 35000;
+
+// The whole CG in one workgroup for small systems (false: the caller runs the
+// per-step solver).
+bool solve_cg_single(SolverImpl &S, const void *b, void *x, mxl_solve_info *info, mxl_status *st) {
     auto t0 = std::chrono::steady_clock::now();
+    *st = MXL_OK;
     if (!S.single) {
         S.single = batch_from_matrix(*S.A, S.P ? S.P->dinv->p : nullptr);
         hipError_t e;
         S.single_out = alloc(64, &e);
-        if (!S.single || !S.single_out) return fail(MXL_ERR_OUT_OF_MEMORY, "single-launch workspace");
+        if (!S.single || !S.single_out) {
+            *st = fail(MXL_ERR_OUT_OF_MEMORY, "single-launch workspace");
+            return true;
+        }
+    }
+    if (S.crit.launch_mode == 0 && S.A->nnz > kSingleStreamNnz) {
+        const bool fits = batch_single_fits(*S.single, st);
+        if (*st != MXL_OK) return true;
+        if (!fits) return false;
     }
     int64_t iters = 0;
     double rel = 0.0;
     int stop = 0;
-    mxl_status st = batch_single_solve(*S.single, S.crit, (const double *)b, (double *)x, S.single_out->p,
-                                       &iters, &rel, &stop);
-    if (st != MXL_OK) return st;
+    *st = batch_single_solve(*S.single, S.crit, (const double *)b, (double *)x, S.single_out->p, &iters, &rel, &stop);
+    if (*st != MXL_OK) return true;
     if (info) {
         info->iterations = iters;
         info->spmv_count = 1 + iters;
@@ -1022,7 +1038,7 @@ mxl_status solve_cg_single(SolverImpl &S, const void *b, void *x, mxl_solve_info
         info->seconds = elapsed_s(t0);
         info->inner_iterations = 0;
     }
-    return MXL_OK;
+    return true;
 }
 
 // x_zero: x is known to be zero (the inner solve of iterative refinement),
@@ -1030,7 +1046,10 @@ mxl_status solve_cg_single(SolverImpl &S, const void *b, void *x, mxl_solve_info
 // state: a zero b or an initial residual below the criterion stops on the
 // device, and the trailing check sees it.
 mxl_status solve_cg(const SolverImpl &S, const void *b, void *x, mxl_solve_info *info, bool x_zero = false) {
-    if (single_launch_ok(S, info)) return solve_cg_single(const_cast<SolverImpl &>(S), b, x, info);
+    if (single_launch_ok(S, info)) {
+        mxl_status st;
+        if (solve_cg_single(const_cast<SolverImpl &>(S), b, x, info, &st)) return st;
+    }
     auto t0 = std::chrono::steady_clock::now();
     const MatrixImpl &A = *S.A;
     mxl_ctx *ctx = A.ctx;

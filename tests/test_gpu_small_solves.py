@@ -7,7 +7,6 @@ of condition below 10 keep rounding (1e-16 a step) under 1e-12 of max |x|.
 """
 import numpy as np
 import pytest
-import torch
 
 import oracle as O
 import workloads as W
@@ -77,3 +76,20 @@ def test_rows_without_a_diagonal(n, width):
     """Such rows keep another entry in the slot that the diagonal has elsewhere."""
     A = _matrix(n, width, 7, False, drop_diagonal=[0, 5, n // 2, n - 1])
     _compare("bicgstab", O.bicgstab, A, False, steps=2)
+
+
+@pytest.mark.parametrize("A", [W.stencil_3d27(12), W.stencil_2d5(70), W.stencil_2d5(90)], ids=lambda a: a.name)
+def test_auto_beyond_the_register_shapes(A):
+    """Up to 35,000 stored entries one workgroup, beyond one kernel per step."""
+    import paper_2006_16852_amd as mxl
+    ctx = mxl.Context(0)
+    M = matrix(mxl, ctx, A)
+    b = O.spmv(A, W.uniform_vec(A.nrows, 1))
+    ref = O.pcg(A, b, dinv=O.jacobi_dinv(A)[0], reduction=1e-10, max_iters=5000)
+    S = mxl.solver("cg", M, mxl.jacobi(M), max_iters=5000, reduction=1e-10)
+    for _ in range(2):  # the second solve of a solver takes the route decided by the first
+        x = dev(np.zeros(A.nrows))
+        info = S.solve(dev(b), x)
+        assert info["stop_reason"] == ref["stop_reason"]
+        assert abs(info["iterations"] - ref["iterations"]) <= max(2, int(0.02 * ref["iterations"]))
+        assert np.linalg.norm(b - O.spmv(A, x.cpu().numpy())) <= 1.01e-10 * np.linalg.norm(b)
