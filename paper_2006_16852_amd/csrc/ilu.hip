@@ -658,16 +658,19 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     P->sweeps = sweeps;
     P->trisolve = trisolve;
     P->trs_sweeps = trs_sweeps;
-    BufPtr row, old, bad, w2;
+    // Allocations are few and as small as they can be: one of 90 MB costs 50 us,
+    // its release 300.  Exact solves run along the rows' chains where they form
+    // some (planned on the device from the pattern, no host copy of the matrix: a new
+    // 101^3 system 33 -> 1.6 ms); the sweeps' second copy of the factors and their row
+    // indices then stand where the packed factors will.
+    BufPtr bad, w2, row, old;
     Arena tmp, keep;
-    tmp.want(row, (size_t)nnz * 4);
-    tmp.want(old, (size_t)nnz * 8);
+    ChainPlan chains;
     tmp.want(bad, 4);
     tmp.want(w2, 8);
-    keep.want(P->lu, (size_t)nnz * 8);
+    if (trisolve == 0) chain_plan_want(chains, n, tmp);
     keep.want(P->dpos, (size_t)n * 4);
     keep.want(P->y, (size_t)n * 8);
-    keep.want(P->t, (size_t)n * 8);
     keep.want(P->z, (size_t)n * 8);
     if (!tmp.alloc() || !keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
     const int *rp = (const int *)A->row_ptr->p, *col = (const int *)A->col->p;
@@ -678,7 +681,7 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
         return set_error(MXL_ERR_DEVICE, hipGetErrorString(e));
     hipLaunchKernelGGL(k_ilu_diag, dim3(blocks(n)), dim3(256), 0, s, n, rp, col, val, (int *)P->dpos->p,
                        (int *)bad->p);
-    if ((e = launch_csr_to_coo(*A, (int *)row->p, s)) != hipSuccess ||
+    if ((e = hipGetLastError()) != hipSuccess ||
         (e = hipMemcpyAsync(&hb, bad->p, 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return set_error(MXL_ERR_DEVICE, std::string("ILU set-up: ") + hipGetErrorString(e));
@@ -687,25 +690,43 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
         snprintf(msg, sizeof msg, "row %d has a missing or zero diagonal", hb);
         return set_error(MXL_ERR_ZERO_DIAG, msg);
     }
+    mxl_status lst;
+    bool chain = false;
+    if (trisolve == 0 && (lst = chain_plan(*P, chains, chain)) != MXL_OK) return lst;
+    const size_t old_bytes = ((size_t)nnz * 8 + 255) / 256 * 256, sweep_bytes = old_bytes + (size_t)nnz * 4;
+    keep.want(P->lu, (size_t)nnz * 8);
+    void *old_p, *row_p;
+    if (chain) {
+        BufPtr rest;  // keeps the sweeps' arrays inside the allocation
+        keep.want(P->tickets, 8);
+        const size_t have = chain_want(*P, chains, keep);
+        keep.want(rest, have < sweep_bytes ? sweep_bytes - have : 0);
+        if (!keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
+        old_p = P->lo.code->p;
+    } else {
+        tmp.want(old, sweep_bytes);
+        keep.want(P->t, (size_t)n * 8);
+        if (!tmp.alloc() || !keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
+        old_p = old->p;
+    }
+    row_p = (char *)old_p + old_bytes;
+    if ((e = launch_csr_to_coo(*A, (int *)row_p, s)) != hipSuccess)
+        return set_error(MXL_ERR_DEVICE, std::string("ILU set-up: ") + hipGetErrorString(e));
     // factors: initial guess, then the sweeps (ping-pong, the result in P->lu)
-    double *cur = (double *)(sweeps % 2 == 0 ? P->lu->p : old->p);
-    double *nxt = (double *)(sweeps % 2 == 0 ? old->p : P->lu->p);
-    hipLaunchKernelGGL(k_ilu_init, dim3(blocks(nnz)), dim3(256), 0, s, nnz, (const int *)row->p, col, val,
+    double *cur = (double *)(sweeps % 2 == 0 ? P->lu->p : old_p);
+    double *nxt = (double *)(sweeps % 2 == 0 ? old_p : P->lu->p);
+    hipLaunchKernelGGL(k_ilu_init, dim3(blocks(nnz)), dim3(256), 0, s, nnz, (const int *)row_p, col, val,
                        (const int *)P->dpos->p, cur);
     for (int k = 0; k < sweeps; ++k) {
-        hipLaunchKernelGGL(k_parilu_sweep, dim3(blocks(nnz)), dim3(256), 0, s, nnz, rp, (const int *)row->p, col,
+        hipLaunchKernelGGL(k_parilu_sweep, dim3(blocks(nnz)), dim3(256), 0, s, nnz, rp, (const int *)row_p, col,
                            val, (const int *)P->dpos->p, (const double *)cur, nxt);
         std::swap(cur, nxt);
     }
     if ((e = hipGetLastError()) != hipSuccess) return set_error(MXL_ERR_DEVICE, hipGetErrorString(e));
-    // exact solves run along the rows' chains where they form some (planned on
-    // the device, no host copy of the matrix: a new 101^3 system 33 -> 2.3 ms), else
-    // over the dependency levels (built on the host); Jacobi sweeps need only
-    // the split layout's slot counts, found on the device
-    mxl_status lst;
-    if (trisolve == 0 && (lst = ilu_build_chains(*P)) != MXL_OK) return lst;
-    if (trisolve == 0 && !P->chain && (lst = ilu_levels(*P)) != MXL_OK) return lst;
-    if (trisolve == 0 && !P->chain && (lst = ilu_pack_levels(*P)) != MXL_OK) return lst;
+    // other exact solves run over the dependency levels (built on the host)
+    if (chain && (lst = chain_pack(*P, chains)) != MXL_OK) return lst;
+    if (trisolve == 0 && !chain && (lst = ilu_levels(*P)) != MXL_OK) return lst;
+    if (trisolve == 0 && !chain && (lst = ilu_pack_levels(*P)) != MXL_OK) return lst;
     // Jacobi sweeps read the factors repacked slot-major when the padding
     // stays within 4x the factor storage
     if (trisolve == 1) {

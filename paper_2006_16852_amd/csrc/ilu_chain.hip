@@ -657,27 +657,36 @@ void trs_launch(const TrsView &M, const double *b, double *x, double *znext, dou
 
 }  // namespace
 
-mxl_status ilu_build_chains(IluImpl &P) {
+namespace {
+struct TrsBoth {
+    TrsInfo f[2];
+    TrsPlan p[2];
+};
+}  // namespace
+
+void chain_plan_want(ChainPlan &C, int64_t n, Arena &tmp) {
+    tmp.want(C.info, 2 * sizeof(TrsInfo));
+    tmp.want(C.sums, ((size_t)trs_grid(n, kTrsScan) + 1) * 4);
+    for (int k = 0; k < 2; ++k) {
+        tmp.want(C.rowchain[k], (size_t)n * 4);
+        tmp.want(C.cstart[k], (size_t)(n + 1) * 4);
+        tmp.want(C.cgroup[k], (size_t)n * 4);
+    }
+}
+
+mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok) {
     const int64_t n = P.A->nrows;
     hipStream_t s = P.A->ctx->stream;
-    BufPtr info, sums, rowchain[2], cstart[2], cgroup[2];
-    Arena tmp;
-    tmp.want(info, 2 * sizeof(TrsInfo));
-    tmp.want(sums, ((size_t)trs_grid(n, kTrsScan) + 1) * 4);
-    for (int k = 0; k < 2; ++k) {
-        tmp.want(rowchain[k], (size_t)n * 4);
-        tmp.want(cstart[k], (size_t)(n + 1) * 4);
-        tmp.want(cgroup[k], (size_t)n * 4);
-    }
-    if (!tmp.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve plan");
-    TrsInfo f[2];
-    hipLaunchKernelGGL(k_trs_info, dim3(1), dim3(64), 0, s, (TrsInfo *)info->p);
+    auto both = std::make_shared<TrsBoth>();
+    TrsInfo *f = both->f;
+    TrsPlan *p = both->p;
+    hipLaunchKernelGGL(k_trs_info, dim3(1), dim3(64), 0, s, (TrsInfo *)C.info->p);
     for (int k = 0; k < 2; ++k)
-        TRS_TRY(trs_gather(P, k == 0, (int *)sums->p, (int *)rowchain[k]->p, (int *)cstart[k]->p,
-                           (TrsInfo *)info->p + k), "triangular solve plan");
-    TRS_TRY(hipMemcpyAsync(f, info->p, sizeof f, hipMemcpyDeviceToHost, s), "triangular solve plan");
+        TRS_TRY(trs_gather(P, k == 0, (int *)C.sums->p, (int *)C.rowchain[k]->p, (int *)C.cstart[k]->p,
+                           (TrsInfo *)C.info->p + k), "triangular solve plan");
+    TRS_TRY(hipMemcpyAsync(f, C.info->p, sizeof both->f, hipMemcpyDeviceToHost, s), "triangular solve plan");
     TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
-    TrsPlan p[2];
+    ok = false;
     for (int k = 0; k < 2; ++k) {
         p[k] = trs_plan(n, f[k]);
         if (!p[k].ok) return MXL_OK;
@@ -686,28 +695,44 @@ mxl_status ilu_build_chains(IluImpl &P) {
             trs_count_groups(p[k], f[k].nch);
         }
     }
+    C.both = both;
+    ok = true;
+    return MXL_OK;
+}
+
+size_t chain_want(IluImpl &P, const ChainPlan &C, Arena &keep) {
+    const int64_t n = P.A->nrows;
+    const TrsBoth &B = *(const TrsBoth *)C.both.get();
     P.n_pad = (n + 63) / 64 * 64;
-    Arena keep;
+    size_t bytes = 0;
+    auto want = [&](BufPtr &b, size_t sz) {
+        keep.want(b, sz);
+        bytes += sz;
+    };
     for (int k = 0; k < 2; ++k) {
         TrsSide &T = k == 0 ? P.lo : P.up;
-        T.groups = p[k].groups;
-        T.C = p[k].C;
-        T.w = f[k].w;
-        T.cap = (int)std::min<int64_t>((int64_t)p[k].C * f[k].longest, p[k].places);
-        keep.want(T.cstart, (size_t)(f[k].nch + 1) * 4);
-        keep.want(T.cbase, (size_t)f[k].nch * 4);
-        keep.want(T.glist, (size_t)f[k].nch * 4);
-        keep.want(T.gptr, (size_t)(p[k].groups + 1) * 4);
-        keep.want(T.code, (size_t)T.w * P.n_pad * 4);
-        keep.want(T.val, (size_t)T.w * P.n_pad * 8);
-        keep.want(T.prev, (size_t)n * 8);
+        T.groups = B.p[k].groups;
+        T.C = B.p[k].C;
+        T.w = B.f[k].w;
+        T.cap = (int)std::min<int64_t>((int64_t)B.p[k].C * B.f[k].longest, B.p[k].places);
+        want(T.code, (size_t)T.w * P.n_pad * 4);
+        want(T.cstart, (size_t)(B.f[k].nch + 1) * 4);
+        want(T.cbase, (size_t)B.f[k].nch * 4);
+        want(T.glist, (size_t)B.f[k].nch * 4);
+        want(T.gptr, (size_t)(B.p[k].groups + 1) * 4);
+        want(T.val, (size_t)T.w * P.n_pad * 8);
+        want(T.prev, (size_t)n * 8);
     }
-    keep.want(P.udiag, (size_t)n * 8);
-    keep.want(P.tickets, 8);
-    if (!keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "triangular solve factors");
+    want(P.udiag, (size_t)n * 8);
+    return bytes;
+}
+
+mxl_status chain_pack(IluImpl &P, const ChainPlan &C) {
+    hipStream_t s = P.A->ctx->stream;
+    const TrsBoth &B = *(const TrsBoth *)C.both.get();
     for (int k = 0; k < 2; ++k)
-        TRS_TRY(trs_pack(P, k == 0, p[k], f[k].nch, k == 0 ? P.lo : P.up, (const int *)rowchain[k]->p,
-                         (const int *)cstart[k]->p, (int *)cgroup[k]->p), "triangular solve factors");
+        TRS_TRY(trs_pack(P, k == 0, B.p[k], B.f[k].nch, k == 0 ? P.lo : P.up, (const int *)C.rowchain[k]->p,
+                         (const int *)C.cstart[k]->p, (int *)C.cgroup[k]->p), "triangular solve factors");
     TRS_TRY((trs_allow_lds<kTrsNarrow, 2>()), "LDS attribute");
     TRS_TRY((trs_allow_lds<kTrsWide, 1>()), "LDS attribute");
     TRS_TRY(hipStreamSynchronize(s), "triangular solve factors");  // the plan's temporaries end here

@@ -401,7 +401,18 @@ hipError_t ilu_apply(const IluImpl &P, double alpha, const void *r, double beta,
 
 // ------------------------------------------------------- ilu_chain.hip
 // Packs both triangles for the chain solve and sets P.chain when they suit it.
-mxl_status ilu_build_chains(IluImpl &P);
+// The exact solves' chains: a plan from the pattern (temporaries in tmp; ok is
+// false if the rows form too few chains), the solves' buffers in keep (returns
+// their bytes, code of the lower triangle first), and the lists and factors in
+// them once the factors are final.
+struct ChainPlan {
+    BufPtr info, sums, rowchain[2], cstart[2], cgroup[2];
+    std::shared_ptr<void> both;
+};
+void chain_plan_want(ChainPlan &C, int64_t n, Arena &tmp);
+mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok);
+size_t chain_want(IluImpl &P, const ChainPlan &C, Arena &keep);
+mxl_status chain_pack(IluImpl &P, const ChainPlan &C);
 hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, double beta, double *out, hipStream_t s);
 
 // ------------------------------------------------------------- runtime.hip
