@@ -12,6 +12,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace mxl {
 
@@ -142,8 +143,9 @@ __device__ __forceinline__ void publish(double (&v)[NV], double *partials, int s
 // values are added in slot order, so the sum does not depend on U.  Slots past
 // the last repeat it and are not added: a load under a lane mask is waited for
 // before the next one, which made the last batch of 8,000 slots serial (1.2 us
-// of a 75 us iteration of the FP32 CG on 4.1 M rows).
-// U shrinks as NV grows to keep the batch at 8 doubles per thread: the update
+// of a 75 us iteration of the FP32 CG on 4.1 M rows).  What is left of a batch
+// goes in halves, so few slots do not load many times over (100^3 CG 15.1 ->
+// 14.9 ms).  U shrinks as NV grows to keep the batch at 8 doubles per thread: the update
 // kernels hold their prefetched operands in registers at the same time.
 template <int NV, int B = kWG>
 __device__ __forceinline__ void gather_all(const double *__restrict__ partials, int nslots,
@@ -155,21 +157,36 @@ __device__ __forceinline__ void gather_all(const double *__restrict__ partials, 
     auto add = [&](int j, double v) {
         tot[j] = (max_mask >> j & 1) ? (v > tot[j] ? v : tot[j]) : tot[j] + v;
     };
-    for (int s0 = threadIdx.x; s0 - (int)threadIdx.x < nslots; s0 += U * B) {
-        double buf[U][NV > 0 ? NV : 1];
+    auto batch = [&](auto rounds, int r0) {  // rounds r0 .. r0 + K - 1, the last perhaps in part
+        constexpr int K = decltype(rounds)::value;
+        double buf[K][NV > 0 ? NV : 1];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int s = s0 + u * B < nslots ? s0 + u * B : nslots - 1;
+        for (int u = 0; u < K; ++u) {
+            const int t = (r0 + u) * B + (int)threadIdx.x, s = t < nslots ? t : nslots - 1;
 #pragma unroll
             for (int j = 0; j < NV; ++j) buf[u][j] = partials[(int64_t)s * NV + j];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (s0 + u * B < nslots) {
+        for (int u = 0; u < K; ++u)
+            if ((r0 + u) * B + (int)threadIdx.x < nslots) {
 #pragma unroll
                 for (int j = 0; j < NV; ++j) add(j, buf[u][j]);
             }
-    }
+    };
+    const int rounds = (nslots + B - 1) / B;  // uniform, as all branches on it
+    int r = 0;
+    for (; r + U <= rounds; r += U) batch(std::integral_constant<int, U>{}, r);
+    if constexpr (U >= 8)
+        if (r + 4 <= rounds) {
+            batch(std::integral_constant<int, 4>{}, r);
+            r += 4;
+        }
+    if constexpr (U >= 4)
+        if (r + 2 <= rounds) {
+            batch(std::integral_constant<int, 2>{}, r);
+            r += 2;
+        }
+    if (r < rounds) batch(std::integral_constant<int, 1>{}, r);
     block_reduce<NV, B>(tot, max_mask);
     if (threadIdx.x == 0) {
 #pragma unroll
