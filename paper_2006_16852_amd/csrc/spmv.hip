@@ -174,7 +174,7 @@ constexpr int kStreamShort = 5;  // the same where runs or blocks hold few entri
 // W lanes a row (k_csr_vector) -> this, us:
 //   27-point 128^3         FP64 235 -> 157 (4.4 TB/s)   FP32 195 -> 110
 //   7-point 160^3          FP64 112 -> 79               FP32  91 -> 58
-//   power law, n = 450,001, 10.2 M entries, rows up to 7,100:  222 -> 80
+//   power law, n = 450,001, 10.2 M entries, rows up to 7,100:  222 -> 74
 __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1268,14 +1268,16 @@ static int stencil_rpt(const MatrixImpl &A) { return A.nx % 2 == 0 ? 2 : 1; }
 // a tenth of a run and leave nothing to stage (us, W lanes / staged, n = 10^6:
 // 1 entry a row FP64 8.1 / 14.0, 2: 12.3 / 17.0, 3: 20.1 / 18.0 and FP32 11.8 /
 // 12.3, 4: 23.4 / 19.2 and 13.2 / 14.7, 5 (a 5-point 1024^2): 27.5 / 19.7 and
-// 22.2 / 14.8), so the line is above 4 a row.  64 rows fill their runs with rows
-// of any length; fewer are taken while that leaves waves idle (27-point 50^3
-// FP64: 16.1 us with 64, 12.7 with 32, 12.0 with 16), but below 8 only rows that
-// fill the runs by themselves.
+// 22.2 / 14.8), so the line is above 4 a row.  A wave that takes one run has the
+// shortest chain: as many rows as a run holds at the mean length, whatever the
+// number of waves (7-point 40^3: 5.9 us with 64 rows, 9.4 with 8 and 6.4 with W
+// lanes; 27-point 30^3: 14.8 with 64, 6.0 with 16 and 7.2).  From 16,384 waves of 64
+// rows on, several runs a wave cost less than the waves they save (27-point 128^3
+// FP32: 110 us with 64, 129 with 16; power law, n = 450,001: 80 with 64, 74 with 16).
 int csr_rows_per_wave(int64_t n, int64_t nnz) {
     if (nnz <= 4 * n) return 0;
     int rw = kWave;
-    while (rw > 1 && n / rw < 4096 && (rw > 8 || (double)rw * (double)nnz > (double)(kStreamK * kWave) * (double)n)) rw /= 2;
+    while (rw > 1 && n / rw < 16384 && (double)rw * (double)nnz > (double)(kStreamK * kWave) * (double)n) rw /= 2;
     return rw;
 }
 

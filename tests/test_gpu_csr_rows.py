@@ -33,7 +33,9 @@ LENGTHS = {
     "one_long": [5] * 900 + [4000] + [5] * 900,
     "empty_ends": [0] * 70 + [300] * 30 + [0] * 70,
     "one_a_run": [400] * 130,
-    # 64 rows a wave (262,144 rows and more): several runs in a block of rows
+    # 64 rows a wave whatever their length (1,048,576 rows and more): several runs in a block of rows
+    "two_runs_a_block": [9] * (64 * 16384 + 5),
+    "two_runs_a_block_unequal": list(np.random.default_rng(4).integers(0, 20, 64 * 16384 + 70)),
     "runs_in_block_equal": [27] * (64 * 4096 + 5),
     "runs_in_block_unequal": list(np.random.default_rng(3).integers(0, 40, 64 * 4096 + 70)),
     # at most 5 entries a row: runs of 320
