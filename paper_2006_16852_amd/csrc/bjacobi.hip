@@ -1023,7 +1023,9 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     // through a binary64 copy, as their places follow from all precisions.  Without
     // the copy 128,000 blocks of 32 take 0.26 GB of new memory instead of 1.3 GB.
     // A large storage is not allocated before some blocks have been looked at:
-    // that costs about 50 us, allocating and freeing it in vain 300.
+    // that costs about 50 us, allocating and freeing it in vain 300.  Below 16 MB
+    // the copy is taken at once: a failed guess would triple the time (27,000
+    // blocks of 8 with mixed precisions: 752 us against 151).
     Arena ar;
     BufPtr flags;
     ar.want(J->bcond, (size_t)nb * 8);
@@ -1070,6 +1072,8 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     if (adaptive && nb > 4 * kLook && nb * out.stride >= (int64_t)16 << 20) {
         if ((st = pass(false, kLook, nb / kLook)) != MXL_OK) return st;
         mixed = hf[1] != 0;
+    } else if (adaptive) {
+        mixed = true;  // small: the copy costs less than a guess that fails
     }
     for (bool strict = false;;) {
         if (mixed && !tmp) {
