@@ -1024,8 +1024,9 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     // the copy 128,000 blocks of 32 take 0.26 GB of new memory instead of 1.3 GB.
     // A large storage is not allocated before some blocks have been looked at:
     // that costs about 50 us, allocating and freeing it in vain 300.  Below 16 MB
-    // the copy is taken at once: a failed guess would triple the time (27,000
-    // blocks of 8 with mixed precisions: 752 us against 151).
+    // the copy is taken at once; a failed guess costs more than the copy does
+    // (mixed precisions: 27,000 blocks of 8 took 752 us with it and take 151,
+    // 2,000 blocks of 32 took 778 and take 186).
     Arena ar;
     BufPtr flags;
     ar.want(J->bcond, (size_t)nb * 8);
