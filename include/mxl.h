@@ -322,7 +322,8 @@ mxl_status mxl_bjacobi_info(const mxl_op *P, int64_t *nblocks, double *cond,
  * y = r and z = y / u_ii.  P preconditions GMRES.  A FP64, square, stored
  * (not matrix-free); P keeps a reference to A.  Errors: INVALID_ARG
  * (sweeps or trs_sweeps < 0, trisolve not 0/1, empty A), NOT_IMPLEMENTED,
- * ZERO_DIAG (a missing or zero diagonal entry), OUT_OF_MEMORY, DEVICE. */
+ * ZERO_DIAG (a missing or zero diagonal entry), INVALID_MATRIX (trisolve 0:
+ * a column outside the matrix), OUT_OF_MEMORY, DEVICE. */
 mxl_status mxl_ilu_generate(const mxl_op *A, int32_t sweeps, int32_t trisolve,
                             int32_t trs_sweeps, mxl_op **P);
 

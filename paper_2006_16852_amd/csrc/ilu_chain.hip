@@ -293,7 +293,9 @@ struct TrsInfo {
     int longest; // rows of the longest chain
     int nch;     // chains
     int bad;     // 1: two-dimensional tiles would not be in solve order
+    int faults;  // kTrsUnsorted, kTrsOutside: what the column indices violate
 };
+constexpr int kTrsUnsorted = 1, kTrsOutside = 2;
 
 // The groups of a triangle: `groups` runs of C consecutive chains, or (W > 0)
 // tiles of kTrsTJ x TK chains of the chains laid out as (t % W, t / W), the
@@ -319,7 +321,10 @@ __host__ __device__ inline TrsPlan trs_plan(int64_t n, const TrsInfo &f) {
     // for records, and rows wider than a record do not fit it: such factors
     // (random patterns, node blocks) have few levels, which the level
     // launches serve.
-    p.ok = f.nch >= 1 && n / f.nch >= 8 && f.w <= kTrsWide;
+    // Rows out of order have no place here: an entry on the wrong side of the
+    // diagonal would be waited for in a circle, and one next to the diagonal's
+    // place would be taken for the chain neighbour.
+    p.ok = !f.faults && f.nch >= 1 && n / f.nch >= 8 && f.w <= kTrsWide;
     if (!p.ok) return p;
     p.wide = f.w > kTrsNarrow;
     const size_t rec = p.wide ? trs_lds_bytes<false, kTrsWide, kTrsLoaders, 1>(0)
@@ -357,7 +362,7 @@ __device__ __forceinline__ void trs_group(const TrsPlan &p, int nch, int g, F f)
 }
 
 __global__ void k_trs_info(TrsInfo *f) {
-    if (threadIdx.x < 2) f[threadIdx.x] = TrsInfo{0, INT_MAX, 0, 0, 0, 0};
+    if (threadIdx.x < 2) f[threadIdx.x] = TrsInfo{0, INT_MAX, 0, 0, 0, 0, 0};
 }
 
 // Row i opens a chain: in L when it has no entry i - 1, in U when row i - 1
@@ -460,18 +465,30 @@ __global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const i
                                                    TrsInfo *f) {
     __shared__ int part[4][kWG / kWave];
     int v[4] = {0, -INT_MAX, 0, 0};  // widest, -closest, farthest, longest
+    // Columns are checked before they index anything: only validated matrices
+    // are known to be canonical.
+    int faults = 0;
     const int64_t nch = *nchp;
     for (int64_t i = (int64_t)blockIdx.x * kWG + threadIdx.x; i < n; i += (int64_t)gridDim.x * kWG) {
-        int a = 0;
+        int a = 0, last = lower ? -1 : (int)i;
         const int me = rowchain[i];
-        trs_entries(lower, (int)i, rp, col, dpos, [&](int, int c) {
+        const int q0 = lower ? rp[i] : dpos[i] + 1, q1 = lower ? dpos[i] : rp[i + 1];
+        for (int q = q0; q < q1; ++q) {
+            const int c = col[q];
+            if (c < 0 || c >= n) {
+                faults |= kTrsOutside;
+                continue;
+            }
+            if (c <= last || (lower && c >= (int)i)) faults |= kTrsUnsorted;
+            last = c;
+            if (c == (lower ? (int)i - 1 : (int)i + 1)) continue;  // the chain neighbour
             ++a;
             const int o = abs(me - rowchain[c]);
             if (o > 1) {
                 v[1] = -o > v[1] ? -o : v[1];
                 v[2] = o > v[2] ? o : v[2];
             }
-        });
+        }
         v[0] = a > v[0] ? a : v[0];
         if (i < nch) {
             const int len = cstart[i + 1] - cstart[i];
@@ -493,6 +510,7 @@ __global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const i
         else if (threadIdx.x == 2) atomicMax(&f->hi, m);
         else atomicMax(&f->longest, m);
     }
+    if (faults) atomicOr(&f->faults, faults);
     if (blockIdx.x == 0 && threadIdx.x == 0) f->nch = (int)nch;
 }
 
@@ -687,6 +705,8 @@ mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok) {
     TRS_TRY(hipMemcpyAsync(f, C.info->p, sizeof both->f, hipMemcpyDeviceToHost, s), "triangular solve plan");
     TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
     ok = false;
+    if ((f[0].faults | f[1].faults) & kTrsOutside)
+        return set_error(MXL_ERR_INVALID_MATRIX, "a column index lies outside the matrix");
     for (int k = 0; k < 2; ++k) {
         p[k] = trs_plan(n, f[k]);
         if (!p[k].ok) return MXL_OK;
