@@ -328,7 +328,9 @@ mxl_status mxl_ilu_generate(const mxl_op *A, int32_t sweeps, int32_t trisolve,
                             int32_t trs_sweeps, mxl_op **P);
 
 /* HOST copies (each may be NULL): the factors in A's CSR order (nnz
- * doubles) and the number of dependency levels of L and of U (levels[2]). */
+ * doubles) and the number of dependency levels of L and of U (levels[2]).
+ * Errors: INTERNAL if an exact solve since the last report gave up waiting
+ * (its result holds NaN); GMRES solves report the same. */
 mxl_status mxl_ilu_info(const mxl_op *P, double *lu, int32_t *levels);
 
 /* Solver factory .generate(A) (Sec. 2.2.3, Sec. 3.1): Krylov solver bound to

@@ -698,7 +698,7 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     void *old_p, *row_p;
     if (chain) {
         BufPtr rest;  // keeps the sweeps' arrays inside the allocation
-        keep.want(P->tickets, 8);
+        keep.want(P->tickets, 12);
         const size_t have = chain_want(*P, chains, keep);
         keep.want(rest, have < sweep_bytes ? sweep_bytes - have : 0);
         if (!keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
@@ -784,7 +784,7 @@ extern "C" mxl_status mxl_ilu_info(const mxl_op *Pop, double *lu_host, int32_t *
             hipStreamSynchronize(s) != hipSuccess)
             return set_error(MXL_ERR_DEVICE, "copy ILU factors");
     }
-    return MXL_OK;
+    return P.chain ? ilu_chain_check(P) : MXL_OK;
 } catch (...) {
     return mxl::abi_exception(__func__);
 }

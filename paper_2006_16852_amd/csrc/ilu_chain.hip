@@ -39,8 +39,12 @@
 // (checked at generation for the tiled order), a ticket is held by a
 // workgroup that runs, and no lane waits inside a branch for another lane of
 // its wave (every pass tries once and goes on).  As a backstop a workgroup
-// that sees no progress for kTrsMaxSpin passes turns its unsolved rows into
-// NaN and ends.
+// whose worker solves no row for trs_wait_passes(n) passes gives up: it turns
+// its unsolved rows into NaN, sets the flag behind the tickets and ends.  The
+// worker alone counts (the loaders end with it), and its limit grows with n: a
+// group may have to wait until all rows before it are solved one after another.
+// The flag is an error of the next call that synchronises (mxl_ilu_info and
+// GMRES solves).
 #include <algorithm>
 #include <climits>
 #include <string>
@@ -54,7 +58,6 @@ namespace mxl {
 constexpr unsigned kTrsWaitHi = 0x7ff4a5a5u;  // a signalling NaN: no arithmetic yields it
 constexpr unsigned long long kTrsWaitBits = 0x7ff4a5a55a5a5a5aull;
 constexpr int kTrsPad = 0x7fffffff;           // code of an empty slot
-constexpr int kTrsMaxSpin = 1 << 26;          // passes without progress: over ten seconds
 constexpr int kTrsLanes = 64;                 // worker lanes = chains of a group
 constexpr int kTrsTJ = 8;                     // tile of chains along the numbering
 constexpr size_t kTrsLdsMax = 158 * 1024;
@@ -64,6 +67,11 @@ constexpr size_t kTrsLdsMax = 158 * 1024;
 // patterns, the wide one up to the 12 of a 27-point one.
 constexpr int kTrsNarrow = 3, kTrsWide = 12;
 constexpr int kTrsLoaders = 256;
+
+// Passes of a worker without progress before it gives up.  A pass takes at least
+// 0.15 us and a row, solved alone, at most some 3 us (a hop through memory), so
+// 64 passes a row cannot run out before all n rows are solved.
+constexpr int64_t trs_wait_passes(int64_t n) { return ((int64_t)1 << 26) + 64 * n; }
 
 __device__ __forceinline__ bool trs_ready(double v) { return (unsigned)__double2hiint(v) != kTrsWaitHi; }
 __device__ __forceinline__ double trs_wait() { return __longlong_as_double((long long)kTrsWaitBits); }
@@ -79,7 +87,8 @@ __device__ __forceinline__ void lds_put(T *p, T v) {
 __device__ __forceinline__ double mem_get(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void mem_put(double *p, double v) {
+template <typename T>
+__device__ __forceinline__ void mem_put(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -96,6 +105,8 @@ struct TrsView {
     const int *cbase;        // LDS place of its first solved row
     const int *glist, *gptr; // group g: chains glist[gptr[g]] .. glist[gptr[g + 1] - 1]
     int groups, C, cap;
+    int fail;                // place of the give-up flag after this triangle's ticket
+    int64_t passes;          // a worker's passes without progress before it gives up
 };
 
 template <bool LOWER, int NE, int NL, int RD>
@@ -170,7 +181,6 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
         fetch(p);
         if (act) take();
         fetch(p + D);
-        int spins = 0;
         while (__any(act)) {
             double xp[NE];
 #pragma unroll
@@ -200,12 +210,8 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
                 act = p < len;
                 if (act) take();
                 fetch(p + D);
-                spins = 0;
             }
-            if (!__any(pub)) {
-                if (++spins > kTrsMaxSpin) lds_put(&s_abort, 1);
-                if (lds_get(&s_abort)) break;
-            }
+            if (!__any(pub) && lds_get(&s_abort)) break;  // the worker has given up
         }
         return;
     }
@@ -215,7 +221,8 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
     const int t = on ? M.glist[q0 + tid] : 0;
     const int cs = on ? M.cstart[t] : 0, len = on ? M.cstart[t + 1] - cs : 0;
     int pl = on ? M.cbase[t] : 0;
-    int p = 0, spins = 0;
+    int p = 0, seen = 0;
+    int64_t idle = 0;  // passes since a row was solved, counted beside the passes that solve one
     int i = LOWER ? cs : cs + len - 1;
     int idx = on ? tid : 0;
     double yprev = 0.0;
@@ -224,52 +231,58 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
     // stores in every pass (vmcnt 0, the other counters untouched)
     __builtin_amdgcn_s_waitcnt(0xF70);
     while (__any(act)) {
-        // the flag first: LDS serves a wave in order, so a record read after
-        // a set flag is whole
-        double s = lds_get(rs + idx);
-        int l[NE];
-        double xv[NE], vv[NE];
+        bool ok;
+        do {
+            // the flag first: LDS serves a wave in order, so a record read after
+            // a set flag is whole
+            double s = lds_get(rs + idx);
+            int l[NE];
+            double xv[NE], vv[NE];
 #pragma unroll
-        for (int m = 0; m < NE; ++m) l[m] = lds_get(rl + m * NS + idx);
+            for (int m = 0; m < NE; ++m) l[m] = lds_get(rl + m * NS + idx);
 #pragma unroll
-        for (int m = 0; m < NE; ++m) vv[m] = lds_get(rv + m * NS + idx);
-        const double vp = lds_get(rvp + idx);
-        double dd = 1.0;
-        if (!LOWER) dd = lds_get(rd + idx);
-        bool ok = act && trs_ready(s);
+            for (int m = 0; m < NE; ++m) vv[m] = lds_get(rv + m * NS + idx);
+            const double vp = lds_get(rvp + idx);
+            double dd = 1.0;
+            if (!LOWER) dd = lds_get(rd + idx);
+            ok = act && trs_ready(s);
 #pragma unroll
-        for (int m = 0; m < NE; ++m) xv[m] = lds_get(xl + (ok ? l[m] : one));
+            for (int m = 0; m < NE; ++m) xv[m] = lds_get(xl + (ok ? l[m] : one));
 #pragma unroll
-        for (int m = 0; m < NE; ++m) ok = ok && trs_ready(xv[m]);
-        // column order: the neighbour is the last entry of L, the first of U;
-        // a chain's first row has none (coefficient and yprev are 0)
-        if (!LOWER) s = s - vp * yprev;
+            for (int m = 0; m < NE; ++m) ok = ok && trs_ready(xv[m]);
+            // column order: the neighbour is the last entry of L, the first of U;
+            // a chain's first row has none (coefficient and yprev are 0)
+            if (!LOWER) s = s - vp * yprev;
 #pragma unroll
-        for (int m = 0; m < NE; ++m) s = s - vv[m] * xv[m];
-        if (LOWER) s = s - vp * yprev;
-        if (ok) {
-            if (!LOWER) s = s / dd;
-            yprev = trs_pub(s);
-            if (pl < cap) lds_put(xl + pl, yprev);
-            mem_put(x + i, yprev);
-            lds_put(rs + idx, trs_wait());  // the slot is free again
-            if (LOWER) {
-                znext[i] = trs_wait();
-            } else if (beta == 0.0) {
-                out[i] = alpha * yprev;
-            } else {
-                out[i] = alpha * yprev + beta * out[i];
+            for (int m = 0; m < NE; ++m) s = s - vv[m] * xv[m];
+            if (LOWER) s = s - vp * yprev;
+            if (ok) {
+                if (!LOWER) s = s / dd;
+                yprev = trs_pub(s);
+                if (pl < cap) lds_put(xl + pl, yprev);
+                mem_put(x + i, yprev);
+                lds_put(rs + idx, trs_wait());  // the slot is free again
+                if (LOWER) {
+                    znext[i] = trs_wait();
+                } else if (beta == 0.0) {
+                    out[i] = alpha * yprev;
+                } else {
+                    out[i] = alpha * yprev + beta * out[i];
+                }
+                ++p;
+                ++pl;
+                i += LOWER ? 1 : -1;
+                act = p < len;
+                idx = act ? (idx + C) & (NS - 1) : 0;  // the next ring slot: NS = RB * C
             }
-            ++p;
-            ++pl;
-            i += LOWER ? 1 : -1;
-            act = p < len;
-            idx = act ? (p & (RB - 1)) * C + tid : 0;
-            spins = 0;
-        }
-        if (!__any(ok)) {
-            if (++spins > kTrsMaxSpin) lds_put(&s_abort, 1);
-            if (lds_get(&s_abort)) break;
+        } while (__any(ok) && __any(act));
+        if (__any(p != seen)) {
+            seen = p;
+            idle = 0;
+        } else if (++idle > M.passes) {
+            lds_put(&s_abort, 1);
+            if (tid == 0) mem_put((int *)ticket + M.fail, 1);
+            break;
         }
     }
     for (; p < len; ++p, i += LOWER ? 1 : -1) {  // the backstop: also ends the waits of later groups
@@ -279,10 +292,15 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
     }
 }
 
+// tickets: one of each triangle, then the give-up flag
 __global__ void k_trs_begin(int64_t n, double *__restrict__ y, unsigned *tickets) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < 2) tickets[i] = 0;
     if (i < n) y[i] = trs_wait();
+}
+
+__global__ void k_trs_clear(unsigned *tickets) {
+    if (threadIdx.x < 3) tickets[threadIdx.x] = 0;
 }
 
 // ------------------------------------------------------------ generation
@@ -663,6 +681,8 @@ TrsView trs_view(const IluImpl &P, const TrsSide &T, bool lower) {
     M.groups = T.groups;
     M.C = T.C;
     M.cap = T.cap;
+    M.fail = lower ? 2 : 1;
+    M.passes = P.wait_passes;
     return M;
 }
 
@@ -755,9 +775,21 @@ mxl_status chain_pack(IluImpl &P, const ChainPlan &C) {
                          (const int *)C.cstart[k]->p, (int *)C.cgroup[k]->p), "triangular solve factors");
     TRS_TRY((trs_allow_lds<kTrsNarrow, 2>()), "LDS attribute");
     TRS_TRY((trs_allow_lds<kTrsWide, 1>()), "LDS attribute");
+    P.wait_passes = trs_wait_passes(P.A->nrows);
+    hipLaunchKernelGGL(k_trs_clear, dim3(1), dim3(64), 0, s, (unsigned *)P.tickets->p);
     TRS_TRY(hipStreamSynchronize(s), "triangular solve factors");  // the plan's temporaries end here
     P.chain = true;
     return MXL_OK;
+}
+
+mxl_status ilu_chain_check(const IluImpl &P) {
+    hipStream_t s = P.A->ctx->stream;
+    unsigned gave_up = 0;
+    TRS_TRY(hipMemcpyAsync(&gave_up, (unsigned *)P.tickets->p + 2, 4, hipMemcpyDeviceToHost, s), "triangular solve");
+    TRS_TRY(hipStreamSynchronize(s), "triangular solve");
+    if (!gave_up) return MXL_OK;
+    hipLaunchKernelGGL(k_trs_clear, dim3(1), dim3(64), 0, s, (unsigned *)P.tickets->p);  // reported once
+    return set_error(MXL_ERR_INTERNAL, "a triangular solve gave up waiting for its operands; its result holds NaN");
 }
 
 hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, double beta, double *out, hipStream_t s) {
@@ -774,3 +806,11 @@ hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, doub
 }
 
 }  // namespace mxl
+
+// Not in the header: lets a test make the solves of P give up after `passes`
+// passes without progress.
+extern "C" mxl_status mxl_ilu_set_wait_passes(mxl_op *Pop, int64_t passes) {
+    if (!Pop || Pop->kind != MXL_OP_ILU || !Pop->ilu->chain || passes < 0) return MXL_ERR_INVALID_ARG;
+    Pop->ilu->wait_passes = passes;
+    return MXL_OK;
+}

@@ -184,7 +184,8 @@ struct IluImpl {
     // exact solves of factors whose rows form chains: no levels are built
     bool chain = false;
     TrsSide lo, up;
-    BufPtr tickets;
+    BufPtr tickets;  // one of each triangle, then the flag of a solve that gave up
+    int64_t wait_passes = 0;
     // other exact solves: the level offsets on the device (runs of small levels are
     // solved by one workgroup in one launch) and the schedule of launches
     BufPtr lptr_d, uptr_d;
@@ -413,6 +414,8 @@ void chain_plan_want(ChainPlan &C, int64_t n, Arena &tmp);
 mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok);
 size_t chain_want(IluImpl &P, const ChainPlan &C, Arena &keep);
 mxl_status chain_pack(IluImpl &P, const ChainPlan &C);
+// Error if a solve since the last check gave up (synchronises the stream).
+mxl_status ilu_chain_check(const IluImpl &P);
 hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, double beta, double *out, hipStream_t s);
 
 // ------------------------------------------------------------- runtime.hip

@@ -1427,6 +1427,7 @@ mxl_status solve_gmres(const SolverImpl &S, const void *b, void *xv, mxl_solve_i
     } else {
         iters = h.iters;
     }
+    if (S.ilu && S.ilu->chain && (rs = ilu_chain_check(*S.ilu)) != MXL_OK) return rs;
     int64_t nspmv = 0;
     HIP_TRY(gm_read(ws, &nspmv, s));
     fill_info(info, S, h, iters, stop, 1 + nspmv + restarts, elapsed_s(t0));

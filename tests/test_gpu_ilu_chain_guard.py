@@ -1,9 +1,13 @@
 """Exact triangular solves of factors that the chain solve must not take or
-must bound: rows whose columns are not in order."""
+must bound: rows whose columns are not in order, and waits that end without
+their operand."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
+import oracle as O
 import workloads as W
 from tests._gpu import DEV, dev, matrix
 
@@ -78,3 +82,60 @@ def test_column_outside_the_matrix_is_an_error(mxl, ctx):
     with pytest.raises(mxl.MxlError) as e:
         mxl.ilu(matrix(mxl, ctx, A), sweeps=1)
     assert e.value.status == mxl.ERR_INVALID_MATRIX
+
+
+def _set_wait_passes(mxl, P, passes):
+    f = mxl.lib.mxl_ilu_set_wait_passes
+    f.argtypes, f.restype = [C.c_void_p, C.c_int64], C.c_int
+    assert f(P.h, passes) == 0
+
+
+def test_a_solve_that_gives_up_is_an_error(mxl, ctx):
+    """With no pass without progress allowed (the worker's first pass never finds a
+    record), every group gives up at once: NaN comes out, the next synchronising
+    call says so once, and with the ordinary limit the same handle solves again."""
+    A = W.convdiff_3d7(19)
+    M = matrix(mxl, ctx, A)
+    P = mxl.ilu(M, sweeps=2)
+    lu = P.info(factors=True)["lu"]
+    r = W.uniform_vec(A.nrows, 5)
+    z = torch.empty(A.nrows, dtype=torch.float64, device=DEV)
+    S = mxl.solver("gmres", M, P, max_iters=200, reduction=1e-8)
+    usual = (1 << 26) + 64 * A.nrows
+    _set_wait_passes(mxl, P, 0)
+    P.apply(dev(r), z)
+    with pytest.raises(mxl.MxlError) as e:
+        P.info()
+    assert e.value.status == mxl.ERR_INTERNAL
+    assert np.isnan(z.cpu().numpy()).any()
+    P.info()  # reported once
+    with pytest.raises(mxl.MxlError):
+        S.solve(dev(r), torch.zeros_like(z))
+    _set_wait_passes(mxl, P, usual)
+    P.apply(dev(r), z)
+    P.info()
+    assert np.array_equal(z.cpu().numpy(), _substitute(A, lu, r))
+    assert S.solve(dev(r), torch.zeros_like(z))["stop_reason"] == mxl.STOP_CONVERGED
+
+
+@pytest.mark.parametrize("n,half", [(4, 30_000), (64, 400)])
+def test_groups_that_wait_for_whole_chains(mxl, ctx, n, half):
+    """Chains one after another: the first row of a chain needs the last row of
+    the chain before it, so that every group waits for all earlier ones."""
+    rows = n * half
+    r = np.arange(rows)
+    cut = r % half == 0
+    pr = np.concatenate([r[~cut], r[cut][1:], r])
+    pc = np.concatenate([r[~cut] - 1, r[cut][1:] - 2, r])
+    key = np.sort(np.unique(np.concatenate([pr * rows + pc, pc * rows + pr])))
+    rr, cc = key // rows, (key % rows).astype(np.int32)
+    v = np.random.default_rng(1).uniform(-1, 1, key.size)
+    v[rr == cc] = np.bincount(rr, weights=np.abs(v), minlength=rows) + 1.0
+    A = W.Csr(rows, rows, np.concatenate([[0], np.cumsum(np.bincount(rr, minlength=rows))]).astype(np.int32), cc, v, "serial")
+    P = mxl.ilu(matrix(mxl, ctx, A), sweeps=1)
+    lu = P.info(factors=True)["lu"]
+    b = W.uniform_vec(rows, 5)
+    z = torch.empty(rows, dtype=torch.float64, device=DEV)
+    P.apply(dev(b), z)
+    P.info()
+    assert np.array_equal(z.cpu().numpy(), O.ilu_apply(A, lu, b, mode=0, sweeps=0))
