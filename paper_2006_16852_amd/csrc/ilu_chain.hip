@@ -84,6 +84,10 @@ template <typename T>
 __device__ __forceinline__ void lds_put(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+// The order of relaxed LDS accesses around a flag: no instructions, as LDS serves
+// a wave's accesses in the order in which they are issued.
+__device__ __forceinline__ void order_after() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront"); }
+__device__ __forceinline__ void order_before() { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); }
 __device__ __forceinline__ double mem_get(const double *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -234,8 +238,9 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
         bool ok;
         do {
             // the flag first: LDS serves a wave in order, so a record read after
-            // a set flag is whole
+            // a set flag is whole; the fence holds the compiler to that order
             double s = lds_get(rs + idx);
+            order_after();
             int l[NE];
             double xv[NE], vv[NE];
 #pragma unroll
@@ -261,6 +266,7 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
                 yprev = trs_pub(s);
                 if (pl < cap) lds_put(xl + pl, yprev);
                 mem_put(x + i, yprev);
+                order_before();                 // the record has been read
                 lds_put(rs + idx, trs_wait());  // the slot is free again
                 if (LOWER) {
                     znext[i] = trs_wait();
