@@ -662,17 +662,22 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     // its release 300.  Exact solves run along the rows' chains where they form
     // some (planned on the device from the pattern, no host copy of the matrix: a new
     // 101^3 system 33 -> 1.6 ms); the sweeps' second copy of the factors and their row
-    // indices then stand where the packed factors will.
+    // indices then stand where the packed factors will.  Without memory for the plan or
+    // the packed factors the solves run by levels, for which the plan's is given back.
     BufPtr bad, w2, row, old;
-    Arena tmp, keep;
+    Arena tmp, keep, plan, packed;
     ChainPlan chains;
-    tmp.want(bad, 4);
-    tmp.want(w2, 8);
-    if (trisolve == 0) chain_plan_want(chains, n, tmp);
+    keep.want(bad, 4);
+    keep.want(w2, 8);
     keep.want(P->dpos, (size_t)n * 4);
     keep.want(P->y, (size_t)n * 8);
     keep.want(P->z, (size_t)n * 8);
-    if (!tmp.alloc() || !keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
+    if (!keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
+    bool chain = false;
+    if (trisolve == 0) {
+        chain_plan_want(chains, n, plan);
+        chain = plan.alloc();
+    }
     const int *rp = (const int *)A->row_ptr->p, *col = (const int *)A->col->p;
     const double *val = (const double *)A->val->p;
     int none = INT_MAX, hb = INT_MAX;
@@ -691,20 +696,22 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
         return set_error(MXL_ERR_ZERO_DIAG, msg);
     }
     mxl_status lst;
-    bool chain = false;
-    if (trisolve == 0 && (lst = chain_plan(*P, chains, chain)) != MXL_OK) return lst;
+    if (chain && (lst = chain_plan(*P, chains, chain)) != MXL_OK) return lst;
     const size_t old_bytes = ((size_t)nnz * 8 + 255) / 256 * 256, sweep_bytes = old_bytes + (size_t)nnz * 4;
-    keep.want(P->lu, (size_t)nnz * 8);
     void *old_p, *row_p;
     if (chain) {
         BufPtr rest;  // keeps the sweeps' arrays inside the allocation
-        keep.want(P->tickets, 12);
-        const size_t have = chain_want(*P, chains, keep);
-        keep.want(rest, have < sweep_bytes ? sweep_bytes - have : 0);
-        if (!keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
-        old_p = P->lo.code->p;
-    } else {
+        packed.want(P->lu, (size_t)nnz * 8);
+        packed.want(P->tickets, 12);
+        const size_t have = chain_want(*P, chains, packed);
+        packed.want(rest, have < sweep_bytes ? sweep_bytes - have : 0);
+        chain = packed.alloc();
+        if (chain) old_p = P->lo.code->p;
+    }
+    if (!chain) {
+        chains = ChainPlan();
         tmp.want(old, sweep_bytes);
+        keep.want(P->lu, (size_t)nnz * 8);
         keep.want(P->t, (size_t)n * 8);
         if (!tmp.alloc() || !keep.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU workspace");
         old_p = old->p;

@@ -741,6 +741,12 @@ mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok) {
             trs_count_groups(p[k], f[k].nch);
         }
     }
+    // Every row is padded to the widest one.  The line is the level layout's, which
+    // counts the neighbour among a row's entries: above it one wide row among short ones
+    // would multiply the factors' memory (a row of 12 entries on either side in a
+    // tridiagonal matrix: 288 bytes a row beside 36) and every application's reads.
+    const int64_t n_pad = (n + 63) / 64 * 64;
+    if ((int64_t)(f[0].w + f[1].w + 2) * n_pad > 4 * P.A->nnz + 2 * n) return MXL_OK;
     C.both = both;
     ok = true;
     return MXL_OK;

@@ -45,6 +45,7 @@ public:
         for (auto &q : parts) total += (q.second + 255) / 256 * 256;
         auto a = std::make_shared<DevBuf>();
         if (hipMalloc(&a->p, total ? total : 256) != hipSuccess) {
+            (void)hipGetLastError();  // the caller may go on without
             a->p = nullptr;
             return false;
         }

@@ -139,3 +139,44 @@ def test_groups_that_wait_for_whole_chains(mxl, ctx, n, half):
     P.apply(dev(b), z)
     P.info()
     assert np.array_equal(z.cpu().numpy(), O.ilu_apply(A, lu, b, mode=0, sweeps=0))
+
+
+def _tridiagonal_with_wide_rows(n, extra):
+    """One row with `extra` more entries before, one with as many behind the diagonal."""
+    A = _banded(n, (-1, 1), 4)
+    rng = np.random.default_rng(6)
+    i, j = n - 3, 2
+    r = np.repeat(np.arange(n, dtype=np.int64), A.row_lengths())
+    add = np.concatenate([i * n + 10 * np.arange(1, extra + 1), j * n + 50 + 10 * np.arange(1, extra + 1)])
+    key = np.concatenate([r * n + A.col, add])
+    val = np.concatenate([A.val, rng.uniform(-0.01, 0.01, add.size)])
+    o = np.argsort(key)
+    key, val = key[o], val[o]
+    r = key // n
+    rp = np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]).astype(np.int32)
+    return W.Csr(n, n, rp, (key % n).astype(np.int32), val, "wide_rows")
+
+
+@pytest.mark.parametrize("extra", [1, 4, 5, 6, 12])
+def test_padding_on_either_side_of_its_line(mxl, ctx, extra):
+    """(2 extra + 2) slots a row against 4 nnz + 2 n: chains up to 5 extra
+    entries, levels above; the same substitution either way."""
+    A = _tridiagonal_with_wide_rows(6001, extra)
+    P = mxl.ilu(matrix(mxl, ctx, A), sweeps=2)
+    lu = P.info(factors=True)["lu"]
+    r = W.uniform_vec(A.nrows, 5)
+    z = torch.empty(A.nrows, dtype=torch.float64, device=DEV)
+    P.apply(dev(r), z)
+    assert np.array_equal(z.cpu().numpy(), O.ilu_apply(A, lu, r, mode=0, sweeps=0))
+
+
+def test_one_wide_row_does_not_multiply_the_memory(mxl, ctx):
+    A = _tridiagonal_with_wide_rows(500_000, 12)
+    M = matrix(mxl, ctx, A)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    P = mxl.ilu(M, sweeps=0)
+    used = before - torch.cuda.mem_get_info()[0]
+    # factors 8 nnz, diagonal, work vectors and level lists: 44 bytes a row; rounding of the allocator
+    assert used <= 8 * A.val.size + 44 * A.nrows + (32 << 20), used
+    del P
