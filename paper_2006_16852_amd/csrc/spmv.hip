@@ -158,27 +158,62 @@ constexpr int kStreamShort = 5;  // the same where runs or blocks hold few entri
 //    rows, g = 64 / m lanes to a row: one gather then covers the same position
 //    of neighbouring rows, in a stencil consecutive x, and not the 64
 //    consecutive entries of two or three rows, far apart in x.
-//  * In a run of unequal rows every lane gathers for the entries it loaded and
-//    the products are parked; g lanes sum each row.  A long row then costs
-//    LDS reads, where the walk would gather with a few lanes active.
+//  * In a run of unequal rows every lane gathers for the entries it loaded, and
+//    values and x are parked; g lanes sum a row of at most 32 or 8 g entries, 16 lanes
+//    a longer one.  A long row then costs LDS reads, where the walk would gather
+//    with a few lanes active.
 //  * A row longer than 64 K is swept by the whole wave.
 //
 // Loads past the end of a run or row repeat its last entry and are left out of
 // the sum: a load under a lane mask makes the compiler wait for it before the
 // next.
 //
+// Every entry is one fused multiply-add, and a lane adds few of them one after
+// another: short chains summed pairwise, as the W lanes of a row were. The split
+// of the nine entries a lane has in flight is the one, of some thirty, whose
+// error is nowhere larger than W lanes' (against 64 bits: 5-point 0.76 of it, 7-point
+// 0.98, 27-point 0.89, random rows of 5 to 300 entries 0.87 to 1.00; rounded products
+// added one after another 1.24, 1.27, 1.63).
+//
+// A wave's rows are written together at the end, lane by lane: a store of each
+// run would have to land before the next run's loads are waited for.
+//
 // Bound by the matrix stream and, per run, its chain row pointers - entries -
-// gathers - sum, which only other waves hide: 24 a CU with K = 8 (6 KB of LDS a
-// wave in FP64).  K = 12 and 16 hold fewer and take 91 and 110 us on the 7-point
+// gathers - sum, which only other waves hide: 20 a CU with K = 8 in FP64 (82
+// registers; 8 KB of LDS a wave, which x of unequal rows may fill but for 32
+// entries).  K = 12 and 16 hold fewer and took 91 and 110 us on the 7-point
 // matrix, g rounded to a power of two 174 us on the 27-point one.
 // W lanes a row (k_csr_vector) -> this, us:
-//   27-point 128^3         FP64 235 -> 157 (4.4 TB/s)   FP32 195 -> 110
-//   7-point 160^3          FP64 112 -> 79               FP32  91 -> 58
-//   power law, n = 450,001, 10.2 M entries, rows up to 7,100:  222 -> 74
+//   27-point 128^3         FP64 217 -> 150 (4.6 TB/s)   FP32 185 -> 97
+//   7-point 128^3          FP64  57 -> 41               FP32  46 -> 29
+//   power law, n = 450,001, 10.1 M entries, rows up to 11,250:  416 -> 82
 __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a * b + c with one rounding.
+__device__ __forceinline__ double fma_v(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_v(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// Sum over each 16-lane row of the wave, in all of its lanes (the same bits),
+// by rotations inside the vector unit.
+template <typename V>
+__device__ __forceinline__ V row16_sum(V v) {
+    typedef typename std::conditional<sizeof(V) == 8, long long, int>::type U;
+#define MXL_ROR(CTRL)                                                          \
+    {                                                                          \
+        U u;                                                                   \
+        __builtin_memcpy(&u, &v, sizeof u);                                    \
+        u = __builtin_amdgcn_update_dpp((U)0, u, CTRL, 0xf, 0xf, true);        \
+        V t;                                                                   \
+        __builtin_memcpy(&t, &u, sizeof t);                                    \
+        v += t;                                                                \
+    }
+    MXL_ROR(0x128) MXL_ROR(0x124) MXL_ROR(0x122) MXL_ROR(0x121)
+#undef MXL_ROR
+    return v;
 }
 
 template <typename V, bool DOT, int K>  // K: entries a lane loads at a time
@@ -186,13 +221,16 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
                                                   const int *__restrict__ col, const V *__restrict__ val,
                                                   SpmvK<V> p) {
     if (p.stop && *p.stop) return;
-    constexpr int kRowsCap = K * kWave;  // entries of a run
+    constexpr int kRowsCap = K * kWave;        // entries of a run
+    constexpr int kUnevenCap = kRowsCap - 32;  // of one of unequal rows: five workgroups a CU have 32,000 bytes each
     constexpr int WPG = kWG / kWave;
+    typedef int __attribute__((may_alias)) int_a;
+    // per wave the values, and the columns (equal rows) or the gathered x (unequal rows)
     __shared__ V s_val[WPG][kRowsCap];
-    __shared__ int s_col[WPG][kRowsCap];
+    __shared__ V s_aux[WPG][sizeof(V) == 8 ? kUnevenCap : kRowsCap];
     const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
-    V *sv = s_val[wid];
-    int *sc = s_col[wid];
+    V *sv = s_val[wid], *sx = s_aux[wid];
+    int_a *sc = (int_a *)s_aux[wid];
     const int G = (int)gridDim.x, nw = G * WPG;
     const int vid = (G % kNumXcd == 0)
                         ? ((int)(blockIdx.x / kNumXcd) * WPG + wid) * kNumXcd + (int)(blockIdx.x % kNumXcd)
@@ -201,30 +239,28 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
     int bs;
     band_walk((n + rw - 1) / rw, vid, nw, b0, b1, bs);
     double dacc = 0.0;
-    auto store = [&](int64_t row, V acc) {
-        const V out = combine(p, acc, row);
-        p.y[row] = out;
-        if (DOT) dacc += (double)p.w[row] * (double)out;
-    };
     for (int64_t b = b0; b < b1; b += bs) {
         const int64_t r0 = b * rw;
         const int nr = (int)(n - r0 < rw ? n - r0 : rw);
         const int64_t rl = r0 + (lane < nr ? lane : nr - 1);
         const int rs = rp[rl], re = rp[rl + 1];
+        const V y0 = p.beta_zero ? (V)0 : p.y[rl];
+        const V w0 = DOT ? p.w[rl] : (V)0;
+        V sum = 0;  // of row r0 + lane
         for (int i = 0; i < nr;) {  // a run of rows i .. i + m - 1 of the block
             const int k0 = __builtin_amdgcn_readlane(rs, i);
             // row ends ascend, so the rows that fit are consecutive from i
-            const int m = __popcll(__ballot(lane < nr && lane >= i && re - k0 <= kRowsCap));
-            const int k1 = __builtin_amdgcn_readlane(re, m ? i + m - 1 : i), tot = k1 - k0;
+            int m = __popcll(__ballot(lane < nr && lane >= i && re - k0 <= kRowsCap));
             // the offsets below are cheaper to form again than to keep in
             // registers across the loop
             int ln = lane;
             asm volatile("" : "+v"(ln));
             if (m == 0) {
+                const int k1 = __builtin_amdgcn_readlane(re, i);
                 V acc = 0;
                 for (uint32_t kb = (uint32_t)k0; kb < (uint32_t)k1; kb += kStreamK * kWave) {
                     int c[kStreamK];
-                    V v[kStreamK];
+                    V v[kStreamK], a[2];
 #pragma unroll
                     for (int j = 0; j < kStreamK; ++j) {
                         const uint32_t k = min((uint32_t)(ln + kWave * j), (uint32_t)k1 - 1 - kb);
@@ -233,24 +269,33 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
                     }
 #pragma unroll
                     for (int j = 0; j < kStreamK; ++j) {
-                        const V t = v[j] * p.x[(uint32_t)c[j]];
-                        acc += kb + ln + kWave * j < (uint32_t)k1 ? t : (V)0;
+                        const V x = p.x[(uint32_t)c[j]], o = j < 2 ? (V)0 : a[j % 2];
+                        a[j % 2] = kb + ln + kWave * j < (uint32_t)k1 ? fma_v(v[j], x, o) : o;
                     }
+                    acc += a[0] + a[1];
                 }
                 acc = wave_sum(acc);
-                if (lane == 0) store(r0 + i, acc);
+                if (lane == i) sum = acc;
                 ++i;
                 continue;
             }
-            V acc = 0;
-            const int g = kWave / m;
+            int tot = __builtin_amdgcn_readlane(re, i + m - 1) - k0;
+            // unequal rows: one has more than 3/2 of the run's mean length
+            bool uneven = __any(lane >= i && lane < i + m && (re - rs) * m > tot + tot / 2 + 8);
+            if (uneven && tot > kUnevenCap) {  // as many rows as leave room for x
+                const int fit = __popcll(__ballot(lane < nr && lane >= i && re - k0 <= kUnevenCap));
+                m = fit > 0 ? fit : 1;
+                uneven = fit > 0;
+                tot = __builtin_amdgcn_readlane(re, i + m - 1) - k0;
+            }
+            const int g = kWave / m;  // lanes for each of the run's rows
             const int row = (ln * (65536 / g + 1)) >> 16, part = ln - row * g;  // ln / g, ln % g
             if (tot > 0) {
+                V acc = 0;
+                bool wide = false;  // the row is summed by 16 lanes below
                 const int src = row < m ? i + row : i;
                 const int q0 = __shfl(rs, src, kWave) - k0, qe = __shfl(re, src, kWave) - k0;  // by all lanes
                 const int q1 = row < m ? qe : q0;
-                // unequal rows: one has more than 3/2 of the run's mean length
-                const bool uneven = __any((q1 - q0) * m > tot + tot / 2 + 8);
                 int c[K];
                 V v[K];
 #pragma unroll
@@ -261,7 +306,12 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
                 }
                 if (uneven) {
 #pragma unroll
-                    for (int j = 0; j < K; ++j) sv[ln + kWave * j] = v[j] * p.x[(uint32_t)c[j]];
+                    for (int j = 0; j < K; ++j) {
+                        const V x = p.x[(uint32_t)c[j]];
+                        const int e = ln + kWave * j;
+                        sv[e] = v[j];
+                        if (j < K - 1 || e < kUnevenCap) sx[e] = x;
+                    }
                 } else {
 #pragma unroll
                     for (int j = 0; j < K; ++j) {
@@ -271,12 +321,61 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
                 }
                 wave_lds_fence();
                 if (uneven) {
-                    for (int q = q0 + part; q < q1; q += g) acc += sv[q];
+                    wide = q1 - q0 > (g < 4 ? 32 : 8 * g);
+                    const int qn = wide ? q0 : q1;
+                    V half = 0;
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) {  // 8 entries of a lane at a time
+                        const int qh = q0 + part + 8 * g * h;
+                        if (!__any(qh < qn)) break;
+                        V vv[8], xv[8], a[2] = {0, 0};
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            const int e = qh + u * g, ec = e < qn ? e : 0;
+                            vv[u] = sv[ec];
+                            xv[u] = sx[ec];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            a[u / 4] = qh + u * g < qn ? fma_v(vv[u], xv[u], a[u / 4]) : a[u / 4];
+                        (h < 2 ? acc : half) += a[0] + a[1];
+                    }
+                    acc += half;
+                    // the longer rows, four at a time with 16 lanes each
+                    for (uint64_t todo = __ballot(wide && part == 0); todo;) {
+                        int e = 0, e1 = 0, to = -1;  // to: the row's first entry
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const int src = todo ? __builtin_ctzll(todo) : 0;
+                            const int s0 = __builtin_amdgcn_readlane(q0, src), s1 = __builtin_amdgcn_readlane(q1, src);
+                            if (ln / 16 == k && todo) {
+                                e = s0 + ln % 16;
+                                e1 = s1;
+                                to = s0;
+                            }
+                            todo &= todo - 1;
+                        }
+                        V t = 0;
+                        for (; __any(e < e1); e += 64) {
+                            V vv[4], xv[4], a = 0;
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const int ec = e + 16 * u < e1 ? e + 16 * u : 0;
+                                vv[u] = sv[ec];
+                                xv[u] = sx[ec];
+                            }
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) a = e + 16 * u < e1 ? fma_v(vv[u], xv[u], a) : a;
+                            t += a;
+                        }
+                        t = row16_sum(t);
+                        if (to >= 0 && ln % 16 == 0) sv[to] = t;
+                    }
                 } else {
                     constexpr int U = 9;  // gathers a lane has in flight
                     for (int q = q0 + part; __any(q < q1); q += U * g) {
                         int cc[U];
-                        V vv[U], xv[U];
+                        V vv[U], xv[U], a[4];
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             const int e = q + u * g, ec = e < q1 ? e : 0;
@@ -285,11 +384,15 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
                         }
 #pragma unroll
                         for (int u = 0; u < U; ++u) xv[u] = p.x[(uint32_t)cc[u]];
+                        asm volatile("" : "+v"(xv[U - 1]));  // gathered with the others, not under a mask of its own
+                        a[0] = a[1] = a[2] = a[3] = 0;
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
-                            const V t = vv[u] * xv[u];
-                            acc += q + u * g < q1 ? t : (V)0;
+                            constexpr bool three = K <= kStreamShort;
+                            V &s = a[three ? u % 3 : u * 4 / U];
+                            s = q + u * g < q1 ? fma_v(vv[u], xv[u], s) : s;
                         }
+                        acc += K <= kStreamShort ? (a[0] + a[1]) + a[2] : (a[0] + a[2]) + (a[1] + a[3]);
                     }
                 }
                 for (int h = g; h > 1;) {  // g is any number: fold the upper half onto the lower
@@ -298,10 +401,19 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
                     if (part + up < h) acc += t;
                     h = up;
                 }
+                // a row's sum takes the place of its first entry, from where the row's lane
+                // fetches it
+                if (part == 0 && !wide && q1 > q0) sv[q0] = acc;
+                wave_lds_fence();
+                if (lane >= i && lane < i + m && re > rs) sum = sv[rs - k0];
+                wave_lds_fence();  // read before the next run's writes
             }
-            if (row < m && part == 0) store(r0 + i + row, acc);
-            __builtin_amdgcn_wave_barrier();  // reads done before the next run's writes
             i += m;
+        }
+        if (lane < nr) {
+            const V out = p.beta_zero ? p.alpha * sum : p.alpha * sum + p.beta * y0;
+            p.y[r0 + lane] = out;
+            if (DOT) dacc += (double)w0 * (double)out;
         }
     }
     if (DOT) {
