@@ -10,6 +10,7 @@
 // HBM-bandwidth bound (about 0.17 flop per byte in FP64), so the designs aim
 // at coalesced, wide, streaming loads of the matrix arrays and keep the
 // gathered x in cache.  No MFMA: this is not a dense contraction.
+#include <algorithm>
 #include <climits>
 
 #include <type_traits>
@@ -178,13 +179,22 @@ constexpr int kStreamShort = 5;  // the same where runs or blocks hold few entri
 // A wave's rows are written together at the end, lane by lane: a store of each
 // run would have to land before the next run's loads are waited for.
 //
+// A block with many times the mean entries would be one wave's chain of runs
+// long after the others are done: helper waves take such blocks cut into parts.
+// Main and helper waves find them by the same rule on the row pointers, nothing
+// is handed over and the sums do not depend on who forms them.  us, without the
+// helpers -> with them (W lanes), n = 10^6, 5 entries a row but for
+//   64 rows of 60,000     5,230 -> 1,100 (2,238)
+//   1,000 rows of 5,000   1,128 ->    94 (268)
+//   300 rows of 1,000       431 ->    46 (95)
+//   the first 2% of 300     305 ->    78 (176)
+//
 // Bound by the matrix stream and, per run, its chain row pointers - entries -
-// gathers - sum, which only other waves hide: 20 a CU with K = 8 in FP64 (82
-// registers; 8 KB of LDS a wave, which x of unequal rows may fill but for 32
-// entries).  K = 12 and 16 hold fewer and took 91 and 110 us on the 7-point
+// gathers - sum, which only other waves hide: 20 a CU with K = 8 in FP64 (8 KB of
+// LDS a wave, which x of unequal rows may fill but for 32 entries).  K = 12 and 16 hold fewer and took 91 and 110 us on the 7-point
 // matrix, g rounded to a power of two 174 us on the 27-point one.
 // W lanes a row (k_csr_vector) -> this, us:
-//   27-point 128^3         FP64 217 -> 150 (4.6 TB/s)   FP32 185 -> 97
+//   27-point 128^3         FP64 217 -> 151 (4.6 TB/s)   FP32 185 -> 99
 //   7-point 128^3          FP64  57 -> 41               FP32  46 -> 29
 //   power law, n = 450,001, 10.1 M entries, rows up to 11,250:  416 -> 82
 __device__ __forceinline__ void wave_lds_fence() {
@@ -216,10 +226,25 @@ __device__ __forceinline__ V row16_sum(V v) {
     return v;
 }
 
+// band_walk's bands for a given number of walkers, from the host: the walk's
+// 64-bit divisions were most of 600 instructions before a wave's first load.
+struct Bands {
+    int lo[kNumXcd + 1];  // XCD x: tiles lo[x] .. lo[x + 1] - 1
+    int q, rem;           // walkers of an XCD, and of how many one more
+};
+
+static Bands bands(int64_t tiles, int walkers) {
+    Bands B;
+    B.q = walkers / kNumXcd;
+    B.rem = walkers % kNumXcd;
+    for (int x = 0; x <= kNumXcd; ++x) B.lo[x] = (int)(tiles * (x * B.q + std::min(x, B.rem)) / std::max(walkers, 1));
+    return B;
+}
+
 template <typename V, bool DOT, int K>  // K: entries a lane loads at a time
-__global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *__restrict__ rp,
-                                                  const int *__restrict__ col, const V *__restrict__ val,
-                                                  SpmvK<V> p) {
+__global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, int64_t heavy, int hg, Bands walk,
+                                                  const int *__restrict__ rp, const int *__restrict__ col,
+                                                  const V *__restrict__ val, SpmvK<V> p) {
     if (p.stop && *p.stop) return;
     constexpr int kRowsCap = K * kWave;        // entries of a run
     constexpr int kUnevenCap = kRowsCap - 32;  // of one of unequal rows: five workgroups a CU have 32,000 bytes each
@@ -228,34 +253,86 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
     // per wave the values, and the columns (equal rows) or the gathered x (unequal rows)
     __shared__ V s_val[WPG][kRowsCap];
     __shared__ V s_aux[WPG][sizeof(V) == 8 ? kUnevenCap : kRowsCap];
-    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+    const int lane = threadIdx.x % kWave, wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     V *sv = s_val[wid], *sx = s_aux[wid];
     int_a *sc = (int_a *)s_aux[wid];
-    const int G = (int)gridDim.x, nw = G * WPG;
-    const int vid = (G % kNumXcd == 0)
-                        ? ((int)(blockIdx.x / kNumXcd) * WPG + wid) * kNumXcd + (int)(blockIdx.x % kNumXcd)
-                        : (int)blockIdx.x * WPG + wid;
-    int64_t b0, b1;
-    int bs;
-    band_walk((n + rw - 1) / rw, vid, nw, b0, b1, bs);
+    // The first hg workgroups do the heavy blocks, the others the rest.  A helper
+    // wave looks at 64 blocks spread over the matrix (ng apart) for every hg-th
+    // group; the four waves that share a group's heavy blocks, each every kHelp-th of
+    // kCuts cuts, lie in different workgroups.
+    constexpr int kHelp = WPG, kCuts = 16;
+    const bool helper = (int)blockIdx.x < hg;
+    int b0 = 0, b1 = 0, bs = 0, cut = kCuts;
+    int ng = 0, group = 0, next = 0;
+    uint64_t todo = 0;
+    if (__builtin_expect(helper, 0)) {
+        ng = (walk.lo[kNumXcd] + kWave - 1) / kWave;
+        next = (int)blockIdx.x + wid * (hg / kHelp);
+        next -= next >= hg ? hg : 0;
+    } else {
+        const int G = (int)gridDim.x - hg, bid = (int)blockIdx.x - hg;
+        const int vid = (G % kNumXcd == 0) ? (bid / kNumXcd * WPG + wid) * kNumXcd + bid % kNumXcd : bid * WPG + wid;
+        const int x = vid % kNumXcd;
+        b0 = walk.lo[x] + vid / kNumXcd;
+        b1 = walk.lo[x + 1];
+        bs = walk.q + (x < walk.rem);
+    }
     double dacc = 0.0;
-    for (int64_t b = b0; b < b1; b += bs) {
-        const int64_t r0 = b * rw;
+    for (;;) {
+        int b = b0;
+        if (__builtin_expect(helper, 0)) {
+            if (cut >= kCuts) {  // the block in hand is done
+                todo &= todo - 1;
+                for (; !todo && next < ng; next += hg) {
+                    group = next;
+                    const int64_t at = ((int64_t)group + (int64_t)lane * ng) * rw, to = at + rw < n ? at + rw : n;
+                    todo = __ballot(at < n && (int64_t)rp[at < n ? to : 0] - rp[at < n ? at : 0] > heavy);
+                }
+                if (!todo) break;
+                cut = wid;
+            }
+            b = group + (int)__builtin_ctzll(todo) * ng;
+        } else {
+            if (b0 >= b1) break;
+            b0 += bs;
+        }
+        const int64_t r0 = (int64_t)b * rw;
         const int nr = (int)(n - r0 < rw ? n - r0 : rw);
         const int64_t rl = r0 + (lane < nr ? lane : nr - 1);
         const int rs = rp[rl], re = rp[rl + 1];
+        const int ks = __builtin_amdgcn_readlane(rs, 0);
+        const int64_t all = (int64_t)__builtin_amdgcn_readlane(re, nr - 1) - ks;
+        int i = 0, last = nr;  // the block's rows i .. last - 1
+        // a row with a quarter of the entries would keep one wave busy all the same
+        const bool shared = all > heavy && !__any(lane < nr && re - rs > all / 4);
+        if (__builtin_expect(helper, 0)) {
+            if (!shared) {
+                cut = kCuts;
+                continue;
+            }
+            const int64_t at = (int64_t)rs - ks;
+            const uint64_t in = __ballot(lane < nr && at >= all * cut / kCuts &&
+                                         (cut == kCuts - 1 || at < all * (cut + 1) / kCuts));
+            cut += kHelp;
+            if (!in) continue;
+            i = __builtin_ctzll(in);
+            last = i + __popcll(in);
+        } else if (shared) {
+            continue;
+        }
+        const bool mine = lane >= i && lane < last;
         const V y0 = p.beta_zero ? (V)0 : p.y[rl];
         const V w0 = DOT ? p.w[rl] : (V)0;
         V sum = 0;  // of row r0 + lane
-        for (int i = 0; i < nr;) {  // a run of rows i .. i + m - 1 of the block
+        while (i < last) {  // a run of rows i .. i + m - 1
             const int k0 = __builtin_amdgcn_readlane(rs, i);
             // row ends ascend, so the rows that fit are consecutive from i
-            int m = __popcll(__ballot(lane < nr && lane >= i && re - k0 <= kRowsCap));
+            int m = __popcll(__ballot(lane < last && lane >= i && re - k0 <= kRowsCap));
             // the offsets below are cheaper to form again than to keep in
             // registers across the loop
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            if (m == 0) {
+            if (__builtin_expect(m == 0, 0)) {
                 const int k1 = __builtin_amdgcn_readlane(re, i);
                 V acc = 0;
                 for (uint32_t kb = (uint32_t)k0; kb < (uint32_t)k1; kb += kStreamK * kWave) {
@@ -283,7 +360,7 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
             // unequal rows: one has more than 3/2 of the run's mean length
             bool uneven = __any(lane >= i && lane < i + m && (re - rs) * m > tot + tot / 2 + 8);
             if (uneven && tot > kUnevenCap) {  // as many rows as leave room for x
-                const int fit = __popcll(__ballot(lane < nr && lane >= i && re - k0 <= kUnevenCap));
+                const int fit = __popcll(__ballot(lane < last && lane >= i && re - k0 <= kUnevenCap));
                 m = fit > 0 ? fit : 1;
                 uneven = fit > 0;
                 tot = __builtin_amdgcn_readlane(re, i + m - 1) - k0;
@@ -410,7 +487,7 @@ __global__ __launch_bounds__(kWG) void k_csr_rows(int64_t n, int rw, const int *
             }
             i += m;
         }
-        if (lane < nr) {
+        if (mine) {
             const V out = p.beta_zero ? p.alpha * sum : p.alpha * sum + p.beta * y0;
             p.y[r0 + lane] = out;
             if (DOT) dacc += (double)w0 * (double)out;
@@ -1393,6 +1470,23 @@ int csr_rows_per_wave(int64_t n, int64_t nnz) {
     return rw;
 }
 
+// Entries above which a block of the staged CSR kernel goes to the helpers: more
+// than four full runs and more than four times the mean block.
+static int64_t csr_rows_heavy(const MatrixImpl &A, int K) {
+    if (!A.grid_tail) return INT64_MAX;
+    const int64_t mean = (int64_t)((double)A.nnz / (double)A.nrows * A.csr_rows);
+    return std::max<int64_t>(4 * K * kWave, 4 * mean);
+}
+
+// Workgroups of its helpers: a wave per 16 blocks, at most 1,024 waves; none
+// where a block is one row, which cannot be cut.
+static int csr_rows_helpers(const MatrixImpl &A) {
+    if (A.csr_rows < 2) return 0;
+    const int64_t nb = (A.nrows + A.csr_rows - 1) / A.csr_rows;
+    const int64_t g = std::min<int64_t>((nb + 63) / 64, 256);
+    return (int)(g < kNumXcd ? g : g / kNumXcd * kNumXcd);
+}
+
 void spmv_plan(MatrixImpl &A) {
     const int cap = spmv_grid_cap(A);
     A.grid_main = A.grid_tail = 0;
@@ -1400,8 +1494,10 @@ void spmv_plan(MatrixImpl &A) {
     switch (A.format) {
     case MXL_FMT_CSR:
         if (A.variant == MXL_CSR_SCALAR) A.grid_main = grid_for((A.nrows + kWG - 1) / kWG, cap);
-        else if (A.variant == MXL_CSR_VECTOR && A.csr_rows)
+        else if (A.variant == MXL_CSR_VECTOR && A.csr_rows) {
             A.grid_main = walker_grid((A.nrows + A.csr_rows - 1) / A.csr_rows, cap);
+            A.grid_tail = csr_rows_helpers(A);
+        }
         else if (A.variant == MXL_CSR_VECTOR)
             A.grid_main = grid_for((A.nrows + kWG / A.vw - 1) / (kWG / A.vw), cap);
         else if (A.variant == MXL_CSR_STREAM) A.grid_main = walker_grid(A.ntiles, cap);
@@ -1496,8 +1592,11 @@ static hipError_t spmv_typed(const MatrixImpl &A, const SpmvArgs &a, hipStream_t
             else hipLaunchKernelGGL((k_csr_scalar<V, false>), dim3(A.grid_main), blk, 0, s, n, rp, col, val, p);
         } else if (A.variant == MXL_CSR_VECTOR && A.csr_rows) {
             // without partials to bound the grid, a block of rows a wave: whoever is done takes the next
-            const dim3 gr(dot ? A.grid_main : walker_grid((n + A.csr_rows - 1) / A.csr_rows, 1 << 20));
-#define MXL_ROWS(D, K) hipLaunchKernelGGL((k_csr_rows<V, D, K>), gr, blk, 0, s, n, A.csr_rows, rp, col, val, p)
+            const dim3 gr(A.grid_tail + (dot ? A.grid_main : walker_grid((n + A.csr_rows - 1) / A.csr_rows, 1 << 20)));
+            const Bands walk = bands((n + A.csr_rows - 1) / A.csr_rows, (int)(gr.x - A.grid_tail) * (kWG / kWave));
+#define MXL_ROWS(D, K)                                                                                      \
+    hipLaunchKernelGGL((k_csr_rows<V, D, K>), gr, blk, 0, s, n, A.csr_rows, csr_rows_heavy(A, K), A.grid_tail, \
+                       walk, rp, col, val, p)
             // 64 rows of at most 5 entries fill runs of 320 (5-point 1024^2 against 512:
             // FP64 19.8 -> 17.9 us, FP32 14.8 -> 13.1)
             if (A.nnz <= kStreamShort * n) {
