@@ -560,11 +560,12 @@ __global__ __launch_bounds__(kWG) void k_csr_stream(int64_t nblk, const int2 *__
                     c[j] = ld_stream(col + kb + k);
                     v[j] = ld_stream(val + kb + k);
                 }
-                // same order as one entry at a time: k = lane, lane + 64, ...
+                // same order as one entry at a time: k = lane, lane + 64, ..., each a
+                // fused multiply-add
 #pragma unroll
                 for (int j = 0; j < kStreamK; ++j) {
-                    const V q = v[j] * p.x[(uint32_t)c[j]];
-                    acc += kb + ln + kWave * j < (uint32_t)k1 ? q : (V)0;
+                    const V q = fma_v(v[j], p.x[(uint32_t)c[j]], acc);
+                    acc = kb + ln + kWave * j < (uint32_t)k1 ? q : acc;
                 }
             }
 #pragma unroll

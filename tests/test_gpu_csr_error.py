@@ -71,3 +71,19 @@ def test_error_is_not_above_w_lanes_a_row(mxl, ctx, name, dtype):
         op.apply(dev(xh), y)
         err[what] = float(np.linalg.norm((y.cpu().numpy().astype(np.longdouble) - want).astype(np.float64)))
     assert err["wrapped"] <= 1.04 * err["lanes"], err
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("short", [3, 9])  # blocks of at most 320 and of 512 entries
+def test_long_rows_of_row_blocks_equal_64_lanes(mxl, ctx, short, dtype):
+    """A row that is a block of its own is swept by the whole wave, one entry a
+    lane after another as with 64 lanes a row: the same bits."""
+    lens = np.where(np.arange(3000) % 50 == 0, np.random.default_rng(1).integers(513, 4000, 3000), short)
+    A = _lengths(lens, 8)
+    M = matrix(mxl, ctx, A, dtype)
+    x = dev(W.uniform_vec(A.ncols, 9), dtype)
+    y = [torch.empty(A.nrows, dtype=dtype, device=DEV) for _ in range(2)]
+    M.convert("csr", variant=mxl.CSR_STREAM).apply(x, y[0])
+    M.convert("csr", variant=1, vector_width=64).apply(x, y[1])
+    long = np.flatnonzero(lens > 512)
+    assert np.array_equal(y[0].cpu().numpy()[long], y[1].cpu().numpy()[long])
