@@ -428,8 +428,10 @@ typedef struct { int32_t wg_size; int32_t wgs_per_cu; int32_t order; int32_t for
  * Sec. 2.5).  With a tuning all systems run in one persistent launch.  tuning
  * NULL runs them by size: systems of at most 1024 rows and 28 entries per row
  * with their matrix in registers, one launch per size class (64, 128, ...,
- * 1024 rows), the others by the autotuned schedule (cached per handle) or the
- * default one; all of them by the autotuned schedule when mxl_batch_autotune
+ * 1024 rows), the others beside them, on a stream of the handle's own, by the
+ * autotuned schedule (cached per handle) or the default one; all of them by
+ * that schedule when there are such others and at most one system a CU, when
+ * mxl_batch_autotune
  * found that faster, or when the batch has no ELL copy.  crit->max_iters <= 0
  * means 10*n_s per system.  b, x: device FP64 of total rows; iters, rel_res,
  * status: device arrays of nsys entries. */
