@@ -42,7 +42,7 @@ __global__ void k_ilu_diag(int64_t n, const int *__restrict__ rp, const int *__r
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int64_t p = row_find(rp, col, i, (int)i);
-    dpos[i] = (int)p;
+    dpos[i] = p < 0 ? rp[i] : (int)p;  // in bounds for what runs before the host has seen *bad
     if (p < 0 || val[p] == 0.0) atomicMin(bad, (int)(i < INT_MAX ? i : INT_MAX));
 }
 
@@ -564,23 +564,28 @@ static mxl_status ilu_levels(IluImpl &P) {
         P.uptr.clear();
         return set_error(MXL_ERR_INTERNAL, "ILU level schedule failed its invariants");
     }
-    auto mk = [](size_t bytes) {
-        auto d = std::make_shared<DevBuf>();
-        if (hipMalloc(&d->p, bytes ? bytes : 16) != hipSuccess) return BufPtr();
-        d->bytes = bytes;
-        d->owned = true;
-        return d;
+    // one allocation and, where the lists are small, one copy: a small system's
+    // generation is host calls
+    Arena lists;
+    lists.want(P.lptr_d, P.lptr.size() * 8);
+    lists.want(P.uptr_d, P.uptr.size() * 8);
+    lists.want(P.lperm, (size_t)n * 4);
+    lists.want(P.uperm, (size_t)n * 4);
+    if (!lists.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU levels");
+    char *base = (char *)P.lptr_d->p;
+    const size_t total = (size_t)((char *)P.uperm->p - base) + (size_t)n * 4;
+    std::vector<char> stage(total <= (64 << 10) ? total : 0);
+    hipError_t e = hipSuccess;
+    auto put = [&](const BufPtr &d, const void *src, size_t bytes) {
+        if (!stage.empty()) memcpy(stage.data() + ((char *)d->p - base), src, bytes);
+        else if (e == hipSuccess) e = hipMemcpyAsync(d->p, src, bytes, hipMemcpyHostToDevice, s);
     };
-    P.lperm = mk((size_t)n * 4);
-    P.uperm = mk((size_t)n * 4);
-    P.lptr_d = mk(P.lptr.size() * 8);
-    P.uptr_d = mk(P.uptr.size() * 8);
-    if (!P.lperm || !P.uperm || !P.lptr_d || !P.uptr_d) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU levels");
-    if (hipMemcpyAsync(P.lperm->p, lperm.data(), n * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(P.uperm->p, uperm.data(), n * 4, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(P.lptr_d->p, P.lptr.data(), P.lptr.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipMemcpyAsync(P.uptr_d->p, P.uptr.data(), P.uptr.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
+    put(P.lptr_d, P.lptr.data(), P.lptr.size() * 8);
+    put(P.uptr_d, P.uptr.data(), P.uptr.size() * 8);
+    put(P.lperm, lperm.data(), (size_t)n * 4);
+    put(P.uperm, uperm.data(), (size_t)n * 4);
+    if (!stage.empty()) e = hipMemcpyAsync(base, stage.data(), total, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return set_error(MXL_ERR_DEVICE, "ILU levels upload");
     P.lruns = trs_runs(P.lptr);
     P.uruns = trs_runs(P.uptr);
@@ -608,17 +613,15 @@ static mxl_status ilu_pack_levels(IluImpl &P) {
     const int64_t n = A.nrows, nnz = A.nnz;
     const int64_t n_pad = (n + 63) / 64 * 64;
     if ((int64_t)(P.lw_lv + P.uw_lv) * n_pad > 4 * nnz + 2 * n) return MXL_OK;
-    auto mk = [](size_t bytes) {
-        auto d = std::make_shared<DevBuf>();
-        if (hipMalloc(&d->p, bytes ? bytes : 16) != hipSuccess) return BufPtr();
-        d->bytes = bytes;
-        d->owned = true;
-        return d;
-    };
     const int wl = P.lw_lv, wu = P.uw_lv;
-    BufPtr lc = mk((size_t)wl * n_pad * 4), lv = mk((size_t)wl * n_pad * 8);
-    BufPtr uc = mk((size_t)wu * n_pad * 4), uv = mk((size_t)wu * n_pad * 8), ud = mk((size_t)n * 8);
-    if (!lc || !lv || !uc || !uv || !ud) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU level-ordered factors");
+    BufPtr lc, lv, uc, uv, ud;
+    Arena a;
+    a.want(lv, (size_t)wl * n_pad * 8);
+    a.want(uv, (size_t)wu * n_pad * 8);
+    a.want(ud, (size_t)n * 8);
+    a.want(lc, (size_t)wl * n_pad * 4);
+    a.want(uc, (size_t)wu * n_pad * 4);
+    if (!a.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "ILU level-ordered factors");
     hipStream_t s = A.ctx->stream;
     const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p;
     const double *lu = (const double *)P.lu->p;
@@ -664,11 +667,10 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     // 101^3 system 33 -> 1.6 ms); the sweeps' second copy of the factors and their row
     // indices then stand where the packed factors will.  Without memory for the plan or
     // the packed factors the solves run by levels, for which the plan's is given back.
-    BufPtr bad, w2, row, old;
+    BufPtr head, old;
     Arena tmp, keep, plan, packed;
     ChainPlan chains;
-    keep.want(bad, 4);
-    keep.want(w2, 8);
+    keep.want(head, chain_head_bytes());
     keep.want(P->dpos, (size_t)n * 4);
     keep.want(P->y, (size_t)n * 8);
     keep.want(P->z, (size_t)n * 8);
@@ -680,23 +682,19 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     }
     const int *rp = (const int *)A->row_ptr->p, *col = (const int *)A->col->p;
     const double *val = (const double *)A->val->p;
-    int none = INT_MAX, hb = INT_MAX;
+    int hb = INT_MAX, *bad, *w2;
     hipError_t e;
-    if ((e = hipMemcpyAsync(bad->p, &none, 4, hipMemcpyHostToDevice, s)) != hipSuccess)
-        return set_error(MXL_ERR_DEVICE, hipGetErrorString(e));
-    hipLaunchKernelGGL(k_ilu_diag, dim3(blocks(n)), dim3(256), 0, s, n, rp, col, val, (int *)P->dpos->p,
-                       (int *)bad->p);
-    if ((e = hipGetLastError()) != hipSuccess ||
-        (e = hipMemcpyAsync(&hb, bad->p, 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
+    mxl_status lst;
+    if ((e = chain_head_init(head, bad, w2, s)) != hipSuccess) return set_error(MXL_ERR_DEVICE, hipGetErrorString(e));
+    hipLaunchKernelGGL(k_ilu_diag, dim3(blocks(n)), dim3(256), 0, s, n, rp, col, val, (int *)P->dpos->p, bad);
+    if ((e = hipGetLastError()) != hipSuccess || (chain && (e = chain_gather(*P, chains, head)) != hipSuccess))
         return set_error(MXL_ERR_DEVICE, std::string("ILU set-up: ") + hipGetErrorString(e));
+    if ((lst = chain_read(*P, chains, head, hb, chain)) != MXL_OK) return lst;
     if (hb != INT_MAX) {
         char msg[96];
         snprintf(msg, sizeof msg, "row %d has a missing or zero diagonal", hb);
         return set_error(MXL_ERR_ZERO_DIAG, msg);
     }
-    mxl_status lst;
-    if (chain && (lst = chain_plan(*P, chains, chain)) != MXL_OK) return lst;
     const size_t old_bytes = ((size_t)nnz * 8 + 255) / 256 * 256, sweep_bytes = old_bytes + (size_t)nnz * 4;
     void *old_p, *row_p;
     if (chain) {
@@ -737,12 +735,10 @@ extern "C" mxl_status mxl_ilu_generate(const mxl_op *Aop, int32_t sweeps, int32_
     // Jacobi sweeps read the factors repacked slot-major when the padding
     // stays within 4x the factor storage
     if (trisolve == 1) {
-        int zero2[2] = {0, 0}, hw[2] = {0, 0};
-        if (hipMemcpyAsync(w2->p, zero2, 8, hipMemcpyHostToDevice, s) != hipSuccess)
-            return set_error(MXL_ERR_DEVICE, "ILU widths init");
+        int hw[2] = {0, 0};
         hipLaunchKernelGGL(k_ilu_widths, dim3((unsigned)std::min<int64_t>(blocks(n), 2048)), dim3(256), 0, s, n, rp,
-                           col, (int *)w2->p);
-        if (hipMemcpyAsync(hw, w2->p, 8, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+                           col, w2);
+        if (hipMemcpyAsync(hw, w2, 8, hipMemcpyDeviceToHost, s) != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
             return set_error(MXL_ERR_DEVICE, "ILU widths read-back");
         const int wl = hw[0], wu = hw[1];
         const int64_t n_pad = (n + 63) / 64 * 64;

@@ -385,9 +385,26 @@ __device__ __forceinline__ void trs_group(const TrsPlan &p, int nch, int g, F f)
         }
 }
 
-__global__ void k_trs_info(TrsInfo *f) {
-    if (threadIdx.x < 2) f[threadIdx.x] = TrsInfo{0, INT_MAX, 0, 0, 0, 0, 0};
+// What a generation reads back at once, in the order of the copy.
+struct TrsHead {
+    int bad;       // first row with a missing or zero diagonal
+    int widths[2];
+    TrsInfo f[2];  // of L and of U
+};
+
+__global__ void k_ilu_begin(TrsHead *h) {
+    if (threadIdx.x == 0) {
+        h->bad = INT_MAX;
+        h->widths[0] = h->widths[1] = 0;
+    }
+    if (threadIdx.x < 2) h->f[threadIdx.x] = TrsInfo{0, INT_MAX, 0, 0, 0, 0, 0};
 }
+
+// Both triangles in every launch (blockIdx.y: 0 the lower, 1 the upper): the plan
+// of a small system costs its launches.
+struct TrsPair {
+    int *sums[2], *rowchain[2], *cstart[2];
+};
 
 // Row i opens a chain: in L when it has no entry i - 1, in U when row i - 1
 // has no entry i (chains are listed by ascending rows in both).
@@ -400,10 +417,12 @@ __device__ __forceinline__ bool trs_head(bool lower, int64_t i, const int *__res
 
 constexpr int kTrsScan = 1024;  // rows per workgroup of the two scan passes
 
-__global__ __launch_bounds__(kWG) void k_trs_count(int64_t n, int lower, const int *__restrict__ rp,
+__global__ __launch_bounds__(kWG) void k_trs_count(int64_t n, const int *__restrict__ rp,
                                                    const int *__restrict__ col, const int *__restrict__ dpos,
-                                                   int *__restrict__ sums) {
+                                                   TrsPair q) {
     __shared__ int part[kWG / kWave];
+    const bool lower = blockIdx.y == 0;
+    int *sums = q.sums[blockIdx.y];
     int h = 0;
     for (int e = 0; e < kTrsScan / kWG; ++e) {
         const int64_t i = (int64_t)blockIdx.x * kTrsScan + e * kWG + threadIdx.x;
@@ -430,10 +449,13 @@ __device__ __forceinline__ int trs_block_scan(int v, int *part) {
     return v;
 }
 
-// Exclusive sums in place (one workgroup); the total goes to sums[nb].
-__global__ __launch_bounds__(kWG) void k_trs_scan(int nb, int *sums) {
+// Exclusive sums in place, a workgroup for each of two arrays; the total goes
+// behind the last.
+__global__ __launch_bounds__(kWG) void k_trs_scan(int n0, int *a0, int n1, int *a1) {
     __shared__ int part[kWG / kWave];
     __shared__ int carry;
+    const int nb = blockIdx.y ? n1 : n0;
+    int *sums = blockIdx.y ? a1 : a0;
     if (threadIdx.x == 0) carry = 0;
     __syncthreads();
     for (int b0 = 0; b0 < nb; b0 += kWG) {
@@ -449,12 +471,14 @@ __global__ __launch_bounds__(kWG) void k_trs_scan(int nb, int *sums) {
 }
 
 // Chain of every row and first row of every chain (cstart[nch] = n).
-__global__ __launch_bounds__(kWG) void k_trs_chains(int64_t n, int lower, const int *__restrict__ rp,
+__global__ __launch_bounds__(kWG) void k_trs_chains(int64_t n, const int *__restrict__ rp,
                                                     const int *__restrict__ col, const int *__restrict__ dpos,
-                                                    const int *__restrict__ sums, int nb, int *__restrict__ rowchain,
-                                                    int *__restrict__ cstart) {
+                                                    TrsPair q, int nb) {
     __shared__ int part[kWG / kWave];
     __shared__ int carry;
+    const bool lower = blockIdx.y == 0;
+    const int *sums = q.sums[blockIdx.y];
+    int *rowchain = q.rowchain[blockIdx.y], *cstart = q.cstart[blockIdx.y];
     if (threadIdx.x == 0) carry = sums[blockIdx.x];
     __syncthreads();
     for (int e = 0; e < kTrsScan / kWG; ++e) {
@@ -482,12 +506,13 @@ __device__ __forceinline__ void trs_entries(bool lower, int i, const int *__rest
         if (col[q] != nb) f(q, col[q]);
 }
 
-__global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const int *__restrict__ rp,
+__global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, const int *__restrict__ rp,
                                                    const int *__restrict__ col, const int *__restrict__ dpos,
-                                                   const int *__restrict__ rowchain,
-                                                   const int *__restrict__ cstart, const int *__restrict__ nchp,
-                                                   TrsInfo *f) {
+                                                   TrsPair pr, int nb, TrsHead *h) {
     __shared__ int part[4][kWG / kWave];
+    const bool lower = blockIdx.y == 0;
+    const int *rowchain = pr.rowchain[blockIdx.y], *cstart = pr.cstart[blockIdx.y], *nchp = pr.sums[blockIdx.y] + nb;
+    TrsInfo *f = h->f + blockIdx.y;
     int v[4] = {0, -INT_MAX, 0, 0};  // widest, -closest, farthest, longest
     // Columns are checked before they index anything: only validated matrices
     // are known to be canonical.
@@ -541,8 +566,11 @@ __global__ __launch_bounds__(kWG) void k_trs_stats(int64_t n, int lower, const i
 // f->bad = 1 when an operand's tile is not at or before its row's tile in
 // both tile coordinates: then a row's operands always come from tiles with
 // earlier tickets, in ascending order for L and descending for U.
-__global__ void k_trs_order(int64_t n, int lower, const int *__restrict__ rp, const int *__restrict__ col,
-                            const int *__restrict__ dpos, const int *__restrict__ rowchain, TrsInfo *f) {
+__global__ void k_trs_order(int64_t n, const int *__restrict__ rp, const int *__restrict__ col,
+                            const int *__restrict__ dpos, TrsPair q, TrsHead *h) {
+    const bool lower = blockIdx.y == 0;
+    const int *rowchain = q.rowchain[blockIdx.y];
+    TrsInfo *f = h->f + blockIdx.y;
     const TrsPlan p = trs_plan(n, *f);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n || !p.ok || p.W == 0) return;
@@ -558,38 +586,54 @@ __global__ void k_trs_order(int64_t n, int lower, const int *__restrict__ rp, co
     if (__any(wrong) && threadIdx.x % kWave == 0) atomicOr(&f->bad, 1);
 }
 
-__global__ void k_trs_sizes(TrsPlan p, int nch, int *__restrict__ gptr) {
+// The packing of a triangle: its plan, the temporaries (rowchain, first, cgroup)
+// and the solve's arrays.
+struct TrsPacked {
+    TrsPlan p;
+    int nch, w, cap;
+    const int *rowchain, *first;  // first: the chains' first rows
+    int *cgroup, *cstart, *gptr, *glist, *cbase, *code;
+    double *val, *prev, *diag;
+};
+
+__global__ void k_trs_sizes(TrsPacked lo, TrsPacked up) {
+    const TrsPacked &T = blockIdx.y ? up : lo;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= p.groups) return;
+    if (g >= T.p.groups) return;
     int c = 0;
-    trs_group(p, nch, g, [&](int) { ++c; });
-    gptr[g] = c;
+    trs_group(T.p, T.nch, g, [&](int) { ++c; });
+    T.gptr[g] = c;
 }
 
 // Each group's chains, their places (one after the other) and their group.
-__global__ void k_trs_lists(TrsPlan p, int nch, const int *__restrict__ gptr, const int *__restrict__ cstart,
-                            int *__restrict__ glist, int *__restrict__ cbase, int *__restrict__ cgroup) {
+__global__ void k_trs_lists(TrsPacked lo, TrsPacked up) {
+    const TrsPacked &T = blockIdx.y ? up : lo;
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g >= p.groups) return;
-    int q = gptr[g];
+    if (g >= T.p.groups) return;
+    int q = T.gptr[g];
     int64_t rows = 0;
-    trs_group(p, nch, g, [&](int t) {
-        glist[q++] = t;
-        cbase[t] = (int)(rows < INT_MAX ? rows : INT_MAX);
-        cgroup[t] = g;
-        rows += cstart[t + 1] - cstart[t];
+    trs_group(T.p, T.nch, g, [&](int t) {
+        T.glist[q++] = t;
+        T.cbase[t] = (int)(rows < INT_MAX ? rows : INT_MAX);
+        T.cgroup[t] = g;
+        rows += T.first[t + 1] - T.first[t];
     });
 }
 
-__global__ void k_trs_encode(int64_t n, int64_t n_pad, int lower, int w, int cap, const int *__restrict__ rp,
-                             const int *__restrict__ col, const int *__restrict__ dpos,
-                             const double *__restrict__ lu, const int *__restrict__ rowchain,
-                             const int *__restrict__ cstart, const int *__restrict__ cbase,
-                             const int *__restrict__ cgroup, int *__restrict__ code, double *__restrict__ val,
-                             double *__restrict__ prev, double *__restrict__ diag) {
+__global__ void k_trs_encode(int64_t n, int64_t n_pad, const int *__restrict__ rp, const int *__restrict__ col,
+                             const int *__restrict__ dpos, const double *__restrict__ lu, TrsPacked lo, TrsPacked up,
+                             unsigned *tickets) {
+    const bool lower = blockIdx.y == 0;
+    const TrsPacked &T = lower ? lo : up;
+    const int *__restrict__ rowchain = T.rowchain, *__restrict__ cstart = T.first, *__restrict__ cgroup = T.cgroup,
+                            *__restrict__ cbase = T.cbase;
+    int *__restrict__ code = T.code;
+    double *__restrict__ val = T.val;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (lower && i < 3) tickets[i] = 0;
+    if (i <= T.nch) T.cstart[i] = cstart[i];
     if (i >= n) return;
-    const int g = cgroup[rowchain[i]];
+    const int g = cgroup[rowchain[i]], w = T.w, cap = T.cap;
     int a = 0;
     trs_entries(lower, (int)i, rp, col, dpos, [&](int q, int c) {
         const int t = rowchain[c];
@@ -608,8 +652,8 @@ __global__ void k_trs_encode(int64_t n, int64_t n_pad, int lower, int w, int cap
     }
     const int nbq = lower ? dpos[i] - 1 : dpos[i] + 1;
     const bool has = lower ? nbq >= rp[i] && col[nbq] == (int)i - 1 : nbq < rp[i + 1] && col[nbq] == (int)i + 1;
-    prev[i] = has ? lu[nbq] : 0.0;
-    if (diag) diag[i] = lu[dpos[i]];
+    T.prev[i] = has ? lu[nbq] : 0.0;
+    if (!lower) T.diag[i] = lu[dpos[i]];
 }
 
 namespace {
@@ -621,45 +665,6 @@ unsigned trs_grid(int64_t n, int per) { return (unsigned)((n + per - 1) / per > 
         const hipError_t e_ = (expr);                                                                          \
         if (e_ != hipSuccess) return set_error(MXL_ERR_DEVICE, std::string(what ": ") + hipGetErrorString(e_)); \
     } while (0)
-
-// The device passes of a triangle's plan, up to its TrsInfo.
-hipError_t trs_gather(const IluImpl &P, bool lower, int *sums, int *rowchain, int *cstart, TrsInfo *f) {
-    const MatrixImpl &A = *P.A;
-    const int64_t n = A.nrows;
-    hipStream_t s = A.ctx->stream;
-    const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p, *dpos = (const int *)P.dpos->p;
-    const int nb = (int)trs_grid(n, kTrsScan), lw = lower;
-    hipLaunchKernelGGL(k_trs_count, dim3(nb), dim3(kWG), 0, s, n, lw, rp, col, dpos, sums);
-    hipLaunchKernelGGL(k_trs_scan, dim3(1), dim3(kWG), 0, s, nb, sums);
-    hipLaunchKernelGGL(k_trs_chains, dim3(nb), dim3(kWG), 0, s, n, lw, rp, col, dpos, (const int *)sums, nb, rowchain,
-                       cstart);
-    hipLaunchKernelGGL(k_trs_stats, dim3(std::min(trs_grid(n, kWG), 1024u)), dim3(kWG), 0, s, n, lw, rp, col, dpos,
-                       (const int *)rowchain, (const int *)cstart, (const int *)sums + nb, f);
-    hipLaunchKernelGGL(k_trs_order, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, lw, rp, col, dpos,
-                       (const int *)rowchain, f);
-    return hipGetLastError();
-}
-
-// Lists and packs a planned triangle (all of it on the stream).
-hipError_t trs_pack(IluImpl &P, bool lower, const TrsPlan &p, int nch, TrsSide &T, const int *rowchain,
-                    const int *cstart, int *cgroup) {
-    const MatrixImpl &A = *P.A;
-    const int64_t n = A.nrows;
-    hipStream_t s = A.ctx->stream;
-    hipError_t e = hipMemcpyAsync(T.cstart->p, cstart, (size_t)(nch + 1) * 4, hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return e;
-    const dim3 g(trs_grid(p.groups, 64));
-    hipLaunchKernelGGL(k_trs_sizes, g, dim3(64), 0, s, p, nch, (int *)T.gptr->p);
-    hipLaunchKernelGGL(k_trs_scan, dim3(1), dim3(kWG), 0, s, p.groups, (int *)T.gptr->p);
-    hipLaunchKernelGGL(k_trs_lists, g, dim3(64), 0, s, p, nch, (const int *)T.gptr->p, (const int *)T.cstart->p,
-                       (int *)T.glist->p, (int *)T.cbase->p, cgroup);
-    hipLaunchKernelGGL(k_trs_encode, dim3(trs_grid(n, 256)), dim3(256), 0, s, n, P.n_pad, (int)lower, T.w, T.cap,
-                       (const int *)A.row_ptr->p, (const int *)A.col->p, (const int *)P.dpos->p,
-                       (const double *)P.lu->p, rowchain, (const int *)T.cstart->p, (const int *)T.cbase->p,
-                       (const int *)cgroup, (int *)T.code->p, (double *)T.val->p, (double *)T.prev->p,
-                       lower ? nullptr : (double *)P.udiag->p);
-    return hipGetLastError();
-}
 
 template <int NE, int RD>
 hipError_t trs_allow_lds() {
@@ -708,29 +713,65 @@ struct TrsBoth {
 };
 }  // namespace
 
+size_t chain_head_bytes() { return sizeof(TrsHead); }
+
+hipError_t chain_head_init(const BufPtr &head, int *&bad, int *&widths, hipStream_t s) {
+    auto *h = (TrsHead *)head->p;
+    bad = &h->bad;
+    widths = h->widths;
+    hipLaunchKernelGGL(k_ilu_begin, dim3(1), dim3(64), 0, s, h);
+    return hipGetLastError();
+}
+
 void chain_plan_want(ChainPlan &C, int64_t n, Arena &tmp) {
-    tmp.want(C.info, 2 * sizeof(TrsInfo));
-    tmp.want(C.sums, ((size_t)trs_grid(n, kTrsScan) + 1) * 4);
     for (int k = 0; k < 2; ++k) {
+        tmp.want(C.sums[k], ((size_t)trs_grid(n, kTrsScan) + 1) * 4);
         tmp.want(C.rowchain[k], (size_t)n * 4);
         tmp.want(C.cstart[k], (size_t)(n + 1) * 4);
         tmp.want(C.cgroup[k], (size_t)n * 4);
     }
 }
 
-mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok) {
+// The device passes of the plan.  Rows without a diagonal (the caller's to
+// report) are read in bounds.
+hipError_t chain_gather(const IluImpl &P, const ChainPlan &C, const BufPtr &head) {
+    const MatrixImpl &A = *P.A;
+    const int64_t n = A.nrows;
+    hipStream_t s = A.ctx->stream;
+    const int *rp = (const int *)A.row_ptr->p, *col = (const int *)A.col->p, *dpos = (const int *)P.dpos->p;
+    const int nb = (int)trs_grid(n, kTrsScan);
+    TrsPair q;
+    for (int k = 0; k < 2; ++k) {
+        q.sums[k] = (int *)C.sums[k]->p;
+        q.rowchain[k] = (int *)C.rowchain[k]->p;
+        q.cstart[k] = (int *)C.cstart[k]->p;
+    }
+    auto *h = (TrsHead *)head->p;
+    hipLaunchKernelGGL(k_trs_count, dim3(nb, 2), dim3(kWG), 0, s, n, rp, col, dpos, q);
+    hipLaunchKernelGGL(k_trs_scan, dim3(1, 2), dim3(kWG), 0, s, nb, q.sums[0], nb, q.sums[1]);
+    hipLaunchKernelGGL(k_trs_chains, dim3(nb, 2), dim3(kWG), 0, s, n, rp, col, dpos, q, nb);
+    hipLaunchKernelGGL(k_trs_stats, dim3(std::min(trs_grid(n, kWG), 1024u), 2), dim3(kWG), 0, s, n, rp, col, dpos, q, nb,
+                       h);
+    hipLaunchKernelGGL(k_trs_order, dim3(trs_grid(n, 256), 2), dim3(256), 0, s, n, rp, col, dpos, q, h);
+    return hipGetLastError();
+}
+
+// Reads the head: bad and, where a plan was gathered (ok), whether the chains suit.
+mxl_status chain_read(const IluImpl &P, ChainPlan &C, const BufPtr &head, int &bad, bool &ok) {
     const int64_t n = P.A->nrows;
     hipStream_t s = P.A->ctx->stream;
+    TrsHead hh;
+    TRS_TRY(hipMemcpyAsync(&hh, head->p, sizeof hh, hipMemcpyDeviceToHost, s), "ILU set-up");
+    TRS_TRY(hipStreamSynchronize(s), "ILU set-up");
+    bad = hh.bad;
+    const bool gathered = ok;
+    ok = false;
+    if (!gathered || bad != INT_MAX) return MXL_OK;
     auto both = std::make_shared<TrsBoth>();
     TrsInfo *f = both->f;
     TrsPlan *p = both->p;
-    hipLaunchKernelGGL(k_trs_info, dim3(1), dim3(64), 0, s, (TrsInfo *)C.info->p);
-    for (int k = 0; k < 2; ++k)
-        TRS_TRY(trs_gather(P, k == 0, (int *)C.sums->p, (int *)C.rowchain[k]->p, (int *)C.cstart[k]->p,
-                           (TrsInfo *)C.info->p + k), "triangular solve plan");
-    TRS_TRY(hipMemcpyAsync(f, C.info->p, sizeof both->f, hipMemcpyDeviceToHost, s), "triangular solve plan");
-    TRS_TRY(hipStreamSynchronize(s), "triangular solve plan");
-    ok = false;
+    f[0] = hh.f[0];
+    f[1] = hh.f[1];
     if ((f[0].faults | f[1].faults) & kTrsOutside)
         return set_error(MXL_ERR_INVALID_MATRIX, "a column index lies outside the matrix");
     for (int k = 0; k < 2; ++k) {
@@ -780,15 +821,28 @@ size_t chain_want(IluImpl &P, const ChainPlan &C, Arena &keep) {
 }
 
 mxl_status chain_pack(IluImpl &P, const ChainPlan &C) {
-    hipStream_t s = P.A->ctx->stream;
+    const MatrixImpl &A = *P.A;
+    const int64_t n = A.nrows;
+    hipStream_t s = A.ctx->stream;
     const TrsBoth &B = *(const TrsBoth *)C.both.get();
-    for (int k = 0; k < 2; ++k)
-        TRS_TRY(trs_pack(P, k == 0, B.p[k], B.f[k].nch, k == 0 ? P.lo : P.up, (const int *)C.rowchain[k]->p,
-                         (const int *)C.cstart[k]->p, (int *)C.cgroup[k]->p), "triangular solve factors");
+    TrsPacked t[2];
+    for (int k = 0; k < 2; ++k) {
+        const TrsSide &T = k == 0 ? P.lo : P.up;
+        t[k] = {B.p[k], B.f[k].nch, T.w, T.cap, (const int *)C.rowchain[k]->p, (const int *)C.cstart[k]->p,
+                (int *)C.cgroup[k]->p, (int *)T.cstart->p, (int *)T.gptr->p, (int *)T.glist->p, (int *)T.cbase->p,
+                (int *)T.code->p, (double *)T.val->p, (double *)T.prev->p, (double *)P.udiag->p};
+    }
+    const dim3 g(trs_grid(std::max(t[0].p.groups, t[1].p.groups), 64), 2);
+    hipLaunchKernelGGL(k_trs_sizes, g, dim3(64), 0, s, t[0], t[1]);
+    hipLaunchKernelGGL(k_trs_scan, dim3(1, 2), dim3(kWG), 0, s, t[0].p.groups, t[0].gptr, t[1].p.groups, t[1].gptr);
+    hipLaunchKernelGGL(k_trs_lists, g, dim3(64), 0, s, t[0], t[1]);
+    hipLaunchKernelGGL(k_trs_encode, dim3(trs_grid(n + 1, 256), 2), dim3(256), 0, s, n, P.n_pad,
+                       (const int *)A.row_ptr->p, (const int *)A.col->p, (const int *)P.dpos->p,
+                       (const double *)P.lu->p, t[0], t[1], (unsigned *)P.tickets->p);
+    TRS_TRY(hipGetLastError(), "triangular solve factors");
     TRS_TRY((trs_allow_lds<kTrsNarrow, 2>()), "LDS attribute");
     TRS_TRY((trs_allow_lds<kTrsWide, 1>()), "LDS attribute");
-    P.wait_passes = trs_wait_passes(P.A->nrows);
-    hipLaunchKernelGGL(k_trs_clear, dim3(1), dim3(64), 0, s, (unsigned *)P.tickets->p);
+    P.wait_passes = trs_wait_passes(n);
     TRS_TRY(hipStreamSynchronize(s), "triangular solve factors");  // the plan's temporaries end here
     P.chain = true;
     return MXL_OK;

@@ -402,17 +402,22 @@ hipError_t gm_small(int n, int m, const int *rp, const int *col, const double *v
 hipError_t ilu_apply(const IluImpl &P, double alpha, const void *r, double beta, void *out, hipStream_t s);
 
 // ------------------------------------------------------- ilu_chain.hip
-// Packs both triangles for the chain solve and sets P.chain when they suit it.
-// The exact solves' chains: a plan from the pattern (temporaries in tmp; ok is
-// false if the rows form too few chains), the solves' buffers in keep (returns
-// their bytes, code of the lower triangle first), and the lists and factors in
-// them once the factors are final.
+// The chains of the exact solves.  A generation's head (device memory of
+// chain_head_bytes) holds the first row without a diagonal, the triangles' widths
+// and what the plan needs; chain_gather forms a plan from the pattern
+// (temporaries from chain_plan_want) and chain_read reads the head back, ok false if
+// nothing was gathered or the rows form too few chains.  chain_want asks for the
+// solves' buffers (returns their bytes, code of the lower triangle first) and
+// chain_pack fills them once the factors are final.
 struct ChainPlan {
-    BufPtr info, sums, rowchain[2], cstart[2], cgroup[2];
+    BufPtr sums[2], rowchain[2], cstart[2], cgroup[2];
     std::shared_ptr<void> both;
 };
+size_t chain_head_bytes();
+hipError_t chain_head_init(const BufPtr &head, int *&bad, int *&widths, hipStream_t s);
 void chain_plan_want(ChainPlan &C, int64_t n, Arena &tmp);
-mxl_status chain_plan(const IluImpl &P, ChainPlan &C, bool &ok);
+hipError_t chain_gather(const IluImpl &P, const ChainPlan &C, const BufPtr &head);
+mxl_status chain_read(const IluImpl &P, ChainPlan &C, const BufPtr &head, int &bad, bool &ok);
 size_t chain_want(IluImpl &P, const ChainPlan &C, Arena &keep);
 mxl_status chain_pack(IluImpl &P, const ChainPlan &C);
 // Error if a solve since the last check gave up (synchronises the stream).
