@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kTrsLanes + NL) void k_trs_chain(TrsView M, const d
                 act = p < len;
                 idx = act ? (idx + C) & (NS - 1) : 0;  // the next ring slot: NS = RB * C
             }
-        } while (__any(ok) && __any(act));
+        } while (__any(ok));
         if (__any(p != seen)) {
             seen = p;
             idle = 0;
@@ -470,16 +470,17 @@ __global__ __launch_bounds__(kWG) void k_trs_scan(int n0, int *a0, int n1, int *
     if (threadIdx.x == 0) sums[nb] = carry;
 }
 
-// Chain of every row and first row of every chain (cstart[nch] = n).
+// Chain of every row and first row of every chain (cstart[nch] = n).  With one
+// block of rows nothing is summed before: the total is found here.
 __global__ __launch_bounds__(kWG) void k_trs_chains(int64_t n, const int *__restrict__ rp,
                                                     const int *__restrict__ col, const int *__restrict__ dpos,
                                                     TrsPair q, int nb) {
     __shared__ int part[kWG / kWave];
     __shared__ int carry;
     const bool lower = blockIdx.y == 0;
-    const int *sums = q.sums[blockIdx.y];
+    int *sums = q.sums[blockIdx.y];
     int *rowchain = q.rowchain[blockIdx.y], *cstart = q.cstart[blockIdx.y];
-    if (threadIdx.x == 0) carry = sums[blockIdx.x];
+    if (threadIdx.x == 0) carry = nb > 1 ? sums[blockIdx.x] : 0;
     __syncthreads();
     for (int e = 0; e < kTrsScan / kWG; ++e) {
         const int64_t i = (int64_t)blockIdx.x * kTrsScan + e * kWG + threadIdx.x;
@@ -493,7 +494,10 @@ __global__ __launch_bounds__(kWG) void k_trs_chains(int64_t n, const int *__rest
         if (threadIdx.x == kWG - 1) carry = s;
         __syncthreads();
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) cstart[sums[nb]] = (int)n;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (nb == 1) sums[1] = carry;
+        cstart[sums[nb]] = (int)n;
+    }
 }
 
 // Entries of row i's triangle besides the chain neighbour, in column order.
@@ -605,12 +609,29 @@ __global__ void k_trs_sizes(TrsPacked lo, TrsPacked up) {
     T.gptr[g] = c;
 }
 
-// Each group's chains, their places (one after the other) and their group.
-__global__ void k_trs_lists(TrsPacked lo, TrsPacked up) {
+// Each group's chains, their places (one after the other) and their group.  SUM:
+// one wave holds all groups and sums their sizes itself.
+template <bool SUM>
+__global__ __launch_bounds__(kWave) void k_trs_lists(TrsPacked lo, TrsPacked up) {
     const TrsPacked &T = blockIdx.y ? up : lo;
-    const int g = blockIdx.x * blockDim.x + threadIdx.x;
+    const int g = blockIdx.x * kWave + threadIdx.x;
+    int q = 0;
+    if (SUM) {
+        int c = 0;
+        if (g < T.p.groups) trs_group(T.p, T.nch, g, [&](int) { ++c; });
+        int end = c;
+        for (int d = 1; d < kWave; d <<= 1) {
+            const int u = __shfl_up(end, d, kWave);
+            if (g >= d) end += u;
+        }
+        q = end - c;
+        if (g < T.p.groups) {
+            T.gptr[g] = q;
+            if (g == T.p.groups - 1) T.gptr[g + 1] = end;
+        }
+    }
     if (g >= T.p.groups) return;
-    int q = T.gptr[g];
+    if (!SUM) q = T.gptr[g];
     int64_t rows = 0;
     trs_group(T.p, T.nch, g, [&](int t) {
         T.glist[q++] = t;
@@ -747,8 +768,10 @@ hipError_t chain_gather(const IluImpl &P, const ChainPlan &C, const BufPtr &head
         q.cstart[k] = (int *)C.cstart[k]->p;
     }
     auto *h = (TrsHead *)head->p;
-    hipLaunchKernelGGL(k_trs_count, dim3(nb, 2), dim3(kWG), 0, s, n, rp, col, dpos, q);
-    hipLaunchKernelGGL(k_trs_scan, dim3(1, 2), dim3(kWG), 0, s, nb, q.sums[0], nb, q.sums[1]);
+    if (nb > 1) {
+        hipLaunchKernelGGL(k_trs_count, dim3(nb, 2), dim3(kWG), 0, s, n, rp, col, dpos, q);
+        hipLaunchKernelGGL(k_trs_scan, dim3(1, 2), dim3(kWG), 0, s, nb, q.sums[0], nb, q.sums[1]);
+    }
     hipLaunchKernelGGL(k_trs_chains, dim3(nb, 2), dim3(kWG), 0, s, n, rp, col, dpos, q, nb);
     hipLaunchKernelGGL(k_trs_stats, dim3(std::min(trs_grid(n, kWG), 1024u), 2), dim3(kWG), 0, s, n, rp, col, dpos, q, nb,
                        h);
@@ -832,10 +855,14 @@ mxl_status chain_pack(IluImpl &P, const ChainPlan &C) {
                 (int *)C.cgroup[k]->p, (int *)T.cstart->p, (int *)T.gptr->p, (int *)T.glist->p, (int *)T.cbase->p,
                 (int *)T.code->p, (double *)T.val->p, (double *)T.prev->p, (double *)P.udiag->p};
     }
-    const dim3 g(trs_grid(std::max(t[0].p.groups, t[1].p.groups), 64), 2);
-    hipLaunchKernelGGL(k_trs_sizes, g, dim3(64), 0, s, t[0], t[1]);
-    hipLaunchKernelGGL(k_trs_scan, dim3(1, 2), dim3(kWG), 0, s, t[0].p.groups, t[0].gptr, t[1].p.groups, t[1].gptr);
-    hipLaunchKernelGGL(k_trs_lists, g, dim3(64), 0, s, t[0], t[1]);
+    const dim3 g(trs_grid(std::max(t[0].p.groups, t[1].p.groups), kWave), 2);
+    if (g.x == 1) {
+        hipLaunchKernelGGL(k_trs_lists<true>, g, dim3(kWave), 0, s, t[0], t[1]);
+    } else {
+        hipLaunchKernelGGL(k_trs_sizes, g, dim3(kWave), 0, s, t[0], t[1]);
+        hipLaunchKernelGGL(k_trs_scan, dim3(1, 2), dim3(kWG), 0, s, t[0].p.groups, t[0].gptr, t[1].p.groups, t[1].gptr);
+        hipLaunchKernelGGL(k_trs_lists<false>, g, dim3(kWave), 0, s, t[0], t[1]);
+    }
     hipLaunchKernelGGL(k_trs_encode, dim3(trs_grid(n + 1, 256), 2), dim3(256), 0, s, n, P.n_pad,
                        (const int *)A.row_ptr->p, (const int *)A.col->p, (const int *)P.dpos->p,
                        (const double *)P.lu->p, t[0], t[1], (unsigned *)P.tickets->p);
