@@ -1032,8 +1032,12 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     ar.want(J->bcond, (size_t)nb * 8);
     ar.want(J->boff, (size_t)nb * 8);
     ar.want(J->bprec, (size_t)nb * 4);
-    // lowest singular block, whether precisions differ, whether to invert strictly; then the offsets' sums
-    ar.want(flags, (kScanGrid + 1) * 8);
+    // What a pass leaves for the host, then the sums of the offsets' chunks.
+    struct Flags {
+        int bad, mixed, redo, pad;  // lowest singular block, whether precisions differ, whether to invert strictly
+        int64_t total;              // bytes of the storage, where the pass found the offsets
+    } hf;
+    ar.want(flags, sizeof(Flags) + kScanGrid * 8);
     auto mk = [&](int64_t bytes) {
         auto d = std::make_shared<DevBuf>();
         if (hipMalloc(&d->p, (size_t)bytes) != hipSuccess) return BufPtr();
@@ -1045,23 +1049,28 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     out.want = adaptive ? BJ_P16 : BJ_P64;
     out.stride = bj_stride(bs, out.want);
     if (!ar.alloc()) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi workspace");
-    int *fl = (int *)flags->p, *prec = (int *)J->bprec->p;
-    int64_t *off = (int64_t *)J->boff->p;
-    int hf[3];
-    out.mixed = fl + 1;
-    out.redo = fl + 2;
+    auto *fl = (Flags *)flags->p;
+    int *prec = (int *)J->bprec->p;
+    int64_t *off = (int64_t *)J->boff->p, *sums = (int64_t *)(fl + 1);
+    out.mixed = &fl->mixed;
+    out.redo = &fl->redo;
     hipError_t e = hipSuccess;
     auto pass = [&](bool strict, int64_t blocks, int64_t every) -> mxl_status {
-        hf[0] = INT_MAX;
-        hf[1] = hf[2] = 0;
-        if ((e = hipMemcpyAsync(fl, hf, 12, hipMemcpyHostToDevice, s)) != hipSuccess ||
-            (e = bj_invert(*A, bs, adaptive ? 1 : 0, accuracy, (double *)J->bcond->p, prec, fl, out, strict, blocks,
-                           every, s)) != hipSuccess)
+        hf = {INT_MAX, 0, 0, 0, 0};
+        if ((e = hipMemcpyAsync(fl, &hf, sizeof hf, hipMemcpyHostToDevice, s)) != hipSuccess ||
+            (e = bj_invert(*A, bs, adaptive ? 1 : 0, accuracy, (double *)J->bcond->p, prec, &fl->bad, out, strict,
+                           blocks, every, s)) != hipSuccess)
             return set_error(MXL_ERR_DEVICE, std::string("block inversion: ") + hipGetErrorString(e));
         if (out.store) hipLaunchKernelGGL(k_bj_offsets, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, s, nb,
                                           out.stride, off);
+        if (out.inv) {  // offsets of mixed precisions, read back with the flags
+            const int g = (int)std::min<int64_t>(kScanGrid, (nb + kScanWG - 1) / kScanWG);
+            const int64_t chunk = (nb + g - 1) / g;
+            if (g > 1) hipLaunchKernelGGL(k_bj_sizes, dim3(g), dim3(kScanWG), 0, s, nb, chunk, bs, prec, sums);
+            hipLaunchKernelGGL(k_bj_scan, dim3(g), dim3(kScanWG), 0, s, nb, chunk, bs, prec, sums, off, &fl->total);
+        }
         if ((e = hipGetLastError()) != hipSuccess ||
-            (e = hipMemcpyAsync(hf, fl, 12, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+            (e = hipMemcpyAsync(&hf, fl, sizeof hf, hipMemcpyDeviceToHost, s)) != hipSuccess ||
             (e = hipStreamSynchronize(s)) != hipSuccess)
             return set_error(MXL_ERR_DEVICE, std::string("block inversion read-back: ") + hipGetErrorString(e));
         return MXL_OK;
@@ -1072,7 +1081,7 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
     bool mixed = false;
     if (adaptive && nb > 4 * kLook && nb * out.stride >= (int64_t)16 << 20) {
         if ((st = pass(false, kLook, nb / kLook)) != MXL_OK) return st;
-        mixed = hf[1] != 0;
+        mixed = hf.mixed != 0;
     } else if (adaptive) {
         mixed = true;  // small: the copy costs less than a guess that fails
     }
@@ -1088,28 +1097,18 @@ extern "C" mxl_status mxl_bjacobi_generate(const mxl_op *Aop, int32_t block_size
             out.store = (unsigned char *)J->bstore->p;
         }
         if ((st = pass(strict, nb, 1)) != MXL_OK) return st;
-        if (hf[2] && !strict) strict = true;
-        else if (hf[1] && !mixed) mixed = true;
+        if (hf.redo && !strict) strict = true;
+        else if (hf.mixed && !mixed) mixed = true;
         else break;
     }
-    if (hf[0] != INT_MAX) {
+    if (hf.bad != INT_MAX) {
         char msg[96];
-        snprintf(msg, sizeof msg, "diagonal block %d is singular", hf[0]);
+        snprintf(msg, sizeof msg, "diagonal block %d is singular", hf.bad);
         return set_error(MXL_ERR_ZERO_DIAG, msg);
     }
     if (tmp) {
-        int64_t total = 0;
-        const int g = (int)std::min<int64_t>(kScanGrid, (nb + kScanWG - 1) / kScanWG);
-        const int64_t chunk = (nb + g - 1) / g;
-        int64_t *sums = (int64_t *)fl;  // the chunks' sums, then the total
-        hipLaunchKernelGGL(k_bj_sizes, dim3(g), dim3(kScanWG), 0, s, nb, chunk, bs, prec, sums);
-        hipLaunchKernelGGL(k_bj_scan, dim3(g), dim3(kScanWG), 0, s, nb, chunk, bs, prec, sums, off, sums + kScanGrid);
-        if ((e = hipGetLastError()) != hipSuccess ||
-            (e = hipMemcpyAsync(&total, sums + kScanGrid, 8, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-            (e = hipStreamSynchronize(s)) != hipSuccess)
-            return set_error(MXL_ERR_DEVICE, std::string("block Jacobi offsets: ") + hipGetErrorString(e));
-        if (!(J->bstore = mk(total))) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi storage");
-        J->bstore_bytes = total;
+        if (!(J->bstore = mk(hf.total))) return set_error(MXL_ERR_OUT_OF_MEMORY, "block Jacobi storage");
+        J->bstore_bytes = hf.total;
         if ((e = bj_pack(bs, nb, (const double *)tmp->p, prec, off, (unsigned char *)J->bstore->p, s)) != hipSuccess ||
             (e = hipStreamSynchronize(s)) != hipSuccess)
             return set_error(MXL_ERR_DEVICE, std::string("block Jacobi packing: ") + hipGetErrorString(e));
