@@ -898,12 +898,12 @@ hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, doub
     return hipGetLastError();
 }
 
-}  // namespace mxl
-
-// Not in the header: lets a test make the solves of P give up after `passes`
+// Not an entry point: lets a test make the solves of P give up after `passes`
 // passes without progress.
-extern "C" mxl_status mxl_ilu_set_wait_passes(mxl_op *Pop, int64_t passes) {
-    if (!Pop || Pop->kind != MXL_OP_ILU || !Pop->ilu->chain || passes < 0) return MXL_ERR_INVALID_ARG;
-    Pop->ilu->wait_passes = passes;
-    return MXL_OK;
+int ilu_chain_set_wait_passes(mxl_op *P, int64_t passes) {
+    if (!P || P->kind != MXL_OP_ILU || !P->ilu->chain || passes < 0) return 1;
+    P->ilu->wait_passes = passes;
+    return 0;
 }
+
+}  // namespace mxl

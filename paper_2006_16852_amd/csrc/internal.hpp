@@ -422,6 +422,7 @@ size_t chain_want(IluImpl &P, const ChainPlan &C, Arena &keep);
 mxl_status chain_pack(IluImpl &P, const ChainPlan &C);
 // Error if a solve since the last check gave up (synchronises the stream).
 mxl_status ilu_chain_check(const IluImpl &P);
+int ilu_chain_set_wait_passes(mxl_op *P, int64_t passes);
 hipError_t ilu_chain_apply(const IluImpl &P, double alpha, const double *r, double beta, double *out, hipStream_t s);
 
 // ------------------------------------------------------------- runtime.hip
