@@ -440,9 +440,12 @@ mxl_status mxl_batch_solve(const mxl_op *B, const mxl_criteria *crit,
                            double *x, int32_t *iters, double *rel_res,
                            uint8_t *status);
 
-/* Autotune the batched schedule: times each candidate (reps launches each)
- * and stores the best on the handle, and whether the solve by size classes is
- * faster still; best may be NULL. */
+/* Autotune the batched schedule: times each candidate of the persistent
+ * kernels (reps launches each) and stores the best on the handle, and whether
+ * the solve by size classes is faster still.  best (may be NULL) and best_ms
+ * are that persistent schedule and its time, also where the classes beat it:
+ * passed to mxl_batch_solve, best runs that schedule, while a call without one
+ * takes the faster of the two. */
 mxl_status mxl_batch_autotune(const mxl_op *B, const mxl_criteria *crit,
                               const double *b, double *x_scratch, int reps,
                               mxl_tuning *best, double *best_ms);

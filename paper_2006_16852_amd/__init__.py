@@ -408,8 +408,8 @@ class Ilu(Op):
 
 
 def ilu(A: Op, sweeps: int = 5, trisolve: str = "exact", trs_sweeps: int = 0) -> Ilu:
-    """ParILU(sweeps) factors; trisolve "exact" (level-scheduled
-    substitution) or "jacobi" (trs_sweeps Jacobi sweeps per triangle)."""
+    """ParILU(sweeps) factors; trisolve "exact" (along chains of rows, or by levels,
+    one row after another) or "jacobi" (trs_sweeps Jacobi sweeps per triangle)."""
     h = C.c_void_p()
     A.ctx.use_current_stream()
     mode = {"exact": 0, "jacobi": 1}[trisolve]
@@ -508,7 +508,10 @@ class Batch(Op):
                                            _ptr(b), _ptr(x), _ptr(iters), _ptr(rel_res), _ptr(status)))
 
     def autotune(self, b, x_scratch, reps: int = 2, **crit):
-        """Time every schedule on this batch; returns ((wg_size, wgs_per_cu, order, format), ms)."""
+        """Time every schedule on this batch and the solve by size classes; solve() without
+        a schedule then takes the fastest.  Returns the best schedule of the persistent
+        kernels, ((wg_size, wgs_per_cu, order, format), ms), whether or not the size
+        classes beat it."""
         _need_cuda(b, x_scratch)
         c = criteria(**({"max_iters": 0} | crit))
         t = Tuning()

@@ -1,17 +1,23 @@
-// batched.hip -- thousands of independent small Jacobi-PCG solves in one
-// persistent launch (per-system stopping status: the per-right-hand-side
-// stopping status of the criteria in Sec. 2.5 of the paper, applied to
-// independent systems).
+// batched.hip -- thousands of independent small Jacobi-PCG solves in one call
+// (per-system stopping status: the per-right-hand-side stopping status of the
+// criteria in Sec. 2.5 of the paper, applied to independent systems), and the
+// one-workgroup solves of a single small system.
 //
-// Design (gfx950): a grid of wgs_per_cu x num_CU workgroups stays resident;
+// Design (gfx950), two ways.  By size classes, the way of a call without a
+// schedule: systems of at most 1,024 rows and kClsW entries a row are sorted
+// by size, and a workgroup a system holds matrix and vectors in registers
+// (k_batch_pcg_cls); the others run beside the classes by the second way.
+// Persistent kernels, the way of a chosen schedule, of a batch that has no ELL
+// copy and of those other systems: a grid of wgs_per_cu x num_CU workgroups
+// stays resident;
 // each workgroup pulls a system id from an atomic queue, runs the whole CG
 // for that system with its vectors r, p, q, x in LDS (or in a per-workgroup
 // global scratch slice when the system is too large for LDS), reduces dot
 // products inside the workgroup (fixed tree: deterministic), writes x, the
 // iteration count, the recurrence residual and the stop reason, and pulls
 // the next id.  Every workgroup exits when the queue is drained.  The
-// schedule (workgroup size, residency, order) is chosen by an autotuner
-// that times the candidates on the actual batch.
+// schedule (workgroup size, residency, order) can be chosen by an autotuner
+// that times the candidates, and the size classes, on the actual batch.
 #include <algorithm>
 #include <chrono>
 #include <climits>
@@ -691,7 +697,8 @@ struct SmallRows {
 // Whole Jacobi-PCG of one small system in one workgroup: the rows, x, r, p and
 // dinv in registers; p, which the product gathers, is mirrored in LDS.  An
 // iteration is the product, two reductions and the updates, and touches no
-// memory.
+// memory, but for what two shapes spill: 196 bytes a lane in <512, 2, 32>, 8 in
+// <512, 8, 5>.
 //
 // Bound by one CU's iteration: vector instructions (61% of the cycles at 4096
 // rows), the LDS reads of the product, three barriers, two reductions (lane
@@ -806,7 +813,7 @@ __global__ __launch_bounds__(B) void k_small_pcg(int n, const int *__restrict__ 
 // r_hat, p, v, x and dinv stay in registers; the vector the product gathers
 // (p_hat, then s_hat) is mirrored in LDS.  Between two writes of it lie the
 // barriers of at least one reduction, as between two uses of a reduction's
-// array.  out3: iterations (int32 at 0), relative residual
+// array.  <512, 8, 5> spills 136 bytes a lane.  out3: iterations (int32 at 0), relative residual
 // (double at 8), status (byte 16), half step (byte 17).
 template <int B, int RPT, int W>
 __global__ __launch_bounds__(B) void k_small_bicgstab(int n, const int *__restrict__ rp,

@@ -150,15 +150,18 @@ __device__ __forceinline__ _Float16 narrow_f16(double x) {
 // columns), and step c turns column c of the block into the column of the
 // inverse that belongs to row c's original row (rows are swapped by partial
 // pivoting).  Column c's entries reach the group by a lane broadcast inside the
-// vector unit, so a step is register arithmetic with no barrier; a row whose
-// entry is zero in every block of the wave is skipped.  Every element of the
+// vector unit, so a step is vector arithmetic with no barrier.  Every element of the
 // inverse sees the same operations in the same order as a sequential
 // Gauss-Jordan elimination of (D | I) with partial pivoting (first row of
 // largest magnitude), with no multiply-add contraction, so the inverse, its
-// condition number and the precision decision are reproducible.
+// condition number and the precision decision are reproducible.  (A zero may
+// differ in its sign: where the sequential elimination skips a row with a zero
+// entry, -0 minus a product of -0 becomes +0 here.)
 //
 // Bound by vector instructions (busy 68% of the cycles at two waves a SIMD; D is
-// 128 registers): 2 of FP64 per element and step and a broadcast per row.
+// 128 registers, and what stands beside it at 32 rows exceeds the other 128 by
+// 180 to 200 bytes of scratch a lane): 2 of FP64 per element and step and a
+// broadcast per row.
 // 128,000 blocks of 32: 4.4 ms with D and I side by side, one block a wave and
 // scalar broadcasts -> 1.05 ms.
 //

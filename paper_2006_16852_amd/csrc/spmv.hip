@@ -191,8 +191,9 @@ constexpr int kStreamShort = 5;  // the same where runs or blocks hold few entri
 //
 // Bound by the matrix stream and, per run, its chain row pointers - entries -
 // gathers - sum, which only other waves hide: 20 a CU with K = 8 in FP64 (8 KB of
-// LDS a wave, which x of unequal rows may fill but for 32 entries).  K = 12 and 16 hold fewer and took 91 and 110 us on the 7-point
-// matrix, g rounded to a power of two 174 us on the 27-point one.
+// LDS a wave, which x of unequal rows may fill but for 32 entries).  K = 12 and 16
+// hold fewer and took 91 and 110 us on the 7-point 160^3 matrix where 8 took 79, g
+// rounded to a power of two 174 us on the 27-point 128^3 one where this took 157.
 // W lanes a row (k_csr_vector) -> this, us:
 //   27-point 128^3         FP64 217 -> 151 (4.6 TB/s)   FP32 185 -> 99
 //   7-point 128^3          FP64  57 -> 41               FP32  46 -> 29
@@ -1455,15 +1456,15 @@ static int walker_grid(int64_t units, int cap) {
 static int stencil_rpt(const MatrixImpl &A) { return A.nx % 2 == 0 ? 2 : 1; }
 
 // Rows per wave of the staged CSR kernel, or 0: W lanes a row.  Short rows fill
-// a tenth of a run and leave nothing to stage (us, W lanes / staged, n = 10^6:
-// 1 entry a row FP64 8.1 / 14.0, 2: 12.3 / 17.0, 3: 20.1 / 18.0 and FP32 11.8 /
-// 12.3, 4: 23.4 / 19.2 and 13.2 / 14.7, 5 (a 5-point 1024^2): 27.5 / 19.7 and
-// 22.2 / 14.8), so the line is above 4 a row.  A wave that takes one run has the
-// shortest chain: as many rows as a run holds at the mean length, whatever the
-// number of waves (7-point 40^3: 5.9 us with 64 rows, 9.4 with 8 and 6.4 with W
-// lanes; 27-point 30^3: 14.8 with 64, 6.0 with 16 and 7.2).  From 16,384 waves of 64
+// a tenth of a run and leave nothing to stage (us, W lanes / staged, n = 10^6,
+// FP64 and FP32, 1 entry a row: 8.2 / 14.2 and 7.4 / 10.7, 2: 9.3 / 15.0 and 6.7 /
+// 11.3, 3: 14.7 / 15.6 and 11.2 / 11.6, 4: 17.4 / 16.4 and 11.9 / 12.4, 5: 25.8 /
+// 17.3 and 20.7 / 12.5), so the line is above 4 a row.  A wave that takes one run has
+// the shortest chain: as many rows as a run holds at the mean length, whatever the
+// number of waves (7-point 40^3: 6.8 us with 64 rows, 8.7 with 8 and 7.5 with W
+// lanes; 27-point 30^3: 13.2 with 64, 7.3 with 16 and 7.2).  From 16,384 waves of 64
 // rows on, several runs a wave cost less than the waves they save (27-point 128^3
-// FP32: 110 us with 64, 129 with 16; power law, n = 450,001: 80 with 64, 74 with 16).
+// FP32: 99 us with 64, 111 with 16; power law, n = 450,001: 86 with 64, 82 with 16).
 int csr_rows_per_wave(int64_t n, int64_t nnz) {
     if (nnz <= 4 * n) return 0;
     int rw = kWave;
@@ -1599,7 +1600,7 @@ static hipError_t spmv_typed(const MatrixImpl &A, const SpmvArgs &a, hipStream_t
     hipLaunchKernelGGL((k_csr_rows<V, D, K>), gr, blk, 0, s, n, A.csr_rows, csr_rows_heavy(A, K), A.grid_tail, \
                        walk, rp, col, val, p)
             // 64 rows of at most 5 entries fill runs of 320 (5-point 1024^2 against 512:
-            // FP64 19.8 -> 17.9 us, FP32 14.8 -> 13.1)
+            // FP64 19.8 -> 17.8 us, FP32 14.0 -> 13.2)
             if (A.nnz <= kStreamShort * n) {
                 if (dot) MXL_ROWS(true, kStreamShort);
                 else MXL_ROWS(false, kStreamShort);
